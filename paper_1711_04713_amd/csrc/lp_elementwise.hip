@@ -18,6 +18,40 @@ static int grid_for(size_t groups)
     return (int)blocks;
 }
 
+// Adds a block's counts to the caller's counters (either may be null): the waves' totals meet in LDS
+// and the block issues one atomic per counter.  The atomics of a launch all hit one address and are
+// served one after the other, about 5.5 ns each: with one per wave (16 k of them) a counting
+// lp_quantize of 25.7 M elements took 208 us instead of 31, a counting lp_act_stochastic of 6.4 M 157.
+template <int THREADS>
+__device__ __forceinline__ void add_block_counts(unsigned zeros, unsigned sats, unsigned long long *zero_count,
+                                                 unsigned long long *sat_count)
+{
+    __shared__ unsigned part[2][THREADS / 64];
+    if ((threadIdx.x & 63) == 0) {
+        part[0][threadIdx.x >> 6] = zeros;
+        part[1][threadIdx.x >> 6] = sats;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned total = 0;
+        for (int w = 0; w < THREADS / 64; ++w) total += part[threadIdx.x][w];
+        unsigned long long *out = threadIdx.x ? sat_count : zero_count;
+        if (out && total) atomicAdd(out, (unsigned long long)total);
+    }
+}
+
+// Counting launches: one block of sixteen waves per CU, so that at most 256 atomics per counter
+// are left and hide behind the streaming.  Measured on 25.7 M / 5.1 M elements, lp_quantize with
+// counters: 256 x 1024 threads 29 / 11 us, 512 x 512 30 / 12, 512 x 256 36 / 12.5, 1024 x 256 37 / 17,
+// 2048 x 256 43 / 29 (without counters 28 / 8).
+constexpr int kCountBlocks = 256;
+constexpr int kCountThreads = 1024;
+
+static int count_grid(size_t groups)
+{
+    return (int)std::min<size_t>(std::max<size_t>((groups + kCountThreads - 1) / kCountThreads, 1), kCountBlocks);
+}
+
 // ------------------------------------------------------------------ Philox4x32-10
 // Counter-based generator of Salmon, Moraes, Dror, Shaw (SC'11): ten rounds of two
 // 32x32->64 multiplies and xors, key bumped by the Weyl constants each round.  One block gives four
@@ -76,49 +110,43 @@ __device__ __forceinline__ int quantize_one(float x, float scale, float lo, floa
 }
 
 template <typename OutT, int MODE, bool COUNT>
-__global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restrict__ x,
+__global__ __launch_bounds__(COUNT ? kCountThreads : kThreads) void quantize_kernel(const float *__restrict__ x,
                                                            OutT *__restrict__ y, size_t count,
                                                            float scale, float lo, float hi,
                                                            uint64_t seed,
                                                            unsigned long long *zero_count,
                                                            unsigned long long *sat_count)
 {
-    const size_t groups = count / 8;
+    constexpr int THREADS = COUNT ? kCountThreads : kThreads;
+    const size_t groups = count / 8, stride = (size_t)gridDim.x * THREADS;
     unsigned zeros = 0, sats = 0; // wave-uniform running totals
-    // lane 0 of a wave has the smallest index, so it runs every iteration any lane of its
-    // wave runs and its running totals see every ballot
-    for (size_t g = (size_t)blockIdx.x * kThreads + threadIdx.x; g < groups;
-         g += (size_t)gridDim.x * kThreads) {
+    auto take = [&](size_t g, const v4f &a, const v4f &b) __attribute__((always_inline)) {
         int c[8];
         bool z[8], s[8];
-        {
-            const v4f a = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(x) + 2 * g);
-            const v4f b = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(x) + 2 * g + 1);
-            const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-            // elements 8g .. 8g+7 draw the words of blocks 2g and 2g+1
-            PhiloxBlock d0 = {}, d1 = {};
-            if constexpr (MODE == LP_ROUND_STOCHASTIC) {
-                d0 = philox4x32_10(2 * g, seed);
-                d1 = philox4x32_10(2 * g + 1, seed);
-            }
+        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        // elements 8g .. 8g+7 draw the words of blocks 2g and 2g+1
+        PhiloxBlock d0 = {}, d1 = {};
+        if constexpr (MODE == LP_ROUND_STOCHASTIC) {
+            d0 = philox4x32_10(2 * g, seed);
+            d1 = philox4x32_10(2 * g + 1, seed);
+        }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                c[j] = quantize_one<MODE>(v[j], scale, lo, hi, j < 4 ? d0.w[j & 3] : d1.w[j & 3], s[j]);
-                z[j] = (c[j] == 0);
-            }
-            if (sizeof(OutT) == 2) {
-                v4i o;
-                o.x = (c[0] & 0xffff) | (c[1] << 16);
-                o.y = (c[2] & 0xffff) | (c[3] << 16);
-                o.z = (c[4] & 0xffff) | (c[5] << 16);
-                o.w = (c[6] & 0xffff) | (c[7] << 16);
-                reinterpret_cast<v4i *>(y)[g] = o;
-            } else {
-                v2i o;
-                o.x = (c[0] & 0xff) | ((c[1] & 0xff) << 8) | ((c[2] & 0xff) << 16) | (c[3] << 24);
-                o.y = (c[4] & 0xff) | ((c[5] & 0xff) << 8) | ((c[6] & 0xff) << 16) | (c[7] << 24);
-                reinterpret_cast<v2i *>(y)[g] = o;
-            }
+        for (int j = 0; j < 8; ++j) {
+            c[j] = quantize_one<MODE>(v[j], scale, lo, hi, j < 4 ? d0.w[j & 3] : d1.w[j & 3], s[j]);
+            z[j] = (c[j] == 0);
+        }
+        if (sizeof(OutT) == 2) {
+            v4i o;
+            o.x = (c[0] & 0xffff) | (c[1] << 16);
+            o.y = (c[2] & 0xffff) | (c[3] << 16);
+            o.z = (c[4] & 0xffff) | (c[5] << 16);
+            o.w = (c[6] & 0xffff) | (c[7] << 16);
+            reinterpret_cast<v4i *>(y)[g] = o;
+        } else {
+            v2i o;
+            o.x = (c[0] & 0xff) | ((c[1] & 0xff) << 8) | ((c[2] & 0xff) << 16) | (c[3] << 24);
+            o.y = (c[4] & 0xff) | ((c[5] & 0xff) << 8) | ((c[6] & 0xff) << 16) | (c[7] << 24);
+            reinterpret_cast<v2i *>(y)[g] = o;
         }
         if (COUNT) {
 #pragma unroll
@@ -127,6 +155,30 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restr
                 sats += wave_count(s[j]);
             }
         }
+    };
+    auto load = [&](size_t g, v4f &a, v4f &b) __attribute__((always_inline)) {
+        a = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(x) + 2 * g);
+        b = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(x) + 2 * g + 1);
+    };
+    // The condition of the unrolled loop is the same for a whole wave (its last lane's), and in the
+    // loop after it lane 0 has the smallest index: lane 0 runs every iteration any lane of its wave
+    // runs and its running totals see every ballot.
+    size_t g = (size_t)blockIdx.x * THREADS + threadIdx.x;
+    const size_t to_last = 63 - (threadIdx.x & 63);
+    // groups in flight per thread: the generator's arithmetic leaves gaps in the request stream that a
+    // second group fills (25.7 M elements with counters: 39 -> 35 us); the other modes need none
+    constexpr int U = MODE == LP_ROUND_STOCHASTIC ? 2 : 1;
+    for (; g + to_last + (U - 1) * stride < groups; g += U * stride) {
+        v4f a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) load(g + u * stride, a[u], b[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) take(g + u * stride, a[u], b[u]);
+    }
+    for (; g < groups; g += stride) {
+        v4f a, b;
+        load(g, a, b);
+        take(g, a, b);
     }
     // ragged tail (fewer than 8 elements): first wave of block 0
     if (blockIdx.x == 0 && threadIdx.x < 64) {
@@ -142,23 +194,19 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restr
             sats += wave_count(s);
         }
     }
-    if (COUNT && (threadIdx.x & 63) == 0) {
-        if (zero_count && zeros) atomicAdd(zero_count, (unsigned long long)zeros);
-        if (sat_count && sats) atomicAdd(sat_count, (unsigned long long)sats);
-    }
+    if (COUNT) add_block_counts<THREADS>(zeros, sats, zero_count, sat_count);
 }
 
 template <typename OutT, int MODE>
 static void launch_quantize(const float *x, void *y, size_t count, float scale, float lo, float hi,
                             uint64_t seed, uint64_t *zc, uint64_t *sc, hipStream_t st)
 {
-    const int grid = grid_for(count / 8);
     if (zc || sc)
-        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true>), dim3(grid), dim3(kThreads), 0, st, x,
+        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true>), dim3(count_grid(count / 8)), dim3(kCountThreads), 0, st, x,
                            (OutT *)y, count, scale, lo, hi, seed, (unsigned long long *)zc,
                            (unsigned long long *)sc);
     else
-        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, false>), dim3(grid), dim3(kThreads), 0, st, x,
+        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, false>), dim3(grid_for(count / 8)), dim3(kThreads), 0, st, x,
                            (OutT *)y, count, scale, lo, hi, seed, nullptr, nullptr);
 }
 
@@ -351,50 +399,49 @@ __device__ __forceinline__ int act_one_stochastic(int64_t v, const ActParams &p,
     return (int)r;
 }
 
-template <typename OutT, bool STOCH>
-__global__ __launch_bounds__(kThreads) void act_kernel(const int64_t *__restrict__ acc,
+template <typename OutT, bool STOCH, bool COUNT>
+__global__ __launch_bounds__(COUNT ? kCountThreads : kThreads) void act_kernel(const int64_t *__restrict__ acc,
                                                       OutT *__restrict__ y, size_t count,
                                                       ActParams p, uint64_t seed,
                                                       unsigned long long *zero_count,
                                                       unsigned long long *sat_count)
 {
-    // counts are kept when either counter is wanted; a wave's totals are scalars
-    const bool counting = zero_count || sat_count;
-    unsigned sats = 0;
+    constexpr int THREADS = COUNT ? kCountThreads : kThreads;
+    unsigned sats = 0; // a wave's totals are scalars
     // w: the element's draw (stochastic scheme only)
     auto one = [&](int64_t v, uint32_t w, bool &sat) {
         if constexpr (STOCH) return act_one_stochastic(v, p, w, sat);
         else return act_one(v, p, sat);
     };
     auto draw = [&](size_t index) { return STOCH ? philox_draw(index, seed) : 0u; };
-    // A block takes 8 * kThreads consecutive accumulators per trip, as four rows of kThreads
+    // A block takes 8 * THREADS consecutive accumulators per trip, as four rows of THREADS
     // 16-byte pairs: a lane's loads are 16 bytes apart from its neighbours' (1 KB contiguous per
     // wave and instruction), and it stores the two codes of each pair (4 or 2 bytes, again
     // contiguous over the wave).
     const size_t groups = count / 8;            // whole groups of 8; the rest is handled below
-    const size_t trips = groups / kThreads;     // whole block trips
+    const size_t trips = groups / THREADS;     // whole block trips
     unsigned zeros = 0;
     for (size_t t = blockIdx.x; t < trips; t += gridDim.x) {
-        const size_t pair0 = t * (4 * kThreads) + threadIdx.x;
+        const size_t pair0 = t * (4 * THREADS) + threadIdx.x;
         v4i a[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            a[j] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(acc) + pair0 + j * kThreads);
+            a[j] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(acc) + pair0 + j * THREADS);
         // Elements 2 * pair and 2 * pair + 1 draw two neighbouring words of block pair / 2, which a
         // lane shares with its neighbour (lanes 2k and 2k + 1 hold pairs 2m and 2m + 1 in every
         // row).  The even lane computes the blocks of rows 0 and 2, the odd lane those of rows 1
         // and 3, and each hands the other its half of the words: two blocks per lane, not four.
-        const unsigned par = threadIdx.x & 1u; // = pair & 1 in every row (kThreads is even)
+        const unsigned par = threadIdx.x & 1u; // = pair & 1 in every row (THREADS is even)
         PhiloxBlock blk[2] = {};
         if constexpr (STOCH) {
-            blk[0] = philox4x32_10((pair0 + par * kThreads) >> 1, seed);
-            blk[1] = philox4x32_10((pair0 + (2 + par) * kThreads) >> 1, seed);
+            blk[0] = philox4x32_10((pair0 + par * THREADS) >> 1, seed);
+            blk[1] = philox4x32_10((pair0 + (2 + par) * THREADS) >> 1, seed);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int64_t a0 = (int64_t)(((uint64_t)(uint32_t)a[j].y << 32) | (uint32_t)a[j].x);
             const int64_t a1 = (int64_t)(((uint64_t)(uint32_t)a[j].w << 32) | (uint32_t)a[j].z);
-            const size_t pair = pair0 + j * kThreads;
+            const size_t pair = pair0 + j * THREADS;
             bool s0, s1;
             uint32_t w0 = 0, w1 = 0;
             if constexpr (STOCH) {
@@ -411,7 +458,7 @@ __global__ __launch_bounds__(kThreads) void act_kernel(const int64_t *__restrict
                 reinterpret_cast<int *>(y)[pair] = (c0 & 0xffff) | (c1 << 16);
             else
                 reinterpret_cast<short *>(y)[pair] = (short)((c0 & 0xff) | (c1 << 8));
-            if (counting) {
+            if constexpr (COUNT) {
                 zeros += wave_count(c0 == 0) + wave_count(c1 == 0);
                 sats += wave_count(s0) + wave_count(s1);
             }
@@ -419,7 +466,7 @@ __global__ __launch_bounds__(kThreads) void act_kernel(const int64_t *__restrict
     }
     // the groups that do not fill a block trip: one group of 8 per thread of block 0
     if (blockIdx.x == 0) {
-        const size_t g = trips * kThreads + threadIdx.x;
+        const size_t g = trips * THREADS + threadIdx.x;
         bool z[8] = {false, false, false, false, false, false, false, false};
         bool st[8] = {false, false, false, false, false, false, false, false};
         if (g < groups) {
@@ -430,7 +477,7 @@ __global__ __launch_bounds__(kThreads) void act_kernel(const int64_t *__restrict
                 z[j] = (c == 0);
             }
         }
-        if (counting) {
+        if constexpr (COUNT) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 zeros += wave_count(z[j]);
@@ -446,15 +493,12 @@ __global__ __launch_bounds__(kThreads) void act_kernel(const int64_t *__restrict
             y[i] = (OutT)c;
             z = (c == 0);
         }
-        if (counting) {
+        if constexpr (COUNT) {
             zeros += wave_count(z);
             sats += wave_count(st);
         }
     }
-    if ((threadIdx.x & 63) == 0) {
-        if (zero_count && zeros) atomicAdd(zero_count, (unsigned long long)zeros);
-        if (sat_count && sats) atomicAdd(sat_count, (unsigned long long)sats);
-    }
+    if constexpr (COUNT) add_block_counts<THREADS>(zeros, sats, zero_count, sat_count);
 }
 
 // ------------------------------------------------------------------------- maxpool
@@ -590,17 +634,29 @@ static lp_status act_launch(const int64_t *acc_dev, size_t count, int f_acc, lp_
     hipStream_t st = as_stream(stream);
     clear_stale_error();
     const ActParams p = make_act_params(f_acc, qy, relu, r);
-    const int grid = grid_for(count / 8); // one trip of the kernel's loop per block, up to the cap
-#define LP_A(T, STOCH) \
-    hipLaunchKernelGGL((act_kernel<T, STOCH>), dim3(grid), dim3(kThreads), 0, st, acc_dev, \
-                       (T *)y_codes_dev, count, p, seed, (unsigned long long *)zero_count_dev, \
-                       (unsigned long long *)sat_count_dev)
+    // one trip of the kernel's loop per block, up to the cap
+    const bool counting = zero_count_dev || sat_count_dev;
+    const int grid = counting ? count_grid(count / 8) : grid_for(count / 8);
+#define LP_A(T, STOCH)                                                                                        \
+    if (counting)                                                                                             \
+        hipLaunchKernelGGL((act_kernel<T, STOCH, true>), dim3(grid), dim3(kCountThreads), 0, st, acc_dev,     \
+                           (T *)y_codes_dev, count, p, seed, (unsigned long long *)zero_count_dev,            \
+                           (unsigned long long *)sat_count_dev);                                              \
+    else                                                                                                      \
+        hipLaunchKernelGGL((act_kernel<T, STOCH, false>), dim3(grid), dim3(kThreads), 0, st, acc_dev,         \
+                           (T *)y_codes_dev, count, p, seed, nullptr, nullptr)
     if (r == LP_ROUND_STOCHASTIC) {
-        if (qy.n > 8) LP_A(int16_t, true);
-        else LP_A(int8_t, true);
+        if (qy.n > 8) {
+            LP_A(int16_t, true);
+        } else {
+            LP_A(int8_t, true);
+        }
     } else {
-        if (qy.n > 8) LP_A(int16_t, false);
-        else LP_A(int8_t, false);
+        if (qy.n > 8) {
+            LP_A(int16_t, false);
+        } else {
+            LP_A(int8_t, false);
+        }
     }
 #undef LP_A
     return launch_status();

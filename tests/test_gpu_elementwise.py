@@ -51,6 +51,37 @@ def test_quantize_config_tensors(oracle):
         assert np.array_equal(got, want) and (gz, gs) == (wz, ws)
 
 
+@pytest.mark.parametrize("count", [8 * 1024 * 256 - 8, 8 * 1024 * 256 + 3, 2 * 8 * 1024 * 256 + 8 * 37 + 5, 3 * 8 * 1024 * 256 + 8])
+def test_counts_of_many_trips(count):
+    """Sizes at which the counting kernels' blocks take one, two or three trips and the last trip ends
+    inside a wave: codes equal those of the kernels without counters, zeros those among the codes,
+    clipped values the planted ones (far outside the range: clipped under every rounding)."""
+    rng = np.random.default_rng(count)
+    x = (rng.standard_normal(count) * 0.5).astype(np.float32)     # |x| stays below 8 = the range of Q4.12
+    planted = rng.integers(0, count, 5000)
+    x[planted] = 9.0
+    clipped = len(np.unique(planted))
+    xd = to_dev(x)
+    acc = torch.round(xd * (1 << 20)).to(torch.int64)
+    for r in (lp.LP_ROUND_NEAREST_AWAY, lp.LP_ROUND_NEAREST_EVEN, lp.LP_ROUND_STOCHASTIC):
+        for q in ((16, 4, 12), (8, 4, 4)):
+            plain, counted = (torch.empty(count, dtype=code_torch_dtype(q[0]), device="cuda") for _ in range(2))
+            z, s = counter(), counter()
+            lp.lp_quantize(xd, plain, q, r, seed=3)
+            lp.lp_quantize(xd, counted, q, r, seed=3, zero_count=z, sat_count=s)
+            assert torch.equal(plain, counted)
+            assert (int(z.item()), int(s.item())) == (int((plain == 0).sum().item()), clipped)
+            z, s = counter(), counter()
+            if r == lp.LP_ROUND_STOCHASTIC:
+                lp.lp_act_stochastic(acc, 20, q, True, 3, plain)
+                lp.lp_act_stochastic(acc, 20, q, True, 3, counted, zero_count=z, sat_count=s)
+            else:
+                lp.lp_act(acc, 20, q, True, plain, r)
+                lp.lp_act(acc, 20, q, True, counted, r, zero_count=z, sat_count=s)
+            assert torch.equal(plain, counted)
+            assert (int(z.item()), int(s.item())) == (int((plain == 0).sum().item()), clipped)
+
+
 def test_quantize_rejects_bad_arguments():
     x = torch.zeros(64, device="cuda")
     y = torch.zeros(64, dtype=torch.int16, device="cuda")

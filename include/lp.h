@@ -76,7 +76,8 @@ const char *lp_status_string(lp_status s);
  * m in [1, n] whose lost share (lost / count) is <= loss_threshold (m = n if
  * none); loss_threshold 0 places the point from max|v|.  NaN is never lost,
  * +-Inf always.  lost_host (nullable) receives n+1 counts, lost_host[m] for
- * m = 1..n (entry 0 unused).  workspace_dev: LP_RANGE_WORKSPACE_WORDS uint64.
+ * m = 1..n (entry 0 unused).  workspace_dev: LP_RANGE_WORKSPACE_WORDS uint64
+ * of scratch (required; nothing is to be read from it afterwards).
  * Synchronises the stream.  count == 0 yields m = 1.
  */
 lp_status lp_range(const float *x_dev, size_t count, int n, double loss_threshold,

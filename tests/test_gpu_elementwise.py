@@ -187,6 +187,32 @@ def test_range_matches_oracle(oracle, count, scale):
             assert lost[1:] == [int(v) for v in want_lost[1:]]
 
 
+def test_range_calls_from_many_threads_and_streams(oracle):
+    """More calls in flight than there are result slots: every thread, on a stream of its own, gets
+    the counts of its own tensor, several times over."""
+    import threading
+
+    xs = [_mixed_values(5000 + 977 * i, i, 2.0 ** (i % 9)) for i in range(40)]
+    want = [oracle.range_float(x, 16) for x in xs]
+    xd = [to_dev(x) for x in xs]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(5):
+                fmt, lost = lp.lp_range(xd[i], 16)
+                if fmt.m != want[i][0] or list(lost[1:17]) != [int(v) for v in want[i][1][1:17]]:
+                    wrong.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(xs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+
+
 def test_range_infinity_is_always_lost(oracle):
     x = np.array([0.5, np.inf, -0.25, 0.0], np.float32)
     fmt, lost = lp.lp_range(to_dev(x), 16, 0.0)

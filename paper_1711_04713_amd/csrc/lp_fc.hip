@@ -28,6 +28,7 @@
 //     sums combined to one int64 per output, and fc_finish_kernel adds the parts (integer sums:
 //     order cannot matter) and runs the same tile epilogue as the convolution.
 #include <algorithm>
+#include <type_traits>
 
 #include "lp_tile.h"
 
@@ -40,6 +41,7 @@ constexpr int FRAG = 1024;     // bytes of one MFMA operand fragment: 64 lanes x
 constexpr int kFcThreads = 512;
 constexpr int FMAXP = 8;       // most parts the reduction is cut into
 constexpr int FKC = 32;        // most K chunks the input split works in (one partial row sum each)
+constexpr int kFewBlocks = 2;  // most 32-row blocks of the few-rows kernel
 
 struct FcPlan {
     int limbs;
@@ -48,6 +50,7 @@ struct FcPlan {
     int n_tiles, m_tiles, tiles, ksplit, khp; // khp: K halves per part (a multiple of FSK)
     int kc, khc;               // input split: K chunks and K halves per chunk (a multiple of 16)
     int per_xcd, grid;
+    int few;                   // few input rows: fc_few_rows_kernel with this many 32-row blocks (0: the tiled kernels)
     size_t wslab;              // packed weight bytes of one 64-column tile
     size_t corr_offset, packed_bytes;
     size_t part_bytes;
@@ -95,6 +98,11 @@ static lp_status make_fc_plan(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw, Fc
     p.ws_xsum = round_up((size_t)p.kc * p.mblocks * 32 * sizeof(int), 256);
     p.ws_parts = p.ksplit > 1 ? (size_t)p.tiles * p.ksplit * p.part_bytes : 0;
     p.ws_total = p.ws_counts + p.ws_xs + p.ws_xsum + p.ws_parts;
+    if (p.mblocks <= kFewBlocks) {
+        p.few = p.mblocks;
+        p.grid = (Nout + 31) / 32;
+        p.ws_total = 256; // nothing to split, nothing to merge
+    }
     *out = p;
     return LP_OK;
 }
@@ -518,6 +526,224 @@ __global__ __launch_bounds__(kFcThreads) void fc_finish_kernel(const FcArgs f)
     }
 }
 
+// ------------------------------------------------------------------- few input rows
+//
+// One image, or a small batch: the weights are read for so few rows that the call is bound by their way
+// out of HBM.  The tiled kernel computes 256 rows whatever M is, and its launch is framed by the input
+// split and the finishing kernel (one row through 25088 -> 4096 -> 4096 -> 1000: 139 us, of which 45
+// frame).  Here a workgroup owns 32 output columns over the whole reduction: its waves take the K = 32
+// halves in turn, weight fragments go from HBM straight into MFMA operands (nobody else wants them, so
+// LDS would only be a detour), input codes are split into limbs on the way into theirs, and the waves'
+// sums meet once, in LDS.  One launch, no workspace.  FEW_DEPTH requests per wave keep the memory
+// busy: 16 waves x 3 halves x 2 KB = 96 KB per workgroup in flight.
+// RB: 32-row blocks (2: half the waves, as a wave then holds 96 accumulators).  VEC: every row starts
+// on a 4-byte boundary, so that codes can be fetched 16 bytes at a time.
+constexpr int kFewDepth = 3;
+template <int RB> constexpr int few_waves() { return RB == 1 ? 16 : 8; }
+
+template <int LIMBS, int RB, bool VEC>
+__global__ __launch_bounds__(64 * few_waves<RB>()) void fc_few_rows_kernel(const FcArgs f)
+{
+    constexpr int WAVES = few_waves<RB>(), D = kFewDepth;
+    constexpr int NACC = LIMBS == 2 ? 3 : 1;
+    constexpr int ESZ = LIMBS == 2 ? 2 : 1;
+    constexpr int XL = LIMBS == 2 ? 2 : 1;       // 16-byte pieces of a lane's sixteen codes
+    constexpr int PIECES = LIMBS == 2 ? 8 : 4;   // 16-byte pieces of a lane's sums per 32-row block
+    typedef typename std::conditional<LIMBS == 2, long long, int>::type sum_t;
+    __shared__ v4i sums[WAVES][RB][PIECES][64];
+    __shared__ int rowpart[WAVES][RB][32];
+    __shared__ long long colterm[32];
+    __shared__ unsigned wave_counts[2][WAVES];
+    const ConvArgs &a = f.c;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
+    const int col0 = blockIdx.x * 32, nt = blockIdx.x >> 1, cb = blockIdx.x & 1;
+    if (tid < 32) {
+        const int col = col0 + tid;
+        colterm[tid] = col < a.Cout ? a.corr[col] + bias_term(a, col) : 0;
+    }
+    constexpr int KHB = LIMBS * 2 * FRAG; // weight bytes of one K half of a 64-column tile
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<unsigned char *>(a.wp) + (size_t)nt * f.wslab, 0, (int)f.wslab, 0x00020000);
+    // (rounded up to a whole word: the word that holds the last code is readable to its end)
+    const __amdgpu_buffer_rsrc_t xrsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, (f.M * f.K * ESZ + 3) & ~3, 0x00020000);
+    // a lane's codes: row l32 of each block, sixteen positions; rows past M and K halves past the end lie
+    // outside the descriptors and read as zeros
+    constexpr unsigned NOWHERE = 0x80000000u;
+    unsigned xrow[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) xrow[rb] = rb * 32 + l32 < f.M ? (unsigned)((rb * 32 + l32) * f.K + kg * 16) * ESZ : NOWHERE;
+    unsigned xshift[RB]; // bytes by which a lane's codes miss a 4-byte boundary: the same for every K half
+    if constexpr (!VEC)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            xshift[rb] = xrow[rb] & 3u;
+            xrow[rb] &= ~3u;
+        }
+    v4i w[D][LIMBS], x[D][RB][XL];
+    int xnext[D][RB];
+    auto request = [&](int kh, int d) __attribute__((always_inline)) {
+        v4i (&wr)[LIMBS] = w[d];
+        v4i (&xr)[RB][XL] = x[d];
+#pragma unroll
+        for (int l = 0; l < LIMBS; ++l) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, kh * KHB + (l * 2 + cb) * FRAG + lane * 16, 0, 0);
+            wr[l] = (v4i){(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const unsigned at = kh < f.KH ? xrow[rb] + (unsigned)(kh * 32 * ESZ) : NOWHERE;
+#pragma unroll
+            for (int p = 0; p < XL; ++p) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)(at + 16u * p), 0, 0);
+                xr[rb][p] = (v4i){(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+            }
+            if constexpr (!VEC) xnext[d][rb] = (int)__builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)(at + 16u * XL), 0, 0);
+        }
+    };
+    // the sixteen codes of a row that does not start on a 4-byte boundary, out of the five (nine)
+    // words they lie in
+    auto realign = [&](int rb, v4i (&xr)[XL], int next) __attribute__((always_inline)) {
+        if constexpr (!VEC) {
+            const unsigned sh = xshift[rb];
+#pragma unroll
+            for (int p = 0; p < XL; ++p) {
+                const int after = p + 1 < XL ? xr[p + 1 < XL ? p + 1 : p].x : next;
+                const v4i c = xr[p];
+                xr[p] = (v4i){(int)__builtin_amdgcn_alignbyte((unsigned)c.y, (unsigned)c.x, sh), (int)__builtin_amdgcn_alignbyte((unsigned)c.z, (unsigned)c.y, sh),
+                              (int)__builtin_amdgcn_alignbyte((unsigned)c.w, (unsigned)c.z, sh), (int)__builtin_amdgcn_alignbyte((unsigned)after, (unsigned)c.w, sh)};
+            }
+        }
+    };
+    v16i acc[RB][NACC];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int q = 0; q < NACC; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[rb][q][v] = 0;
+    int sum[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) sum[rb] = 0;
+    auto multiply = [&](int kh, int d) __attribute__((always_inline)) {
+        const v4i (&wr)[LIMBS] = w[d];
+        v4i (&xr)[RB][XL] = x[d];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            realign(rb, xr[rb], VEC ? 0 : xnext[d][rb]);
+            if constexpr (LIMBS == 2) {
+                unsigned pr[8] = {(unsigned)xr[rb][0].x, (unsigned)xr[rb][0].y, (unsigned)xr[rb][0].z, (unsigned)xr[rb][0].w,
+                                  (unsigned)xr[rb][1].x, (unsigned)xr[rb][1].y, (unsigned)xr[rb][1].z, (unsigned)xr[rb][1].w};
+                if ((kh + 1) * 32 > f.K) { // (uniform) what follows the row's end meets zero weights but is no part of its sum
+                    const int nv = f.K - (kh * 32 + kg * 16);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const int m = min(max(nv - 2 * q, 0), 2);
+                        pr[q] &= m == 2 ? 0xffffffffu : m == 1 ? 0xffffu : 0u;
+                    }
+                }
+                unsigned h[4], l[4];
+                const v2s ones = {1, 1};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    h[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x07050301u);
+                    l[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x06040200u) ^ 0x80808080u;
+                    sum[rb] = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[2 * q]), ones, sum[rb], false);
+                    sum[rb] = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[2 * q + 1]), ones, sum[rb], false);
+                }
+                const v4i xh = {(int)h[0], (int)h[1], (int)h[2], (int)h[3]}, xl = {(int)l[0], (int)l[1], (int)l[2], (int)l[3]};
+                acc[rb][0] = mfma_i8(wr[0], xh, acc[rb][0]);
+                acc[rb][1] = mfma_i8(wr[1], xh, acc[rb][1]);
+                acc[rb][2] = mfma_i8(wr[1], xl, acc[rb][2]);
+                acc[rb][1] = mfma_i8(wr[0], xl, acc[rb][1]);
+            } else {
+                acc[rb][0] = mfma_i8(wr[0], xr[rb][0], acc[rb][0]);
+            }
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) request(wave + d * WAVES, d);
+    for (int kh = wave; kh < f.KH; kh += D * WAVES) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) { // (halves past the last one multiply zero weights)
+            multiply(kh + d * WAVES, d);
+            request(kh + (d + D) * WAVES, d);
+        }
+    }
+    // the waves' sums: one exact integer per output, in register order (see tile_epilogue for the
+    // layout: register 4 * g + e of a lane is channel 8 * g + 4 * kg + e of row l32)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        if (rb * 32 + l32 < f.M) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                if constexpr (LIMBS == 2) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const int v = 4 * g + 2 * h;
+                        const long long s0 = fc_combine(acc[rb][0][v], acc[rb][1][v], acc[rb][2][v]);
+                        const long long s1 = fc_combine(acc[rb][0][v + 1], acc[rb][1][v + 1], acc[rb][2][v + 1]);
+                        sums[wave][rb][2 * g + h][lane] = (v4i){(int)s0, (int)(s0 >> 32), (int)s1, (int)(s1 >> 32)};
+                    }
+                } else {
+                    sums[wave][rb][g][lane] = (v4i){acc[rb][0][4 * g], acc[rb][0][4 * g + 1], acc[rb][0][4 * g + 2], acc[rb][0][4 * g + 3]};
+                }
+            }
+        }
+        const int both = sum[rb] + __shfl_xor(sum[rb], 32, 64); // a row's two lanes hold different positions
+        if (kg == 0) rowpart[wave][rb][l32] = both;
+    }
+    __syncthreads();
+    // every wave finishes RB * 16 / WAVES registers of all lanes
+    unsigned zeros = 0, sats = 0;
+#pragma unroll
+    for (int i = 0; i < RB * 16 / WAVES; ++i) {
+        const int item = wave * (RB * 16 / WAVES) + i, rb = item >> 4, v = item & 15;
+        const int row = rb * 32 + l32, cl = 8 * (v >> 2) + 4 * kg + (v & 3), col = col0 + cl;
+        bool z = false, sat = false;
+        if (row < f.M && col < a.Cout) {
+            long long val = colterm[cl];
+            int rs = 0;
+#pragma unroll
+            for (int o = 0; o < WAVES; ++o) {
+                val += ((const sum_t *)&sums[o][rb][v * sizeof(sum_t) / 16][lane])[v % (16 / sizeof(sum_t))];
+                if constexpr (LIMBS == 2) rs += rowpart[o][rb][l32];
+            }
+            val += (long long)128 * rs;
+            const size_t idx = (size_t)row * a.Cout + col;
+            if (a.acc_out) a.acc_out[idx] = val;
+            if (a.y) {
+                const int c = act_one(val, a.act, sat);
+                if (a.y16) ((int16_t *)a.y)[idx] = (int16_t)c;
+                else ((int8_t *)a.y)[idx] = (int8_t)c;
+                z = c == 0;
+            }
+        }
+        zeros += wave_count(z);
+        sats += wave_count(sat);
+    }
+    if (!a.y || (!a.zero_count && !a.sat_count)) return;
+    if (lane == 0) {
+        wave_counts[0][wave] = zeros;
+        wave_counts[1][wave] = sats;
+    }
+    __syncthreads();
+    if (tid < 2) {
+        unsigned total = 0;
+        for (int i = 0; i < WAVES; ++i) total += wave_counts[tid][i];
+        unsigned long long *dst = tid ? a.sat_count : a.zero_count;
+        if (total && dst) atomicAdd(dst, (unsigned long long)total);
+    }
+}
+
+template <int LIMBS, int RB>
+static void launch_few_rows(const FcArgs &f, int grid, bool vec, hipStream_t hs)
+{
+    const dim3 block(64 * few_waves<RB>());
+    if (vec) hipLaunchKernelGGL((fc_few_rows_kernel<LIMBS, RB, true>), dim3(grid), block, 0, hs, f);
+    else hipLaunchKernelGGL((fc_few_rows_kernel<LIMBS, RB, false>), dim3(grid), block, 0, hs, f);
+}
+
 // ---------------------------------------------------------------------------- host
 
 static lp_status fc_pack(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw, const void *w, void *packed, size_t packed_bytes,
@@ -608,6 +834,13 @@ static lp_status fc_forward(int M, int K, int Nout, const void *x, lp_qfmt qx, c
     f.wslab = (unsigned)p.wslab;
     hipStream_t hs = as_stream(stream);
     clear_stale_error();
+    if (p.few) {
+        // 4-byte aligned rows (one row starts at the tensor's own, 16-byte aligned start)
+        const bool vec = M == 1 || (size_t)K * (p.limbs == 2 ? 2 : 1) % 4 == 0;
+        if (p.limbs == 2) p.few == 1 ? launch_few_rows<2, 1>(f, p.grid, vec, hs) : launch_few_rows<2, 2>(f, p.grid, vec, hs);
+        else p.few == 1 ? launch_few_rows<1, 1>(f, p.grid, vec, hs) : launch_few_rows<1, 2>(f, p.grid, vec, hs);
+        return launch_status();
+    }
     const dim3 sgrid(p.mblocks, p.kc);
     if (p.limbs == 2) {
         hipLaunchKernelGGL((fc_split_x_kernel<int16_t, 2>), sgrid, dim3(64 * kSplitWaves), 0, hs, (const int16_t *)x,

@@ -338,6 +338,24 @@ def test_fc_int8(oracle):
     assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
 
 
+@pytest.mark.parametrize("M", [1, 2, 31, 32, 33, 63, 64, 65])
+@pytest.mark.parametrize("K,Nout", [(16, 1), (31, 10), (33, 33), (500, 64), (1537, 97), (2049, 40)])
+def test_fc_few_rows(oracle, M, K, Nout):
+    """The few-rows kernel's edges: one and two 32-row blocks and the first size past them, rows that
+    start off a 4-byte boundary (odd K), reductions shorter than one turn of the waves and ending inside
+    a K half, ragged columns; 16-bit and 8-bit codes, both epilogues' options."""
+    rng = np.random.default_rng(M * 10007 + K)
+    for n, qx, qw, qy in ((16, QX, QW, (16, 14, 2)), (8, (8, 3, 5), (8, 1, 7), (8, 8, 0))):
+        x, w, bias = _codes(rng, (M, K), n=n, zero_frac=0.5), _codes(rng, (Nout, K), n=n), _codes(rng, (Nout,), n=n)
+        f_acc, qb = qx[2] + qw[2], (n, 1, n - 1)
+        want = oracle.fc(x, w, bias=bias, f_acc=f_acc, fb=n - 1)
+        for relu, r_gpu, r_cpu in ((True, lp.LP_ROUND_NEAREST_AWAY, oracle.ROUND_AWAY), (False, lp.LP_ROUND_NEAREST_EVEN, oracle.ROUND_EVEN)):
+            got = fc(x, qx, w, qw, qy=qy, relu=relu, r=r_gpu, bias=bias, qb=qb)
+            assert np.array_equal(got["acc"], want)
+            y, z, sat = oracle.act(want, f_acc, *qy, relu, r_cpu, with_sat=True)
+            assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
+
+
 def test_zero_count_needs_workspace_and_accumulates(oracle):
     import torch
     from gpu_helpers import to_dev

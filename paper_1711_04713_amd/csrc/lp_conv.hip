@@ -43,7 +43,8 @@ enum { PATH_DIRECT = 0, PATH_MFMA = 1 };
 struct Plan {
     int path;
     int pool;    // the epilogue stores 2x2 maxima instead of the codes
-    int limbs;   // 1: int8 x int8, 2: 16-bit x 16-bit
+    int limbs;   // 8-bit limbs of the activations: 1 (int8 codes) or 2 (16-bit codes)
+    int wl;      // of the weights: as limbs, but 1 for 8-bit weights under 16-bit activations on the patch kernel
     int flat;    // whole window gathered as one K <= 64 slab (tiny Cin)
     int rows;    // reduction over window rows (16-bit codes, 16 / 32 / 48 input channels): conv_rows_kernel
     int KHR, KHP; // rows: K = 32 pieces per window row, and in all (padded to a multiple of 4)
@@ -320,12 +321,15 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
         p.taps = one_slab ? 1 : d->R * d->S;
         p.ksteps = p.flat ? (int)((K + 31) / 32) : 2;
         p.CoutP = (int)round_up(d->Cout, 64);
+        p.wl = (p.limbs == 2 && !w16 && !one_slab) ? 1 : p.limbs;
         p.tiles_m = p.tiles_r * p.tiles_c;
         // 128-wide channel tiles halve the patch re-reads, but a grid with fewer workgroups than
         // the chip has slots (256 CUs x 2) is better cut finer
         p.BN = (p.CoutP % 128 == 0 && (long long)p.tiles_m * (p.CoutP / 128) >= 512) ? 128 : 64;
         // the two-limb kernel holds three accumulator sets; at 128 channels they leave too few
-        // registers for the prefetch pipeline, so it always runs 64-wide
+        // registers for the prefetch pipeline, so it always runs 64-wide.  With one-limb weights (two
+        // sets) 128 channels fit at two waves per SIMD instead of four and halve the fragment reads per
+        // MFMA: measured slower on VGG16 at batch 16 (conv2_2 78 against 69 us, conv3_2 67 against 62)
         if (p.limbs == 2) p.BN = 64;
         p.tiles_n = p.CoutP / p.BN;
         if (!p.rows) p.PITCH = p.flat ? 0 : 16 * choose_pitch(p.PW, p.TW, p.RH, d->R, d->S);
@@ -334,14 +338,14 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
         {
             // workgroup slots per die: what registers and LDS allow
             const int total = p.tiles_m * p.tiles_n, nslabs = p.nchunks * p.taps;
-            // (two-limb kernel: three waves per SIMD by registers; one-limb kernels: four)
+            // (two-limb weights: three waves per SIMD by registers; one-limb weights: four)
             // (window-row kernel: four, or three where it takes two column blocks)
-            const int by_regs = p.rows ? (d->Cout <= 32 ? 4 : 3) : p.limbs == 2 ? 3 : 4;
+            const int by_regs = p.rows ? (d->Cout <= 32 ? 4 : 3) : p.wl == 2 ? 3 : 4;
             const int wg_per_cu = (int)std::max<size_t>(1, std::min<size_t>(by_regs, (160 * 1024) / p.lds_bytes));
             const int slots = wg_per_cu * (kCUs / kXCDs);
             p.per_xcd = (total + kXCDs - 1) / kXCDs;
             p.full_per_xcd = p.per_xcd / slots * slots;
-            p.part_bytes = (size_t)BM * p.BN * (p.limbs == 2 ? 3 : 1) * 4 + (size_t)BM * 4;
+            p.part_bytes = (size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4 + (size_t)BM * 4;
             p.split = 1;
             if (p.per_xcd > p.full_per_xcd && nslabs > 1)
                 p.split = choose_split(p.per_xcd - p.full_per_xcd, slots, nslabs, p.part_bytes);
@@ -349,7 +353,7 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
             p.grid = kXCDs * (p.full_per_xcd + (p.per_xcd - p.full_per_xcd) * p.split);
         }
         p.corr_offset = p.rows ? round_up((size_t)p.KHP * 2 * p.CoutP * 32, 256)
-                               : round_up((size_t)p.taps * p.nchunks * p.limbs * p.CoutP * CK, 256);
+                               : round_up((size_t)p.taps * p.nchunks * p.wl * p.CoutP * CK, 256);
         // the kernel addresses the slabs with 32-bit byte offsets
         if (p.corr_offset >= (1ull << 31)) return LP_EUNSUPPORTED;
         p.packed_bytes = p.corr_offset + (size_t)p.CoutP * sizeof(int64_t);
@@ -523,12 +527,18 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(const ConvArgs a)
 
 // -------------------------------------------------------------------------- MFMA path
 
-// LIMBS: 1 (int8 codes) or 2 (16-bit codes as two int8 limbs).  NB: 32-column blocks per
+// LIMBS: 8-bit limbs of the activations, 1 (int8 codes) or 2 (16-bit codes); WL: of the weights (8-bit
+// weights under 16-bit activations: 2, 1; half the products of 2, 2 and no row sums: 73 instead of
+// 108 us on VGG16's conv2_2 and 71 instead of 104 on conv3_2 at batch 16, where the weights used to be
+// widened; what a workgroup does between its multiply loops does not shrink with them).  NB: 32-column blocks per
 // wave; the workgroup covers BN = 64*NB output channels with 2x2 waves of 64 x 32*NB each.
-template <int LIMBS, int NB, int MB>
+// Waves per SIMD the registers of the patch kernel are budgeted for: three with 96 accumulator
+// registers (two-limb weights), else four.
+constexpr int patch_waves(int wl, int mb) { return wl == 2 && mb == 2 ? 3 : 4; }
+
+template <int LIMBS, int WL, int NB, int MB>
 __global__ __launch_bounds__(MB == 2 ? 256 : 512)
-    __attribute__((amdgpu_waves_per_eu(MB == 2 && LIMBS == 2 ? 3 : 4, MB == 2 && LIMBS == 2 ? 3 : 4))) void conv_mfma_kernel(
-        const ConvArgs a)
+    __attribute__((amdgpu_waves_per_eu(patch_waves(WL, MB), patch_waves(WL, MB)))) void conv_mfma_kernel(const ConvArgs a)
 {
     // MB: 32-row blocks per wave.  MB = 2: 4 waves (2 x 2) of 64 rows, the only form launched.
     // MB = 1 (8 waves of 32 rows, a fourth wave per SIMD) is kept compilable as a tuning knob: with
@@ -538,7 +548,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
     constexpr int WMC = BM / (32 * MB);       // waves along the pixel dimension
     constexpr int WROWS = 32 * MB;            // tile rows per wave
     constexpr int BN = 64 * NB;
-    constexpr int NACC = (LIMBS == 2) ? 3 : 1;
+    constexpr int NACC = LIMBS + WL - 1;
     extern __shared__ __align__(16) unsigned char smem[];
 
     // XCD-aware work order: consecutive workgroup ids land on the 8 XCDs round-robin, so
@@ -613,7 +623,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
             abase_s[m] = ok ? (img * a.Hp + yo - vr0) * a.PW + t : 0;
             pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
         }
-        build_colterms<BN, THREADS>(a, ntile, ctab, LIMBS, deadmask);
+        build_colterms<BN, THREADS>(a, ntile, ctab, LIMBS, WL, deadmask);
     };
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WMC, wn = wave / WMC;
@@ -667,7 +677,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
     // the operand loads below).  t counts the slabs this workgroup multiplies.
     const int nslabs = (skipping ? __builtin_popcount(livemask) : a.nchunks) * a.taps;
     const int s0 = part * nslabs / nparts, s1 = (part + 1) * nslabs / nparts; // this workgroup's slabs
-    const int slab_bytes = LIMBS * a.CoutP * CK;
+    const int slab_bytes = WL * a.CoutP * CK;
     constexpr bool LATE_ROWS = LIMBS == 2; // (the one-limb kernels' 128 registers leave no room for the overlap)
     if constexpr (!LATE_ROWS) row_tables();
     __syncthreads(); // the patch tables are complete
@@ -731,15 +741,17 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
             hi.y = (int)__builtin_amdgcn_perm((unsigned)v.w, (unsigned)v.z, 0x07050301u);
             lo.x = (int)(__builtin_amdgcn_perm((unsigned)v.y, (unsigned)v.x, 0x06040200u) ^ 0x80808080u);
             lo.y = (int)(__builtin_amdgcn_perm((unsigned)v.w, (unsigned)v.z, 0x06040200u) ^ 0x80808080u);
-            // sum of the eight codes: four two-element dot products with (1, 1); each of a
-            // pixel's eight pieces adds its share to the pixel's sum
-            const v2s ones = {1, 1};
-            const int w0 = v.x, w1 = v.y, w2 = v.z, w3 = v.w;
-            int sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w0), ones, 0, false);
-            sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w1), ones, sum, false);
-            sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w2), ones, sum, false);
-            sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w3), ones, sum, false);
-            if (own_sums) atomicAdd(&psum[p], sum); // no value returned
+            if constexpr (WL == 2) {
+                // sum of the eight codes: four two-element dot products with (1, 1); each of a
+                // pixel's eight pieces adds its share to the pixel's sum
+                const v2s ones = {1, 1};
+                const int w0 = v.x, w1 = v.y, w2 = v.z, w3 = v.w;
+                int sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w0), ones, 0, false);
+                sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w1), ones, sum, false);
+                sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w2), ones, sum, false);
+                sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w3), ones, sum, false);
+                if (own_sums) atomicAdd(&psum[p], sum); // no value returned
+            }
             *(__attribute__((address_space(3))) v2i *)(unsigned)at = hi;
             *(__attribute__((address_space(3))) v2i *)(unsigned)(at + APL) = lo;
         } else {
@@ -838,7 +850,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
         for (int nb = 0; nb < NB; ++nb) {
             const auto vh = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, blane + nb * 32 * 32, slab_off, 0);
             h[nb] = (v4i){(int)vh[0], (int)vh[1], (int)vh[2], (int)vh[3]};
-            if constexpr (LIMBS == 2) {
+            if constexpr (WL == 2) {
                 const auto vl = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, blane + nb * 32 * 32, slab_off + limb_bytes, 0);
                 l[nb] = (v4i){(int)vl[0], (int)vl[1], (int)vl[2], (int)vl[3]};
             }
@@ -861,7 +873,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             acc[mb][nb][0] = mfma_i8(wh[nb], ah[mb], acc[mb][nb][0]);
-            if constexpr (LIMBS == 2) {
+            if constexpr (WL == 2) {
                 acc[mb][nb][1] = mfma_i8(wl[nb], ah[mb], acc[mb][nb][1]);
                 acc[mb][nb][2] = mfma_i8(wl[nb], al[mb], acc[mb][nb][2]);
             }
@@ -1030,7 +1042,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
                         mine[(((mb * NB + nb) * NACC + q) * 4 + g) * THREADS + tid] =
                             (v4i){c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
                     }
-        if constexpr (LIMBS == 2) {
+        if constexpr (WL == 2) {
             int *rs = (int *)(mine + MB * NB * NACC * 4 * THREADS);
             for (int m = tid; m < BM; m += THREADS) rs[m] = row_sum(m);
         }
@@ -1039,7 +1051,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
         return;
     }
 
-    const TileCounts counts = tile_epilogue<LIMBS, NB, BN, MB, 4>(a, acc, row_sum, outoff, pooloff, ctab, ntile, wm * WROWS,
+    const TileCounts counts = tile_epilogue<LIMBS, WL, NB, BN, MB, 4>(a, acc, row_sum, outoff, pooloff, ctab, ntile, wm * WROWS,
                                                                   wn * (NB * 32), 0, 0);
     // one pair of counts per workgroup; on large grids they go to per-workgroup slots, not to the
     // counters: thousands of same-address atomics would serialise
@@ -1071,12 +1083,12 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
 // 16-byte pieces per part, so the pieces of all parts are requested together and the memory
 // latency is paid once.  Zero counts go straight to the total (few workgroups); workgroup 0 also
 // adds the per-workgroup counts of the main kernel.
-template <int LIMBS, int NB, int MB>
+template <int LIMBS, int WL, int NB, int MB>
 __global__ __launch_bounds__(256) void conv_finish_kernel(const ConvArgs a, int main_grid)
 {
     constexpr int THREADS = 256;
     constexpr int BN = 64 * NB;
-    constexpr int NACC = (LIMBS == 2) ? 3 : 1;
+    constexpr int NACC = LIMBS + WL - 1;
     constexpr int SUB = 4 * MB;       // workgroups per tile
     constexpr int MAXP = 8;           // most parts a tile is cut into (see choose_split)
     __shared__ int outoff[BM];
@@ -1107,7 +1119,7 @@ __global__ __launch_bounds__(256) void conv_finish_kernel(const ConvArgs a, int 
 #pragma unroll
                 for (int q = 0; q < NACC; ++q)
                     piece[o][nb][q] = ((const v4i *)theirs)[((((mb0 * NB + nb) * NACC + q) * 4 + g0) * THREADS) + tid];
-            rsp[o] = (LIMBS == 2 && tid < BM) ? ((const int *)(theirs + (size_t)MB * NB * NACC * 4 * THREADS * 16))[tid] : 0;
+            rsp[o] = (WL == 2 && tid < BM) ? ((const int *)(theirs + (size_t)MB * NB * NACC * 4 * THREADS * 16))[tid] : 0;
         }
         for (int m = tid; m < BM; m += THREADS) {
             const int j = m / a.TW, t = m % a.TW;
@@ -1117,7 +1129,7 @@ __global__ __launch_bounds__(256) void conv_finish_kernel(const ConvArgs a, int 
             pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1))
                              ? ((fr / a.Ho) * (a.Ho >> 1) + ((fr % a.Ho) >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
         }
-        build_colterms<BN, THREADS>(a, ntile, ctab, LIMBS);
+        build_colterms<BN, THREADS>(a, ntile, ctab, LIMBS, WL);
         v16i acc[1][NB][NACC];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
@@ -1146,7 +1158,7 @@ __global__ __launch_bounds__(256) void conv_finish_kernel(const ConvArgs a, int 
         // same wave arrangement as the main kernel: BM / (32 * MB) waves along the pixels
         constexpr int WMC = BM / (32 * MB);
         const int wave = tid >> 6;
-        const TileCounts counts = tile_epilogue<LIMBS, NB, BN, 1, 1>(
+        const TileCounts counts = tile_epilogue<LIMBS, WL, NB, BN, 1, 1>(
             a, acc, [&](int m) { return rowsum[m]; }, outoff, pooloff, ctab, ntile, (wave % WMC) * (32 * MB),
             (wave / WMC) * (NB * 32), mb0, g0);
         if (a.zout) {
@@ -1313,7 +1325,7 @@ __global__ __launch_bounds__(256)
         abase[m] = ok ? ((img * a.Hp + yo - vr0) * a.PW + t) * a.Cin * 2 : 0;
         pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
     }
-    build_colterms<BN, THREADS>(a, ntile, ctab, 2);
+    build_colterms<BN, THREADS>(a, ntile, ctab, 2, 2);
 #pragma unroll
     for (int i = 0; i < WPT; ++i)
         if (wave + 4 * i < WPIECES) wlds[wave + 4 * i][lane] = wreg[i];
@@ -1376,7 +1388,7 @@ __global__ __launch_bounds__(256)
             acc[0][0][2] = mfma_i8(wl, al[h], acc[0][0][2]);
             acc[0][0][1] = mfma_i8(wh, al[h], acc[0][0][1]);
         }
-        const TileCounts c = tile_epilogue<2, 1, BN, 1, 4>(
+        const TileCounts c = tile_epilogue<2, 2, 1, BN, 1, 4>(
             a, acc, [&](int) { return rowsum; }, outoff, pooloff, ctab, ntile, wave * 32, cb * 32, 0, 0);
         counts.zeros += c.zeros;
         counts.sats += c.sats;
@@ -1518,7 +1530,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         ubase[m] = ok ? prow * a.UPR + t * a.CU : 0;
         pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
     }
-    build_colterms<BN, THREADS>(a, ntile, ctab, 2);
+    build_colterms<BN, THREADS>(a, ntile, ctab, 2, 2);
     __syncthreads();
 
     // the sum of the codes under the row's window: its two lanes take alternate window rows
@@ -1568,7 +1580,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
             step(h + 2, integral_constant<int, 2>{});
             step(h + 3, integral_constant<int, 3>{});
         }
-        const TileCounts c = tile_epilogue<2, 1, BN, 1, 4>(
+        const TileCounts c = tile_epilogue<2, 2, 1, BN, 1, 4>(
             a, acc, [&](int) { return rowsum; }, outoff, pooloff, ctab, ntile, wave * 32, cb * 32, 0, 0);
         counts.zeros += c.zeros;
         counts.sats += c.sats;
@@ -1603,7 +1615,7 @@ lp_status launch_sum_partials(const unsigned *partials, int n, unsigned long lon
     return launch_status();
 }
 
-template <int LIMBS, int NB, int MB>
+template <int LIMBS, int WL, int NB, int MB>
 static lp_status launch_mfma(const ConvArgs &a, const Plan &p, int grid, int tails, hipStream_t st)
 {
     // raise the dynamic LDS limit once per kernel instance and device
@@ -1611,15 +1623,15 @@ static lp_status launch_mfma(const ConvArgs &a, const Plan &p, int grid, int tai
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return LP_EDEVICE;
     if (!attr_set[dev].load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute((const void *)conv_mfma_kernel<LIMBS, NB, MB>,
+        if (hipFuncSetAttribute((const void *)conv_mfma_kernel<LIMBS, WL, NB, MB>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
             return LP_EDEVICE;
         attr_set[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((conv_mfma_kernel<LIMBS, NB, MB>), dim3(grid), dim3(MB == 2 ? 256 : 512),
+    hipLaunchKernelGGL((conv_mfma_kernel<LIMBS, WL, NB, MB>), dim3(grid), dim3(MB == 2 ? 256 : 512),
                        p.lds_bytes, st, a);
     if (tails) // the split tail tiles are merged and written by a second, small kernel
-        hipLaunchKernelGGL((conv_finish_kernel<LIMBS, NB, MB>), dim3(tails * 4 * MB), dim3(256), 0, st, a, grid);
+        hipLaunchKernelGGL((conv_finish_kernel<LIMBS, WL, NB, MB>), dim3(tails * 4 * MB), dim3(256), 0, st, a, grid);
     return launch_status();
 }
 
@@ -1777,8 +1789,9 @@ static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, 
         }
         st2 = launch_status();
     }
-    else if (p.limbs == 2) st2 = launch_mfma<2, 1, 2>(a, p, grid, tails, hs);
-    else st2 = p.BN == 128 ? launch_mfma<1, 2, 2>(a, p, grid, tails, hs) : launch_mfma<1, 1, 2>(a, p, grid, tails, hs);
+    else if (p.wl == 2) st2 = launch_mfma<2, 2, 1, 2>(a, p, grid, tails, hs);
+    else if (p.limbs == 2) st2 = launch_mfma<2, 1, 1, 2>(a, p, grid, tails, hs);
+    else st2 = p.BN == 128 ? launch_mfma<1, 1, 2, 2>(a, p, grid, tails, hs) : launch_mfma<1, 1, 1, 2>(a, p, grid, tails, hs);
     if (st2 != LP_OK || tails || !counting || direct) return st2;
     return launch_sum_partials(a.zero_partial, grid, (unsigned long long *)zero_count, (unsigned long long *)sat_count, hs);
 }
@@ -1815,12 +1828,12 @@ static lp_status pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, con
             hipLaunchKernelGGL(pack_weights_rows_kernel<int16_t>, dim3(rgrid), dim3(256), 0, hs, (const int16_t *)w, out,
                                d->Cout, d->R, d->S * d->Cin, p.KHR, p.KHP, p.CoutP);
             hipLaunchKernelGGL(weight_corr_kernel<int16_t>, dim3(cgrid), dim3(64), 0, hs,
-                               (const int16_t *)w, corr, d->Cout, p.CoutP, K, 2);
+                               (const int16_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         } else {
             hipLaunchKernelGGL(pack_weights_rows_kernel<int8_t>, dim3(rgrid), dim3(256), 0, hs, (const int8_t *)w, out,
                                d->Cout, d->R, d->S * d->Cin, p.KHR, p.KHP, p.CoutP);
             hipLaunchKernelGGL(weight_corr_kernel<int8_t>, dim3(cgrid), dim3(64), 0, hs,
-                               (const int8_t *)w, corr, d->Cout, p.CoutP, K, 2);
+                               (const int8_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         }
         return launch_status();
     }
@@ -1830,27 +1843,27 @@ static lp_status pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, con
             hipLaunchKernelGGL(pack_weights_flat_kernel<int16_t>, dim3(fgrid), dim3(256), 0, hs,
                                (const int16_t *)w, out, d->Cout, K, p.CoutP);
             hipLaunchKernelGGL(weight_corr_kernel<int16_t>, dim3(cgrid), dim3(64), 0, hs,
-                               (const int16_t *)w, corr, d->Cout, p.CoutP, K, 2);
+                               (const int16_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         } else {
             hipLaunchKernelGGL(pack_weights_flat_kernel<int8_t>, dim3(fgrid), dim3(256), 0, hs,
                                (const int8_t *)w, out, d->Cout, K, p.CoutP);
             hipLaunchKernelGGL(weight_corr_kernel<int8_t>, dim3(cgrid), dim3(64), 0, hs,
-                               (const int8_t *)w, corr, d->Cout, p.CoutP, K, 2);
+                               (const int8_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         }
         return launch_status();
     }
-#define LP_PACK(WT, L)                                                                              \
-    hipLaunchKernelGGL((pack_weights_kernel<WT, L>), dim3(grid), dim3(256), 0, hs, (const WT *)w, out, \
+#define LP_PACK(WT, L, W)                                                                           \
+    hipLaunchKernelGGL((pack_weights_kernel<WT, W>), dim3(grid), dim3(256), 0, hs, (const WT *)w, out, \
                        d->Cout, d->Cin, RS, p.nchunks, p.CoutP, total);                                \
     hipLaunchKernelGGL(weight_corr_kernel<WT>, dim3(cgrid), dim3(64), 0, hs, (const WT *)w, corr,      \
-                       d->Cout, p.CoutP, RS * d->Cin, L);                                              \
+                       d->Cout, p.CoutP, RS * d->Cin, L, W);                                           \
     if (L == 2)                                                                                        \
     hipLaunchKernelGGL(chunk_weight_sums_kernel<WT>, dim3(p.CoutP, p.nchunks), dim3(64), 0, hs,        \
                        (const WT *)w, (int *)(out + p.wsum_offset), d->Cout, p.CoutP, d->Cin, RS)
     if (p.limbs == 2) {
-        if (w16) { LP_PACK(int16_t, 2); } else { LP_PACK(int8_t, 2); }
+        if (w16) { LP_PACK(int16_t, 2, 2); } else { LP_PACK(int8_t, 2, 1); }
     } else {
-        LP_PACK(int8_t, 1);
+        LP_PACK(int8_t, 1, 1);
     }
 #undef LP_PACK
     return launch_status();

@@ -254,7 +254,7 @@ __device__ __forceinline__ void fc_tile_tables(const FcArgs &f, int mt, int nt, 
         }
         rowsum[m] = t;
     }
-    build_colterms<FN, kFcThreads>(f.c, nt, ctab, LIMBS);
+    build_colterms<FN, kFcThreads>(f.c, nt, ctab, LIMBS, LIMBS);
 }
 
 // Sums in the 32-bit pieces the epilogue combines <-> one exact int64 per output.
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(kFcThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 
     fc_tile_tables<LIMBS>(f, mt, nt, outoff, rowsum, ctab);
     __syncthreads();
-    const TileCounts counts = tile_epilogue<LIMBS, 2, FN, 1, 4>(
+    const TileCounts counts = tile_epilogue<LIMBS, LIMBS, 2, FN, 1, 4>(
         f.c, acc, [&](int m) { return rowsum[m]; }, outoff, outoff, ctab, nt, wave * 32, 0, 0, 0);
     if (f.c.zero_partial || f.c.direct_counts) {
         if (lane == 0) {
@@ -510,7 +510,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_finish_kernel(const FcArgs f)
             }
     }
     __syncthreads();
-    const TileCounts counts = tile_epilogue<LIMBS, 1, FN, 1, 1>(
+    const TileCounts counts = tile_epilogue<LIMBS, LIMBS, 1, FN, 1, 1>(
         f.c, acc, [&](int m) { return rowsum[m]; }, outoff, outoff, ctab, nt, wave * 32, cb * 32, 0, g);
     if (!f.c.zero_count && !f.c.sat_count) return;
     if ((tid & 63) == 0) {
@@ -764,7 +764,7 @@ static lp_status fc_pack(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw, const v
 #define LP_FCPACK(WT, L)                                                                                     \
     hipLaunchKernelGGL((fc_pack_weights_kernel<WT, L>), dim3(grid), dim3(256), 0, hs, (const WT *)w, out, Nout, K, \
                        p.KH, pieces);                                                                        \
-    hipLaunchKernelGGL(weight_corr_kernel<WT>, dim3(CoutP), dim3(64), 0, hs, (const WT *)w, corr, Nout, CoutP, K, L)
+    hipLaunchKernelGGL(weight_corr_kernel<WT>, dim3(CoutP), dim3(64), 0, hs, (const WT *)w, corr, Nout, CoutP, K, L, L)
     if (p.limbs == 2) {
         if (qw.n > 8) { LP_FCPACK(int16_t, 2); } else { LP_FCPACK(int8_t, 2); }
     } else {

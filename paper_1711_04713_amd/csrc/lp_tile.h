@@ -135,9 +135,11 @@ __device__ __forceinline__ int requant_relu32(int hi, int lo16, int s)
 // wants: three int32 planes (bits 16.., 8..15, 0..7) for the 32-bit epilogue, else int64.
 // deadmask: chunks of 64 input channels that were skipped as all-zero; their share of the weight
 // correction, 128 * sum(w over the chunk) - 16384 * (positions of the chunk), is taken out again
-// (their limb products, which it would have cancelled, were never formed).
+// (their limb products, which it would have cancelled, were never formed).  With 8-bit weights under
+// 16-bit activations (limbs 2, wlimbs 1) the correction has no 16384 * K term: the weights carry no offset.
 template <int BN, int THREADS>
-__device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int *ctab, int limbs, unsigned deadmask = 0)
+__device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int *ctab, int limbs, int wlimbs,
+                                              unsigned deadmask = 0)
 {
     for (int c = threadIdx.x; c < BN; c += THREADS) {
         const int colg = ntile * BN + c;
@@ -146,16 +148,16 @@ __device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int
             for (unsigned rem = deadmask; rem; rem &= rem - 1) {
                 const int ch = __builtin_ctz(rem);
                 const int kc = a.taps * min(64, a.Cin - 64 * ch);
-                t -= (int64_t)128 * a.wsum[(size_t)ch * a.CoutP + colg] - (int64_t)16384 * kc;
+                t -= (int64_t)128 * a.wsum[(size_t)ch * a.CoutP + colg] - (wlimbs == 2 ? (int64_t)16384 * kc : 0);
             }
         }
         if (a.fast) {
             // (shifts 9..16: the epilogue's rounding half 2^(s-1) rides in the constants, as 2^(s-9)
-            // at the scale of v / 256; one limb: the top plane arrives clamped and at that scale,
+            // at the scale of v / 256; one weight limb: the top plane arrives clamped and at that scale,
             // the middle plane holds the low 16 bits)
             const bool mid = a.act.s >= 9 && a.act.s <= 16;
             const int half9 = mid ? 1 << (a.act.s - 9) : 0;
-            if (mid && limbs == 1) {
+            if (mid && wlimbs == 1) {
                 const int64_t top = t >> 16;
                 const int topc = (int)(top > (1 << 22) ? (1 << 22) : top < -(1 << 22) ? -(1 << 22) : top);
                 ctab[c] = topc * 256 + half9;
@@ -163,7 +165,7 @@ __device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int
                 ctab[2 * BN + c] = 0;
             } else {
                 ctab[c] = (int)(t >> 16);
-                ctab[BN + c] = (int)((t >> 8) & 255) + (limbs == 2 ? half9 : 0);
+                ctab[BN + c] = (int)((t >> 8) & 255) + (wlimbs == 2 ? half9 : 0);
                 ctab[2 * BN + c] = (int)(t & 255);
             }
         } else {
@@ -179,7 +181,7 @@ __device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int
 // 8*(v/4) + 4*(lane/32) + v%4 of its 32-channel block (the wave's blocks start at channel col0w
 // of the tile): four consecutive channels per group of four registers, which leave as one 8-byte
 // (4-byte) store.
-// row_sum(m): sum of the codes under tile row m's window (two-limb only); outoff and ctab (see
+// row_sum(m): sum of the codes under tile row m's window (two-limb weights only); outoff and ctab (see
 // build_colterms) are LDS tables, complete and visible.  Returns the wave's counts of zero codes
 // and (when a.count_sat) of values clipped at an end of the code range, the same in every lane.
 // The accumulators passed in cover MBL of the wave's MB row blocks, starting at block mb0, and GL
@@ -190,8 +192,10 @@ struct TileCounts {
     unsigned zeros, sats;
 };
 
-template <int LIMBS, int NB, int BN, int MBL, int GL, typename RowSum>
-__device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&acc)[MBL][NB][LIMBS == 2 ? 3 : 1],
+// LIMBS / WL: 8-bit limbs of the activations and of the weights; LIMBS + WL - 1 accumulator planes, the
+// most significant first (2, 2: HH, HL + LH, LL; 2, 1: H, L; 1, 1: one).
+template <int LIMBS, int WL, int NB, int BN, int MBL, int GL, typename RowSum>
+__device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&acc)[MBL][NB][LIMBS + WL - 1],
                                                   RowSum row_sum, const int *outoff, const int *pooloff,
                                                   const int *ctab, int ntile, int row0, int col0w, int mb0, int g0)
 {
@@ -205,7 +209,7 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
         const int m = row0 + (mb0 + mb) * 32 + l32;
         oo[mb] = outoff[m];
         po[mb] = a.pool ? pooloff[m] : -1; // pooled output pixel, at the window's top-left lane only
-        rs[mb] = (LIMBS == 2) ? row_sum(m) : 0;
+        rs[mb] = (WL == 2) ? row_sum(m) : 0;
     }
     if (a.fast) {
         // v = 2^16*A + 2^8*B + C with every piece in int32: the channel constant is split the same
@@ -259,7 +263,7 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                         for (int e = 0; e < 4; ++e) {
                             const int v = 4 * gl + e;
                             int hi, lo16 = 0;
-                            if constexpr (LIMBS == 2 && S16 == 3) {
+                            if constexpr (WL == 2 && S16 == 3) {
                                 // Shifts 9..16 (above, only the top plane matters and the class-0 form is
                                 // shorter).  With W = floor(v / 256) the code is (W + 2^(s-9)) >> (s-8):
                                 // the dropped low byte of v cannot carry into a multiple of 256.  W =
@@ -274,16 +278,19 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                                 q[e] = clamp_code(raw[e], cmax);
                                 continue;
                             } else if constexpr (S16 == 3) {
-                                // one limb, shifts 9..16: the same with v = 65536*cA + (acc + low 16
-                                // bits of the constant); cA arrives clamped, times 256, plus the half
-                                const int W = ((acc[mb][nb][0][v] + cB[e]) >> 8) + cA[e];
+                                // one weight limb, shifts 9..16: the same with v = 65536*cA + 256*H + (L +
+                                // low 16 bits of the constant); cA arrives clamped, times 256, plus the
+                                // half.  |H|, |L| <= 2^27 for K <= 8192: W stays inside 32 bits
+                                int W = ((acc[mb][nb][LIMBS - 1][v] + cB[e]) >> 8) + cA[e];
+                                if constexpr (LIMBS == 2) W += acc[mb][nb][0][v];
                                 raw[e] = W >> (s - 8);
                                 q[e] = clamp_code(raw[e], cmax);
                                 continue;
                             } else if constexpr (LIMBS == 2) {
-                                const int C = acc[mb][nb][2][v] + cC[e] + ((rs[mb] & 1) << 7);
-                                const int B = acc[mb][nb][1][v] + cB[e] + (rs[mb] >> 1) + (C >> 8);
-                                hi = acc[mb][nb][0][v] + cA[e] + (B >> 8);
+                                const int C = acc[mb][nb][WL][v] + cC[e] + (WL == 2 ? (rs[mb] & 1) << 7 : 0);
+                                const int B = acc[mb][nb][WL - 1][v] + cB[e] + (WL == 2 ? rs[mb] >> 1 : 0) + (C >> 8);
+                                hi = cA[e] + (B >> 8);
+                                if constexpr (WL == 2) hi += acc[mb][nb][0][v];
                                 if constexpr (S16 != 0) lo16 = ((B & 255) << 8) | (C & 255);
                             } else {
                                 // one limb: the plane split is 2^16*cA + (2^8*cB + cC)
@@ -388,12 +395,14 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                 const int col0 = ntile * BN + cl;
 #pragma unroll
                 for (int mb = 0; mb < MBL; ++mb) {
-                    const int64_t rt = (LIMBS == 2) ? (int64_t)rs[mb] * 128 : 0;
+                    const int64_t rt = (WL == 2) ? (int64_t)rs[mb] * 128 : 0;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int v = 4 * gl + e;
                         int64_t val;
-                        if constexpr (LIMBS == 2)
+                        if constexpr (LIMBS == 2 && WL == 1)
+                            val = ((int64_t)acc[mb][nb][0][v] << 8) + (int64_t)acc[mb][nb][1][v] + ct64[cl + e];
+                        else if constexpr (LIMBS == 2)
                             val = ((int64_t)acc[mb][nb][0][v] << 16) + ((int64_t)acc[mb][nb][1][v] << 8) +
                                   (int64_t)acc[mb][nb][2][v] + rt + ct64[cl + e];
                         else
@@ -426,12 +435,12 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
 }
 
 
-// corr[co] = 128 * sum_k w[co][k] - 16384 * K for the two-limb path, 0 otherwise: the weight half of
-// the offset correction, computed once when the weights are packed.  One wave per output channel
+// corr[co] = 128 * sum_k w[co][k] (- 16384 * K with two-limb weights) for two-limb activations, 0 otherwise:
+// the weight half of the offset correction, computed once when the weights are packed.  One wave per output channel
 // (blockIdx.x = co, 64 threads), lanes striding over K.
 template <typename WT>
 __global__ __launch_bounds__(64) void weight_corr_kernel(const WT *__restrict__ w, int64_t *__restrict__ corr, int Cout,
-                                                        int CoutP, int K, int limbs)
+                                                        int CoutP, int K, int limbs, int wlimbs)
 {
     const int co = blockIdx.x;
     if (co >= CoutP) return;
@@ -440,7 +449,7 @@ __global__ __launch_bounds__(64) void weight_corr_kernel(const WT *__restrict__ 
         for (int k = threadIdx.x; k < K; k += 64) s += (long long)w[(size_t)co * K + k];
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) s += __shfl_down(s, off, 64);
-    if (threadIdx.x == 0) corr[co] = (limbs == 2 && co < Cout) ? 128 * s - (long long)16384 * K : 0;
+    if (threadIdx.x == 0) corr[co] = (limbs == 2 && co < Cout) ? 128 * s - (wlimbs == 2 ? (long long)16384 * K : 0) : 0;
 }
 
 // Adds n per-workgroup counts (zeros at partials[0..n), clipped values at partials[n..2n)) to the

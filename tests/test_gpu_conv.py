@@ -125,6 +125,35 @@ def test_conv_random_shapes_8bit(oracle, N, Cin, H, W, Cout, R, S, pad):
     assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
 
 
+@pytest.mark.parametrize("N,Cin,H,W,Cout,pad,fx,fy", [
+    (2, 64, 20, 24, 64, 1, 12, 4),       # shift 15
+    (1, 136, 9, 11, 40, 0, 12, 12),      # shift 7; three chunks, the last an eighth full, ragged channels
+    (3, 72, 14, 14, 128, 1, 8, 0),       # shift 15, images straddled by tiles
+    (1, 904, 7, 7, 72, 1, 12, 2),        # K = 8136: just inside the 32-bit epilogue; shift 17
+    (1, 920, 6, 7, 64, 1, 12, 3),        # K = 8280: just past it; shift 16
+    (70, 64, 32, 32, 128, 1, 12, 6),     # a grid that takes 128-channel tiles
+    (40, 128, 28, 28, 256, 1, 12, 6),    # ... and shares the last round's reductions
+])
+def test_conv_16bit_activations_8bit_weights(oracle, N, Cin, H, W, Cout, pad, fx, fy):
+    """One-limb weights under two-limb activations: every code of both widths with the extremes forced,
+    raw sums, both tie rules, the fused epilogue of every shift class."""
+    rng = np.random.default_rng(Cin + H)
+    x = _codes(rng, (N, Cin, H, W), zero_frac=0.3)
+    w = _codes(rng, (Cout, Cin, 3, 3), n=8)
+    x[0], w[0], w[-1] = -32768, -128, 127           # the largest sums of either sign
+    qx, qw, qy = (16, 16 - fx, fx), (8, 1, 7), (16, 16 - fy, fy)
+    acc = oracle.conv(x, w, pad=pad, threads=8)
+    got = conv(x, qx, w, qw, qy=qy, r=lp.LP_ROUND_NEAREST_EVEN, pad=pad)
+    assert got["info"]["path"] == 1 and np.array_equal(got["acc"], acc)
+    y, z, sat = oracle.act(acc, fx + 7, *qy, True, oracle.ROUND_EVEN, with_sat=True)
+    assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
+    bias = _codes(rng, (Cout,), n=8)
+    acc = acc + (bias.astype(np.int64) << (fx + 7 - 5)).reshape(1, -1, 1, 1)
+    got = conv(x, qx, w, qw, qy=qy, bias=bias, qb=(8, 3, 5), pad=pad, want_acc=False)
+    y, z, sat = oracle.act(acc, fx + 7, *qy, True, oracle.ROUND_AWAY, with_sat=True)
+    assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
+
+
 def test_conv_realistic_values_and_bias(oracle):
     rng = np.random.default_rng(5)
     x = np.maximum(_codes(rng, (2, 64, 18, 18), full_range=False), 0)

@@ -38,6 +38,12 @@ constexpr int kConvThreads = 256;
 constexpr int kMaxDevices = 64;
 constexpr int kDirectCountGrid = 2048; // largest grid whose workgroups add to the zero / saturation counters directly
 
+// int32 planes a part of a split tile leaves per output: two-limb sums meet as 2^16 * hi + lo, whose
+// pieces stay inside 32 bits over all parts together (K < 65536: |HH|, |LL| < 2^30, the carries
+// from the middle plane and the row sums are below 2^24 and, per part, 2^17); one weight limb
+// leaves its own two planes.
+constexpr int part_planes(int limbs, int wl) { return wl == 2 ? 2 : limbs + wl - 1; }
+
 enum { PATH_DIRECT = 0, PATH_MFMA = 1 };
 
 struct Plan {
@@ -59,7 +65,7 @@ struct Plan {
     // each; each of the remaining tail tiles is cut along the reduction into `split` parts, so
     // that the last, partly filled round keeps every CU busy (see the kernel's merge step).
     int per_xcd, full_per_xcd, split, grid;
-    size_t part_bytes;   // bytes of one part's accumulators and row sums in the workspace
+    size_t part_bytes;   // bytes of one part's sums in the workspace
     size_t lds_bytes;
     size_t packed_bytes, corr_offset;
     size_t wsum_offset;  // per-chunk weight sums [nchunks][CoutP] int32 (two-limb patch path), else 0
@@ -183,9 +189,9 @@ constexpr size_t kLdsBudgets[2] = {54400, 80000};
 // tail takes as many rounds as its parts need slots, the finishing kernel costs about 6, and
 // every part adds traffic (its accumulators are written once and read once).  A split must
 // promise a clear gain over the plain launch to be taken.
-static int choose_split(int tail_tiles, int slots, int nslabs, size_t part_bytes)
+static int choose_split(int tail_tiles, int slots, int nslabs, size_t part_acc)
 {
-    const double fixed = 10.0, finish = 6.0, per_part = 0.03 * (double)part_bytes / 98816.0;
+    const double fixed = 10.0, finish = 6.0, per_part = 0.03 * (double)part_acc / 98304.0;
     const double whole = nslabs + fixed;
     int best = 1;
     double best_t = 0.8 * whole;
@@ -345,10 +351,10 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
             const int slots = wg_per_cu * (kCUs / kXCDs);
             p.per_xcd = (total + kXCDs - 1) / kXCDs;
             p.full_per_xcd = p.per_xcd / slots * slots;
-            p.part_bytes = (size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4 + (size_t)BM * 4;
+            p.part_bytes = (size_t)BM * p.BN * part_planes(p.limbs, p.wl) * 4;
             p.split = 1;
             if (p.per_xcd > p.full_per_xcd && nslabs > 1)
-                p.split = choose_split(p.per_xcd - p.full_per_xcd, slots, nslabs, p.part_bytes);
+                p.split = choose_split(p.per_xcd - p.full_per_xcd, slots, nslabs, (size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4);
             if (p.split == 1) p.full_per_xcd = p.per_xcd;
             p.grid = kXCDs * (p.full_per_xcd + (p.per_xcd - p.full_per_xcd) * p.split);
         }
@@ -623,7 +629,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
             abase_s[m] = ok ? (img * a.Hp + yo - vr0) * a.PW + t : 0;
             pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
         }
-        build_colterms<BN, THREADS>(a, ntile, ctab, LIMBS, WL, deadmask);
+        build_colterms<BN>(a, ntile, ctab, LIMBS, WL, deadmask);
     };
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WMC, wn = wave / WMC;
@@ -1030,21 +1036,31 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
     if (nparts > 1) {
         const int tail_tile = xcd * (a.per_xcd - a.full_per_xcd) + (tl - a.full_per_xcd);
         v4i *mine = (v4i *)(a.partials + ((size_t)tail_tile * nparts + part) * a.part_bytes);
+        constexpr int PP = part_planes(LIMBS, WL);
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb) {
+            // the row's code sum joins the two planes: 128 * sum = 2^16 * (sum >> 9) + 128 * (sum & 511)
+            const int rs = WL == 2 ? row_sum(wm * WROWS + mb * 32 + l32) : 0;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int q = 0; q < NACC; ++q)
+                for (int g = 0; g < 4; ++g) {
+                    const v16i(&c)[NACC] = acc[mb][nb];
+                    v4i out[PP];
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const v16i &c = acc[mb][nb][q];
-                        mine[(((mb * NB + nb) * NACC + q) * 4 + g) * THREADS + tid] =
-                            (v4i){c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+                    for (int e = 0; e < 4; ++e) {
+                        const int v = 4 * g + e;
+                        if constexpr (WL == 2) {
+                            out[0][e] = c[0][v] + (c[1][v] >> 8) + (rs >> 9);
+                            out[1][e] = c[2][v] + ((c[1][v] & 255) << 8) + ((rs & 511) << 7);
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < PP; ++q) out[q][e] = c[q][v];
+                        }
                     }
-        if constexpr (WL == 2) {
-            int *rs = (int *)(mine + MB * NB * NACC * 4 * THREADS);
-            for (int m = tid; m < BM; m += THREADS) rs[m] = row_sum(m);
+#pragma unroll
+                    for (int q = 0; q < PP; ++q) mine[(((mb * NB + nb) * 4 + g) * PP + q) * THREADS + tid] = out[q];
+                }
         }
         if (a.zero_partial && tid == 0) a.zero_partial[blockIdx.x] = a.zero_partial[a.partial_stride + blockIdx.x] = 0;
         if (a.zout && part == 0 && tid == 0) a.zout[wi] = 0; // the finishing kernel sets it if it meets a nonzero code
@@ -1078,113 +1094,125 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
 }
 
 
-// Finishes the tail tiles.  A tile's parts are added up and the epilogue run by 4 * MB workgroups,
-// one per (32-row block, channel group of the MFMA layout): each thread then needs only NB * NACC
-// 16-byte pieces per part, so the pieces of all parts are requested together and the memory
-// latency is paid once.  Zero counts go straight to the total (few workgroups); workgroup 0 also
-// adds the per-workgroup counts of the main kernel.
+// Finishes the tail tiles.  A tile is 4 * MB units, one per (32-row block, channel group of the MFMA
+// layout); 256 threads take a unit, each then needs only NB * part_planes 16-byte pieces per part,
+// and the pieces of four parts are requested together.
+// A launch is bound by the counters as soon as it has more than a few hundred workgroups: their
+// adds to one address are served one per 13.7 ns (1600 workgroups with one unit each took 26 us,
+// 2048 took 33, 15 and 15 now).  So a workgroup takes several units, up to four side
+// by side, and leaves one add per counter: see launch_mfma.  Workgroup 0 also adds the
+// per-workgroup counts of the main kernel.
 template <int LIMBS, int WL, int NB, int MB>
-__global__ __launch_bounds__(256) void conv_finish_kernel(const ConvArgs a, int main_grid)
+__global__ __launch_bounds__(1024) void conv_finish_kernel(const ConvArgs a, int main_grid, int wgs_per_tile)
 {
-    constexpr int THREADS = 256;
     constexpr int BN = 64 * NB;
     constexpr int NACC = LIMBS + WL - 1;
-    constexpr int SUB = 4 * MB;       // workgroups per tile
-    constexpr int MAXP = 8;           // most parts a tile is cut into (see choose_split)
+    constexpr int PP = part_planes(LIMBS, WL);
+    constexpr int UNIT = 256;         // threads per unit
+    constexpr int BATCH = 4;          // parts requested at once (eight spill)
+    constexpr int UNITS = 4 * MB;     // units per tile
     __shared__ int outoff[BM];
-    __shared__ int rowsum[BM];
     __shared__ int pooloff[BM];
     __shared__ __align__(16) int ctab[3 * BN];
-    __shared__ unsigned wave_zeros[2][THREADS / 64]; // [zeros, clipped][wave]
-    const int tid = threadIdx.x;
+    __shared__ unsigned long long wave_counts[2][16]; // [zeros, clipped][wave]
+    const int tid = threadIdx.x, threads = blockDim.x, side = threads / UNIT, utid = tid & (UNIT - 1);
+    const int wave = utid >> 6; // within the unit: the main kernel's wave arrangement, BM / (32 * MB) waves along the pixels
+    constexpr int WMC = BM / (32 * MB);
     const int tails = a.per_xcd - a.full_per_xcd;
-    const int tile_b = blockIdx.x / SUB, sub = blockIdx.x % SUB;
-    const int mb0 = sub >> 2, g0 = sub & 3;
+    const int tile_b = blockIdx.x / wgs_per_tile, share = blockIdx.x % wgs_per_tile;
     const int xcd = tile_b / tails, tl = a.full_per_xcd + tile_b % tails;
     const int wi = xcd * a.per_xcd + tl;
-    unsigned long long total = 0; // thread 0: zeros, thread 1: clipped values
+    unsigned long long zeros = 0, sats = 0; // of the wave
     if (wi < a.total_work) {
         const int mtile = wi / a.tiles_n, ntile = wi % a.tiles_n;
         const int tile_r = mtile / a.tiles_c, tile_c = mtile % a.tiles_c;
         const int fr0 = tile_r * a.RH, x0 = tile_c * a.TW;
-        // every request first: accumulator pieces and row sums of all parts
         const unsigned char *slots = a.partials + (size_t)tile_b * a.split * a.part_bytes;
-        v4i piece[MAXP][NB][NACC];
-        int rsp[MAXP];
+        for (int u = share * side + __builtin_amdgcn_readfirstlane(tid / UNIT); u < UNITS; u += wgs_per_tile * side) { // (the same trips for every thread)
+            const int mb0 = u >> 2, g0 = u & 3;
+            v4i piece[BATCH][NB][PP];
+            auto request = [&](int o0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int o = 0; o < MAXP; ++o) {
-            const unsigned char *theirs = slots + (size_t)min(o, a.split - 1) * a.part_bytes; // clamped: unconditional loads
+                for (int o = 0; o < BATCH; ++o)
+                    if (o0 + o < a.split) { // (uniform)
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                            for (int q = 0; q < PP; ++q)
+                                piece[o][nb][q] = ((const v4i *)(slots + (size_t)(o0 + o) * a.part_bytes))[(((mb0 * NB + nb) * 4 + g0) * PP + q) * UNIT + utid];
+                    }
+            };
+            request(0);
+            if (u < side * wgs_per_tile) { // first trip: the tile's tables
+                for (int m = tid; m < BM; m += threads) {
+                    const int j = m / a.TW, t = m % a.TW;
+                    const int fr = fr0 + j, xo = x0 + t;
+                    const bool ok = j < a.RH && fr < a.FR && xo < a.Wo;
+                    outoff[m] = ok ? fr * a.Wo + xo : -1;
+                    pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1))
+                                     ? ((fr / a.Ho) * (a.Ho >> 1) + ((fr % a.Ho) >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
+                }
+                build_colterms<BN>(a, ntile, ctab, LIMBS, WL);
+            }
+            int sum[NB][PP][4];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int q = 0; q < NACC; ++q)
-                    piece[o][nb][q] = ((const v4i *)theirs)[((((mb0 * NB + nb) * NACC + q) * 4 + g0) * THREADS) + tid];
-            rsp[o] = (WL == 2 && tid < BM) ? ((const int *)(theirs + (size_t)MB * NB * NACC * 4 * THREADS * 16))[tid] : 0;
-        }
-        for (int m = tid; m < BM; m += THREADS) {
-            const int j = m / a.TW, t = m % a.TW;
-            const int fr = fr0 + j, xo = x0 + t;
-            const bool ok = j < a.RH && fr < a.FR && xo < a.Wo;
-            outoff[m] = ok ? fr * a.Wo + xo : -1;
-            pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1))
-                             ? ((fr / a.Ho) * (a.Ho >> 1) + ((fr % a.Ho) >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
-        }
-        build_colterms<BN, THREADS>(a, ntile, ctab, LIMBS, WL);
-        v16i acc[1][NB][NACC];
+                for (int q = 0; q < PP; ++q)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+                    for (int e = 0; e < 4; ++e) sum[nb][q][e] = 0;
+            for (int o0 = 0;;) {
 #pragma unroll
-            for (int q = 0; q < NACC; ++q)
+                for (int o = 0; o < BATCH; ++o)
+                    if (o0 + o < a.split) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[0][nb][q][v] = 0;
-        int rs = 0;
+                        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int o = 0; o < MAXP; ++o) {
-            if (o < a.split) {
+                            for (int q = 0; q < PP; ++q)
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int q = 0; q < NACC; ++q) {
-                        acc[0][nb][q][0] += piece[o][nb][q].x;
-                        acc[0][nb][q][1] += piece[o][nb][q].y;
-                        acc[0][nb][q][2] += piece[o][nb][q].z;
-                        acc[0][nb][q][3] += piece[o][nb][q].w;
+                                for (int e = 0; e < 4; ++e) sum[nb][q][e] += piece[o][nb][q][e];
                     }
-                rs += rsp[o];
+                o0 += BATCH;
+                if (o0 >= a.split) break;
+                request(o0);
             }
-        }
-        if (tid < BM) rowsum[tid] = rs;
-        __syncthreads();
-        // same wave arrangement as the main kernel: BM / (32 * MB) waves along the pixels
-        constexpr int WMC = BM / (32 * MB);
-        const int wave = tid >> 6;
-        const TileCounts counts = tile_epilogue<LIMBS, WL, NB, BN, 1, 1>(
-            a, acc, [&](int m) { return rowsum[m]; }, outoff, pooloff, ctab, ntile, (wave % WMC) * (32 * MB),
-            (wave / WMC) * (NB * 32), mb0, g0);
-        if (a.zout) {
-            // codes of this workgroup's part of the tile that exist; a zero count below it = a nonzero code
-            const int m = (wave % WMC) * (32 * MB) + mb0 * 32 + (tid & 31);
-            const int col0 = ntile * BN + (wave / WMC) * (NB * 32) + 8 * g0 + 4 * ((tid & 63) >> 5);
-            unsigned exist = 0;
+            v16i acc[1][NB][NACC];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) exist += outoff[m] >= 0 ? (unsigned)min(max(a.Cout - (col0 + nb * 32), 0), 4) : 0u;
-            unsigned wave_exist = 0;
+            for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int b = 0; b < 5; ++b) wave_exist += wave_count((exist >> b) & 1) << b;
-            if ((tid & 63) == 0 && wave_exist != counts.zeros) a.zout[wi] = 1;
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (WL == 2) { // 2^16 * hi + lo into the three planes the epilogue combines
+                        acc[0][nb][0][e] = sum[nb][0][e] + (sum[nb][1][e] >> 16);
+                        acc[0][nb][1][e] = (sum[nb][1][e] >> 8) & 255;
+                        acc[0][nb][2][e] = sum[nb][1][e] & 255;
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < PP; ++q) acc[0][nb][q][e] = sum[nb][q][e];
+                    }
+                }
+            if (u < side * wgs_per_tile) __syncthreads(); // (every thread: see the trip count)
+            const TileCounts counts = tile_epilogue<LIMBS, WL, NB, BN, 1, 1>(
+                a, acc, [](int) { return 0; }, outoff, pooloff, ctab, ntile, (wave % WMC) * (32 * MB), (wave / WMC) * (NB * 32), mb0, g0);
+            if (a.zout) {
+                // codes of the unit that exist; a zero count below it = a nonzero code
+                const int m = (wave % WMC) * (32 * MB) + mb0 * 32 + (tid & 31);
+                const int col0 = ntile * BN + (wave / WMC) * (NB * 32) + 8 * g0 + 4 * ((tid & 63) >> 5);
+                unsigned exist = 0;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) exist += outoff[m] >= 0 ? (unsigned)min(max(a.Cout - (col0 + nb * 32), 0), 4) : 0u;
+                unsigned wave_exist = 0;
+#pragma unroll
+                for (int b = 0; b < 5; ++b) wave_exist += wave_count((exist >> b) & 1) << b;
+                if ((tid & 63) == 0 && wave_exist != counts.zeros) a.zout[wi] = 1;
+            }
+            zeros += counts.zeros;
+            sats += counts.sats;
         }
-        if ((tid & 63) == 0) {
-            wave_zeros[0][tid >> 6] = counts.zeros;
-            wave_zeros[1][tid >> 6] = counts.sats;
-        }
-        __syncthreads();
-        if (tid < 2)
-            for (int w = 0; w < THREADS / 64; ++w) total += wave_zeros[tid][w];
     }
     if (!a.zero_partial) return;
     if (blockIdx.x == 0) {
         unsigned long long sum[2] = {0, 0};
-        for (int i = tid; i < main_grid; i += THREADS) {
+        for (int i = tid; i < main_grid; i += threads) {
             sum[0] += a.zero_partial[i];
             sum[1] += a.zero_partial[a.partial_stride + i];
         }
@@ -1193,17 +1221,20 @@ __global__ __launch_bounds__(256) void conv_finish_kernel(const ConvArgs a, int 
             sum[0] += __shfl_down(sum[0], off, 64);
             sum[1] += __shfl_down(sum[1], off, 64);
         }
-        __syncthreads(); // wave_zeros[] has been read
-        if ((tid & 63) == 0) { // a launch has fewer than 2^32 outputs
-            wave_zeros[0][tid >> 6] = (unsigned)sum[0];
-            wave_zeros[1][tid >> 6] = (unsigned)sum[1];
-        }
-        __syncthreads();
-        if (tid < 2)
-            for (int w = 0; w < THREADS / 64; ++w) total += wave_zeros[tid][w];
+        zeros += sum[0]; // (right in the wave's first lane)
+        sats += sum[1];
     }
-    if (tid == 0 && total && a.zero_count) atomicAdd(a.zero_count, total);
-    if (tid == 1 && total && a.sat_count) atomicAdd(a.sat_count, total);
+    if ((tid & 63) == 0) {
+        wave_counts[0][tid >> 6] = zeros;
+        wave_counts[1][tid >> 6] = sats;
+    }
+    __syncthreads();
+    if (tid < 2) {
+        unsigned long long total = 0;
+        for (int w = 0; w < threads / 64; ++w) total += wave_counts[tid][w];
+        unsigned long long *dst = tid ? a.sat_count : a.zero_count;
+        if (total && dst) atomicAdd(dst, total);
+    }
 }
 
 // Adds the per-workgroup counts to the caller's counters: blockIdx.y = 0 the zero counts, 1 the
@@ -1325,7 +1356,7 @@ __global__ __launch_bounds__(256)
         abase[m] = ok ? ((img * a.Hp + yo - vr0) * a.PW + t) * a.Cin * 2 : 0;
         pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
     }
-    build_colterms<BN, THREADS>(a, ntile, ctab, 2, 2);
+    build_colterms<BN>(a, ntile, ctab, 2, 2);
 #pragma unroll
     for (int i = 0; i < WPT; ++i)
         if (wave + 4 * i < WPIECES) wlds[wave + 4 * i][lane] = wreg[i];
@@ -1530,7 +1561,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         ubase[m] = ok ? prow * a.UPR + t * a.CU : 0;
         pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
     }
-    build_colterms<BN, THREADS>(a, ntile, ctab, 2, 2);
+    build_colterms<BN>(a, ntile, ctab, 2, 2);
     __syncthreads();
 
     // the sum of the codes under the row's window: its two lanes take alternate window rows
@@ -1630,8 +1661,15 @@ static lp_status launch_mfma(const ConvArgs &a, const Plan &p, int grid, int tai
     }
     hipLaunchKernelGGL((conv_mfma_kernel<LIMBS, WL, NB, MB>), dim3(grid), dim3(MB == 2 ? 256 : 512),
                        p.lds_bytes, st, a);
-    if (tails) // the split tail tiles are merged and written by a second, small kernel
-        hipLaunchKernelGGL((conv_finish_kernel<LIMBS, WL, NB, MB>), dim3(tails * 4 * MB), dim3(256), 0, st, a, grid);
+    if (tails) { // the split tail tiles are merged and written by a second, small kernel
+        // few tiles: a workgroup per unit; more: four units side by side, all of a tile's units at once
+        // while that is one workgroup per CU (a second round costs its whole latency, 7 us), then
+        // one after the other
+        const bool spread = tails * 4 * MB <= kCUs;
+        const int per_tile = spread ? 4 * MB : tails * MB <= kCUs ? MB : 1;
+        hipLaunchKernelGGL((conv_finish_kernel<LIMBS, WL, NB, MB>), dim3(tails * per_tile), dim3(spread ? 256 : 1024), 0, st, a,
+                           grid, per_tile);
+    }
     return launch_status();
 }
 
@@ -1641,7 +1679,9 @@ static WorkspaceLayout workspace_layout(const Plan &p)
     if (p.path != PATH_MFMA) return w;
     const size_t tails = (size_t)kXCDs * (p.per_xcd - p.full_per_xcd);
     w.partials = round_up((size_t)2 * p.grid * sizeof(unsigned), 256); // zero counts, counts of clipped values
-    w.total = w.partials + tails * p.split * p.part_bytes;
+    // sized for every accumulator plane and the row sums of a part (the contract of lp_conv_workspace_bytes
+    // and of what the static array holds); two-limb sums are combined and use two thirds of it
+    w.total = w.partials + tails * p.split * ((size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4 + (size_t)BM * 4);
     return w;
 }
 

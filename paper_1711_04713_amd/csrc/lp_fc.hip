@@ -240,7 +240,7 @@ struct FcArgs {
 template <int LIMBS>
 __device__ __forceinline__ void fc_tile_tables(const FcArgs &f, int mt, int nt, int *outoff, int *rowsum, int *ctab)
 {
-    for (int m = threadIdx.x; m < FM; m += kFcThreads) {
+    for (int m = threadIdx.x; m < FM; m += blockDim.x) {
         const int row = mt * FM + m;
         outoff[m] = row < f.M ? row : -1;
         // the row's partial sums, all requested before any is added (kc is uniform)
@@ -254,7 +254,7 @@ __device__ __forceinline__ void fc_tile_tables(const FcArgs &f, int mt, int nt, 
         }
         rowsum[m] = t;
     }
-    build_colterms<FN, kFcThreads>(f.c, nt, ctab, LIMBS, LIMBS);
+    build_colterms<FN>(f.c, nt, ctab, LIMBS, LIMBS);
 }
 
 // Sums in the 32-bit pieces the epilogue combines <-> one exact int64 per output.
@@ -447,22 +447,24 @@ __global__ __launch_bounds__(kFcThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
-// Adds up the parts of a tile and runs the epilogue: eight workgroups per tile, one per (column
-// block, group of four channels) of the MFMA layout, threads mapped to rows as in the main
-// kernel, so that a thread needs two 16-byte pieces (one with one limb) per part.  Counts go
-// straight to the caller's counters.
+// Adds up the parts of a tile and runs the epilogue: four workgroups per tile, one per group of
+// four channels of the MFMA layout, half of its threads for each column block, mapped to rows as in
+// the main kernel, so that a thread needs two 16-byte pieces (one with one limb) per part.  Counts go
+// straight to the caller's counters, whose adds are served one per 13.7 ns: with twice as many
+// workgroups of half the size the classifier at 256 rows took 171 us, now 166.
+constexpr int kFinishThreads = 2 * kFcThreads;
 template <int LIMBS>
-__global__ __launch_bounds__(kFcThreads) void fc_finish_kernel(const FcArgs f)
+__global__ __launch_bounds__(kFinishThreads) void fc_finish_kernel(const FcArgs f)
 {
     constexpr int NACC = (LIMBS == 2) ? 3 : 1;
-    constexpr int WAVES = kFcThreads / 64;
+    constexpr int WAVES = kFinishThreads / 64;
     constexpr int PP = LIMBS == 2 ? 2 : 1;    // pieces per part and thread
     __shared__ int outoff[FM];
     __shared__ int rowsum[FM];
     __shared__ __align__(16) int ctab[3 * FN];
     __shared__ unsigned wave_counts[2][WAVES];
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const int tile = blockIdx.x >> 3, cb = (blockIdx.x >> 2) & 1, g = blockIdx.x & 3;
+    const int tid = threadIdx.x, rtid = tid & (kFcThreads - 1), wave = rtid >> 6;
+    const int tile = blockIdx.x >> 2, cb = __builtin_amdgcn_readfirstlane(tid / kFcThreads), g = blockIdx.x & 3;
     const int mt = tile / f.n_tiles, nt = tile - mt * f.n_tiles;
     const v4i *slots = (const v4i *)(f.c.partials + (size_t)tile * f.ksplit * f.c.part_bytes);
     const size_t part_v4 = (size_t)f.c.part_bytes / 16;
@@ -472,7 +474,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_finish_kernel(const FcArgs f)
     for (int o = 0; o < FMAXP; ++o)
         if (o < f.ksplit) {
 #pragma unroll
-            for (int h = 0; h < PP; ++h) piece[o][h] = slots[o * part_v4 + ((cb * 4 + g) * PP + h) * kFcThreads + tid];
+            for (int h = 0; h < PP; ++h) piece[o][h] = slots[o * part_v4 + ((cb * 4 + g) * PP + h) * kFcThreads + rtid];
         }
     fc_tile_tables<LIMBS>(f, mt, nt, outoff, rowsum, ctab);
     v16i acc[1][1][NACC];
@@ -514,8 +516,8 @@ __global__ __launch_bounds__(kFcThreads) void fc_finish_kernel(const FcArgs f)
         f.c, acc, [&](int m) { return rowsum[m]; }, outoff, outoff, ctab, nt, wave * 32, cb * 32, 0, g);
     if (!f.c.zero_count && !f.c.sat_count) return;
     if ((tid & 63) == 0) {
-        wave_counts[0][wave] = counts.zeros;
-        wave_counts[1][wave] = counts.sats;
+        wave_counts[0][tid >> 6] = counts.zeros;
+        wave_counts[1][tid >> 6] = counts.sats;
     }
     __syncthreads();
     if (tid < 2) {
@@ -846,12 +848,12 @@ static lp_status fc_forward(int M, int K, int Nout, const void *x, lp_qfmt qx, c
         hipLaunchKernelGGL((fc_split_x_kernel<int16_t, 2>), sgrid, dim3(64 * kSplitWaves), 0, hs, (const int16_t *)x,
                            const_cast<unsigned char *>(f.xs), const_cast<int *>(f.xsum), M, K, p.KH, p.khc);
         hipLaunchKernelGGL(fc_mfma_kernel<2>, dim3(p.grid), dim3(kFcThreads), 0, hs, f);
-        if (p.ksplit > 1) hipLaunchKernelGGL(fc_finish_kernel<2>, dim3(p.tiles * 8), dim3(kFcThreads), 0, hs, f);
+        if (p.ksplit > 1) hipLaunchKernelGGL(fc_finish_kernel<2>, dim3(p.tiles * 4), dim3(kFinishThreads), 0, hs, f);
     } else {
         hipLaunchKernelGGL((fc_split_x_kernel<int8_t, 1>), sgrid, dim3(64 * kSplitWaves), 0, hs, (const int8_t *)x,
                            const_cast<unsigned char *>(f.xs), const_cast<int *>(f.xsum), M, K, p.KH, p.khc);
         hipLaunchKernelGGL(fc_mfma_kernel<1>, dim3(p.grid), dim3(kFcThreads), 0, hs, f);
-        if (p.ksplit > 1) hipLaunchKernelGGL(fc_finish_kernel<1>, dim3(p.tiles * 8), dim3(kFcThreads), 0, hs, f);
+        if (p.ksplit > 1) hipLaunchKernelGGL(fc_finish_kernel<1>, dim3(p.tiles * 4), dim3(kFinishThreads), 0, hs, f);
     }
     const lp_status ls = launch_status();
     if (ls != LP_OK || p.ksplit > 1 || !counting || direct) return ls;

@@ -480,3 +480,53 @@ def test_fused_maxpool_matches_conv_act_pool(oracle, shape):
     with pytest.raises(lp.LpError) as e:
         lp.lp_conv_plan_info(lp.ConvDesc(N, H + 1, W, Cin, Cout, 3, 3, 1, 1, 1), QX, QW)
     assert e.value.status == 2
+
+
+FINISH_FORMS = [
+    # (N, H, W, Cin, Cout, kernel, activation bits, weight bits)
+    (1, 12, 10, 256, 64, 3, 16, 16),       # few tiles: a workgroup per unit
+    (1, 12, 10, 256, 72, 3, 16, 8),        # one weight limb, ragged channels
+    (1, 28, 28, 512, 512, 3, 16, 16),      # four units side by side, seven parts: more than one batch of requests
+    (1, 28, 28, 512, 512, 3, 16, 8),
+    (5, 28, 28, 512, 512, 3, 16, 16),      # every tile of 256 in one workgroup, two trips
+    (5, 28, 28, 512, 512, 3, 16, 8),
+    (1, 12, 10, 256, 64, 3, 8, 8),         # one limb, 64 and 128 channels
+    (64, 28, 28, 256, 256, 3, 8, 8),
+]
+
+
+@pytest.mark.parametrize("form", FINISH_FORMS)
+def test_merged_parts_equal_whole_tiles(form):
+    """Tiles cut along the reduction and merged by the finishing kernel give what one workgroup per tile
+    gives (no workspace, the form the oracle tests cover): codes, accumulators; the counters
+    equal counts of those codes."""
+    import torch
+
+    N, H, W, Cin, Cout, k, nx, nw = form
+    qx, qw, qy = (nx, 4, nx - 4), (nw, 1, nw - 1), (nx, 6, nx - 6)
+    d = lp.ConvDesc(N, H, W, Cin, Cout, k, k, 1, k // 2)
+    info = lp.lp_conv_plan_info(d, qx, qw)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(71)
+    dt = torch.int16 if nx > 8 else torch.int8
+    top = 1 << (nx - 1)
+    x = torch.randint(-top, top, (N, H, W, Cin), device="cuda", generator=gen).to(dt)
+    x[..., : Cin // 4] = top - 1                                                    # the row sums reach their largest
+    w = torch.randint(-(1 << (nw - 1)), 1 << (nw - 1), (Cout, k, k, Cin), device="cuda", generator=gen).to(torch.int16 if nw > 8 else torch.int8)
+    packed = torch.empty(lp.lp_conv_packed_bytes(d, qx, qw), dtype=torch.uint8, device="cuda")
+    lp.lp_conv_pack_weights(d, qx, qw, w, packed)
+    shape = (N, H, W, Cout)
+    y0, y1, y2 = (torch.full(shape, -7, dtype=dt, device="cuda") for _ in range(3))
+    acc0, acc1 = (torch.full(shape, -7, dtype=torch.int64, device="cuda") for _ in range(2))
+    count = torch.full((4,), 1000, dtype=torch.int64, device="cuda")
+    ws = torch.full((lp.lp_conv_workspace_bytes(d, qx, qw),), 0x5A, dtype=torch.uint8, device="cuda")
+    lp.lp_conv_fwd(d, x, qx, packed, qw, qy=qy, y_codes=y0)
+    lp.lp_conv_fwd(d, x, qx, packed, qw, acc_out=acc0)
+    lp.lp_conv_fwd(d, x, qx, packed, qw, qy=qy, y_codes=y1, zero_count=count[0:1], sat_count=count[1:2], workspace=ws)
+    lp.lp_conv_fwd(d, x, qx, packed, qw, qy=qy, y_codes=y2, acc_out=acc1, zero_count=count[2:3], sat_count=count[3:4], workspace=ws)
+    assert torch.equal(y0, y1) and torch.equal(y0, y2) and torch.equal(acc0, acc1)
+    zeros = int((y0 == 0).sum().item())
+    s = qx[2] + qw[2] - qy[2]
+    sats = int((((acc0.clamp(min=0) + (1 << (s - 1))) >> s) > top - 1).sum().item())
+    assert count.tolist() == [1000 + zeros, 1000 + sats] * 2 and sats > 0
+    assert info["path"] == 1

@@ -69,6 +69,8 @@ struct Plan {
     // each; each of the remaining tail tiles is cut along the reduction into `split` parts, so
     // that the last, partly filled round keeps every CU busy (see the kernel's merge step).
     int per_xcd, full_per_xcd, split, grid;
+    int kg;              // patch kernel: wave groups per workgroup (3: the wide form)
+    int ws_grid, ws_parts; // workgroups and parts the workspace is sized for (those of the one-group form)
     size_t part_bytes;   // bytes of one part's sums in the workspace
     size_t lds_bytes;
     size_t packed_bytes, corr_offset;
@@ -161,28 +163,32 @@ static size_t rows_lds_bytes(int pra, int pw, int cin, int pitch)
 // Three fit the two-limb kernel's registers as well, but the patches of the VGG16 layers are 6 to
 // 7 pieces per thread, which batches of two cover in 8 and batches of three in 12 (measured: 2 %
 // slower); four, which would put a whole patch in flight at once, spill.
-constexpr int kStageBatch = 2;
+// The wide form has three times the threads: batches of one, and three pieces up front.
+constexpr int stage_batch(int kg) { return kg > 1 ? 1 : 2; }
+constexpr int stage_deep(int kg) { return kg > 1 ? 3 : 8; }
 
 // Entries of the per-pixel patch tables.  The staging loops run whole batches of pieces, so they
 // overshoot the patch by less than two double batches and the first, deep batch covers 8 * 256
-// pieces whatever the patch size; the entries past the patch send those pieces to a source
+// pieces (wide form: 3 * 768) whatever the patch size; the entries past the patch send those pieces to a source
 // offset that reads as zeros and to a parking slot behind the plane.
-static int patch_table_len(int limbs, int npixa, int flat)
+static int patch_table_len(int limbs, int npixa, int flat, int kg = 1)
 {
     if (flat) return std::max(npixa, BM);
-    const int per_pass = 256 / (limbs == 2 ? 8 : 4); // pixels a pass of all threads covers
-    return std::max(npixa + 2 * kStageBatch * per_pass, 8 * per_pass);
+    const int per_pass = 256 * kg / (limbs == 2 ? 8 : 4); // pixels a pass of all threads covers
+    return std::max(npixa + 2 * stage_batch(kg) * per_pass, stage_deep(kg) * per_pass);
 }
 
 // LDS: tables (3*ntab + 2*BM ints, 3*bn ints of channel constants, BM pooled offsets), staged patch (one plane per
 // limb); the flat-window kernel: its fixed arrays (raw patch, weight operands, tables)
-static size_t mfma_lds_bytes(int limbs, int pra, int pw, int pitch_bytes, int bn, int flat)
+static size_t mfma_lds_bytes(int limbs, int pra, int pw, int pitch_bytes, int bn, int flat, int kg = 1)
 {
     if (flat) return (size_t)kFlatRawBytes + 8192 + 4096;
-    const int ntab = patch_table_len(limbs, pra * pw, flat);
+    const int ntab = patch_table_len(limbs, pra * pw, flat, kg);
     const size_t plane = (size_t)pra * pitch_bytes + PSP; // + the slot overshoot pieces are parked in
     size_t tables = round_up((size_t)(3 * ntab + 2 * BM) * 4, 16) + (size_t)3 * bn * 4 + (size_t)BM * 4;
-    return tables + (size_t)limbs * plane;
+    // wide form: two planes of two row blocks of four waves change hands in the patch's place
+    const size_t exchange = kg > 1 ? (size_t)4 * (bn / 64) * 4 * 256 * 16 : 0;
+    return tables + std::max((size_t)limbs * plane, exchange);
 }
 // LDS budgets tried in turn: three workgroups per CU (160 KB / 3), else two
 constexpr size_t kLdsBudgets[2] = {54400, 80000};
@@ -208,6 +214,43 @@ static int choose_split(int tail_tiles, int slots, int nslabs, size_t part_acc)
         }
     }
     return best;
+}
+
+// Wide form: three wave groups per workgroup, one workgroup per CU, for grids of at most one tile per CU
+// and parts of whole chunks.  It wins where the narrow form either leaves one wave per SIMD or cuts its
+// tiles and pays for the finishing kernel.  Narrow (conv + finishing) against wide, us:
+//   72 slabs: 256 tiles 38 + 15 : 47; 64 tiles 20 + 9.7 : 19 + 8.6; 56 tiles 18 + 8.9 : 16 + 8.6;
+//             200 tiles of one-limb weights 26 + 13 : 32
+//   50 slabs (5x5): 184 tiles 30 : 28
+//   36 slabs: 256 tiles 28.6 : 30.4, 112 tiles 23.9 : 22.8; 18 slabs: 168 tiles 16.8 : 17.8, 200 tiles
+//             17.4 : 17.6 -- the exchange and the third barrier-locked staging eat the gain, so the line is at 48
+//   two tiles per CU (400 tiles, 72 slabs): two narrow workgroups side by side are the better, 62 : 76
+//   at most two tiles on a die (16 tiles, 72 slabs): 11.5 + 6.5 : 11.7 + 6.4, narrow parts can be finer than a chunk
+static void choose_wide(Plan &p)
+{
+    constexpr int die = kCUs / kXCDs;
+    if (p.taps < 3 || p.taps * p.nchunks < 48 || p.per_xcd > die) return; // (a group takes whole taps)
+    if (p.split > 1 && p.per_xcd <= 2) return;
+    const size_t lds = mfma_lds_bytes(p.limbs, p.PRA, p.PW, p.PITCH, p.BN, 0, 3);
+    if (lds > kLdsBudgets[1]) return;
+    // Parts are whole chunks, and no more of them than the workspace holds.  In us: 0.7 a tap of the longest share,
+    // 0.9 a staging, 9 the finishing kernel.
+    const int most = p.full_per_xcd == 0 ? std::min(p.split, p.nchunks) : 1, tap_share = (p.taps + 2) / 3;
+    int best = 1;
+    double best_t = 1e300;
+    for (int s = 1; s <= most && p.per_xcd * s <= die; ++s) {
+        const int chunks = (p.nchunks + s - 1) / s;
+        const double t = chunks * (0.7 * tap_share + 0.9) + (s > 1 ? 9.0 : 0.0);
+        if (t < best_t) {
+            best_t = t;
+            best = s;
+        }
+    }
+    p.kg = 3;
+    p.lds_bytes = lds;
+    p.full_per_xcd = best > 1 ? 0 : p.per_xcd;
+    p.split = best;
+    p.grid = kXCDs * p.per_xcd * best;
 }
 
 // virtual row (in the stack of zero-padded images, Hp rows each) of stacked output row fr
@@ -361,6 +404,10 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
                 p.split = choose_split(p.per_xcd - p.full_per_xcd, slots, nslabs, (size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4);
             if (p.split == 1) p.full_per_xcd = p.per_xcd;
             p.grid = kXCDs * (p.full_per_xcd + (p.per_xcd - p.full_per_xcd) * p.split);
+            p.ws_grid = p.grid;
+            p.ws_parts = kXCDs * (p.per_xcd - p.full_per_xcd) * p.split;
+            p.kg = 1;
+            if (!one_slab && p.BN == 64) choose_wide(p);
         }
         p.corr_offset = p.rows ? round_up((size_t)p.KHP * 2 * p.CoutP * 32, 256)
                                : round_up((size_t)p.taps * p.nchunks * p.wl * p.CoutP * CK, 256);
@@ -544,17 +591,20 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(const ConvArgs a)
 // wave; the workgroup covers BN = 64*NB output channels with 2x2 waves of 64 x 32*NB each.
 // Waves per SIMD the registers of the patch kernel are budgeted for: three with 96 accumulator
 // registers (two-limb weights), else four.
-constexpr int patch_waves(int wl, int mb) { return wl == 2 && mb == 2 ? 3 : 4; }
+constexpr int patch_waves(int wl) { return wl == 2 ? 3 : 4; }
 
-template <int LIMBS, int WL, int NB, int MB>
-__global__ __launch_bounds__(MB == 2 ? 256 : 512)
-    __attribute__((amdgpu_waves_per_eu(patch_waves(WL, MB), patch_waves(WL, MB)))) void conv_mfma_kernel(const ConvArgs a)
+// KG: wave groups of four.  1: the workgroup above, several of them on a CU.  3 (the wide form, one
+// workgroup of 768 threads per CU): the groups share one staged patch and take a third of its taps each, and
+// their sums meet in LDS.  A grid of at most one tile per CU leaves a lone wave on each SIMD, which
+// keeps the matrix pipe less than half busy; see choose_wide.
+template <int LIMBS, int WL, int NB, int MB, int KG>
+__global__ __launch_bounds__(256 * KG)
+    __attribute__((amdgpu_waves_per_eu(KG > 1 ? 3 : patch_waves(WL), KG > 1 ? 3 : patch_waves(WL)))) void conv_mfma_kernel(const ConvArgs a)
 {
-    // MB: 32-row blocks per wave.  MB = 2: 4 waves (2 x 2) of 64 rows, the only form launched.
-    // MB = 1 (8 waves of 32 rows, a fourth wave per SIMD) is kept compilable as a tuning knob: with
-    // the weights read per wave it doubles their traffic and measured 14 % slower even on the
-    // smallest grids.
-    constexpr int THREADS = (MB == 2) ? 256 : 512;
+    // MB: 32-row blocks per wave: 4 waves (2 x 2) of 64 rows.  (8 waves of 32 rows, a fourth wave per SIMD, double
+    // the weight traffic and measured 14 % slower even on the smallest grids.)
+    static_assert(MB == 2, "two row blocks per wave");
+    constexpr int THREADS = 256 * KG;
     constexpr int WMC = BM / (32 * MB);       // waves along the pixel dimension
     constexpr int WROWS = 32 * MB;            // tile rows per wave
     constexpr int BN = 64 * NB;
@@ -635,7 +685,8 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
         }
         build_colterms<BN>(a, ntile, ctab, LIMBS, WL, deadmask);
     };
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = KG > 1 ? (tid >> 6) & 3 : tid >> 6; // the wave within its group
+    const int group = KG > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
     const int wm = wave % WMC, wn = wave / WMC;
     const int l32 = lane & 31, kg = lane >> 5;
 
@@ -685,8 +736,13 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
     // Weight slabs: slab (chunk, tap) lives at [chunk][tap][limb][K half][CoutP][32], i.e.
     // consecutive in memory in the order they are consumed; they never pass through LDS (see
     // the operand loads below).  t counts the slabs this workgroup multiplies.
-    const int nslabs = (skipping ? __builtin_popcount(livemask) : a.nchunks) * a.taps;
-    const int s0 = part * nslabs / nparts, s1 = (part + 1) * nslabs / nparts; // this workgroup's slabs
+    // A wide workgroup's parts are whole chunks, and a wave group takes the taps [tap0, tap1) of each of them.
+    const int nlive = skipping ? __builtin_popcount(livemask) : a.nchunks, nslabs = nlive * a.taps;
+    const int tap0 = KG > 1 ? group * a.taps / KG : 0, tap1 = KG > 1 ? (group + 1) * a.taps / KG : a.taps;
+    const int c0 = part * nlive / nparts;
+    // the slabs of this workgroup (of this wave group, counted from its first)
+    const int s0 = KG > 1 ? 0 : part * nslabs / nparts;
+    const int s1 = KG > 1 ? ((part + 1) * nlive / nparts - c0) * (tap1 - tap0) : (part + 1) * nslabs / nparts;
     const int slab_bytes = WL * a.CoutP * CK;
     constexpr bool LATE_ROWS = LIMBS == 2; // (the one-limb kernels' 128 registers leave no room for the overlap)
     if constexpr (!LATE_ROWS) row_tables();
@@ -710,8 +766,8 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
     // THREADS is a multiple of PIECES, a thread always handles the same piece of its pixels.
     // A chunk's channel sums are collected by the part that holds the chunk's first tap, so that
     // parts which share a chunk do not count it twice.
-    bool own_sums = (s0 % a.taps) == 0;
-    constexpr int APF = kStageBatch;
+    bool own_sums = KG > 1 || (s0 % a.taps) == 0;
+    constexpr int APF = stage_batch(KG);
     constexpr int PIECES = (LIMBS == 2) ? 8 : 4;
     constexpr int ESZ_X = (LIMBS == 2) ? 2 : 1;
     v4i aregA[APF], aregB[APF];
@@ -782,7 +838,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
 #pragma unroll
         for (int j = 0; j < APF; ++j) store_piece(first + j * THREADS, reg[j], at[j]);
     };
-    constexpr int DEEP = 8;
+    constexpr int DEEP = stage_deep(KG);
     // between(): work that does not depend on the patch, done while the first requests fly
     auto stage_activations = [&](int cc, bool deep, auto between) __attribute__((always_inline)) {
         // two batches of requests in flight; a request past the end of the patch reads as
@@ -829,10 +885,17 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
     // (when chunks are skipped the workgroup owns its whole tile: s0 = 0 and the first chunk is
     // the first one that is multiplied)
     int cc, tap, tap_r = 0, tap_s = 0;
-    udivmod(s0, a.taps, a.mg_taps, cc, tap);
+    if constexpr (KG > 1) {
+        cc = c0;
+        tap = tap0;
+    } else {
+        udivmod(s0, a.taps, a.mg_taps, cc, tap);
+    }
     if (skipping) cc = __builtin_ctz(livemask);
     udivmod(tap, a.S, a.mg_S, tap_r, tap_s);
     int taprow = tap_r * a.PITCH, tapoff = taprow + tap_s * PSP;
+    // where a chunk's first tap of this wave group lies (group 0, and a workgroup of one group: tap 0)
+    const int first_r = KG > 1 ? tap_r : 0, first_s = KG > 1 ? tap_s : 0;
     // Weights go straight from global memory / L2 into the MFMA operand registers, NSETS - 1
     // K=32 halves ahead of their use; with no slab to publish, the waves of a workgroup meet only
     // when a new patch is staged.  A lane's B operand for (slab, K half, limb, column block) is the
@@ -964,11 +1027,13 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
     for (int mb = 0; mb < MB; ++mb) afetch(mb, cur[mb], curl[mb]);
     auto step = [&](int t, auto P) __attribute__((always_inline)) {
         // move the bookkeeping on to slab t + 1
-        if (++tap == a.taps) {
-            tap = 0;
+        if (++tap == tap1) {
+            tap = tap0;
             cc = next_chunk(cc);
-            tap_s = tap_r = 0;
-            tapoff = taprow = 0;
+            tap_s = first_s;
+            tap_r = first_r;
+            taprow = first_r * a.PITCH;
+            tapoff = taprow + first_s * PSP;
         } else {
             tapoff += PSP;
             if (++tap_s == a.S) {
@@ -981,7 +1046,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
         int nxt[MB], nxtl[MB];
         fragment_offsets(nxt, nxtl);
         const bool more = t + 1 < s1;
-        const bool restage = more && tap == 0; // slab t + 1 opens a chunk: a new patch
+        const bool restage = more && tap == tap0; // slab t + 1 opens a chunk: a new patch
         wnext = more ? (cc * a.taps + tap) * slab_bytes : wcur;
         half_step(t, P, integral_constant<int, 0>{}, cur, curl, nxt, nxtl);
         half_step(t, P, integral_constant<int, 1>{}, cur, curl, nxt, nxtl);
@@ -1035,6 +1100,62 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
         return sum;
     };
 
+    // ---- wide form: the groups' sums meet in LDS, in the patch's place.  Group 0 ends up with row block 0 of
+    // its waves' tiles in acc[0], group 1 with row block 1: they swap halves, and group 2 hands over
+    // both.  One accumulator plane of one of the two transfers takes 32 KB; two of them go at a time.
+    if constexpr (KG > 1) {
+        static_assert(KG == 3, "two groups that finish, one that hands over");
+        v4i *const xch = (v4i *)Asm;
+        const int gtid = tid & 255;
+        auto put = [&](const v16i &c, int nb, int slot) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                xch[((slot * NB + nb) * 4 + j) * 256 + gtid] = (v4i){c[4 * j], c[4 * j + 1], c[4 * j + 2], c[4 * j + 3]};
+        };
+        auto add = [&](v16i &c, int nb, int slot) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const v4i p = xch[((slot * NB + nb) * 4 + j) * 256 + gtid];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) c[4 * j + e] += p[e];
+            }
+        };
+        // transfers in order: the swap of planes 0 .. NACC - 1, then group 2's planes from the last down
+#pragma unroll
+        for (int u0 = 0; u0 < 2 * NACC; u0 += 2) {
+            __syncthreads(); // the last fragments (the last transfers) have been read
+#pragma unroll
+            for (int u = u0; u < u0 + 2; ++u)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int q = u < NACC ? u : 2 * NACC - 1 - u, slot = 2 * (u - u0);
+                    if (u < NACC) {
+                        if (group == 0) put(acc[1][nb][q], nb, slot);
+                        if (group == 1) {
+                            put(acc[0][nb][q], nb, slot + 1);
+                            acc[0][nb][q] = acc[1][nb][q];
+                        }
+                    } else if (group == 2) {
+                        put(acc[0][nb][q], nb, slot);
+                        put(acc[1][nb][q], nb, slot + 1);
+                    }
+                }
+            __syncthreads();
+            if (group < 2) {
+#pragma unroll
+                for (int u = u0; u < u0 + 2; ++u)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const int q = u < NACC ? u : 2 * NACC - 1 - u, slot = 2 * (u - u0);
+                        add(acc[0][nb][q], nb, u < NACC ? slot + 1 - group : slot + group);
+                    }
+            }
+        }
+    }
+    // row blocks whose sums this wave holds: MBF of them from block mbf on
+    constexpr int MBF = KG > 1 ? 1 : MB;
+    const int mbf = KG > 1 ? group : 0;
+
     // ---- tail tiles: a part stores its accumulators and row sums and is done; the finishing
     // kernel adds the parts up (integer sums: the order cannot matter) and runs the epilogue.
     if (nparts > 1) {
@@ -1042,9 +1163,10 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
         v4i *mine = (v4i *)(a.partials + ((size_t)tail_tile * nparts + part) * a.part_bytes);
         constexpr int PP = part_planes(LIMBS, WL);
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
+        for (int mb = 0; mb < MBF; ++mb) {
+            if (KG > 1 && group >= 2) break; // handed over
             // the row's code sum joins the two planes: 128 * sum = 2^16 * (sum >> 9) + 128 * (sum & 511)
-            const int rs = WL == 2 ? row_sum(wm * WROWS + mb * 32 + l32) : 0;
+            const int rs = WL == 2 ? row_sum(wm * WROWS + (mbf + mb) * 32 + l32) : 0;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -1063,7 +1185,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
                         }
                     }
 #pragma unroll
-                    for (int q = 0; q < PP; ++q) mine[(((mb * NB + nb) * 4 + g) * PP + q) * THREADS + tid] = out[q];
+                    for (int q = 0; q < PP; ++q) mine[((((mbf + mb) * NB + nb) * 4 + g) * PP + q) * 256 + (tid & 255)] = out[q];
                 }
         }
         if (a.zero_partial && tid == 0) a.zero_partial[blockIdx.x] = a.zero_partial[a.partial_stride + blockIdx.x] = 0;
@@ -1071,14 +1193,26 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
         return;
     }
 
-    const TileCounts counts = tile_epilogue<LIMBS, WL, NB, BN, MB, 4>(a, acc, row_sum, outoff, pooloff, ctab, ntile, wm * WROWS,
-                                                                  wn * (NB * 32), 0, 0);
+    TileCounts counts = {0, 0};
+    if constexpr (KG > 1) {
+        if (group < 2) {
+            v16i fin[1][NB][NACC];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int q = 0; q < NACC; ++q) fin[0][nb][q] = acc[0][nb][q];
+            counts = tile_epilogue<LIMBS, WL, NB, BN, 1, 4>(a, fin, row_sum, outoff, pooloff, ctab, ntile, wm * WROWS,
+                                                           wn * (NB * 32), mbf, 0);
+        }
+    } else {
+        counts = tile_epilogue<LIMBS, WL, NB, BN, MB, 4>(a, acc, row_sum, outoff, pooloff, ctab, ntile, wm * WROWS, wn * (NB * 32), 0, 0);
+    }
     // one pair of counts per workgroup; on large grids they go to per-workgroup slots, not to the
     // counters: thousands of same-address atomics would serialise
     if (a.zero_partial || a.zout || a.direct_counts) {
         if (lane == 0) { // tab[] was last read while staging
-            tab[wave] = (int)counts.zeros;
-            tab[THREADS / 64 + wave] = (int)counts.sats;
+            tab[tid >> 6] = (int)counts.zeros;
+            tab[THREADS / 64 + (tid >> 6)] = (int)counts.sats;
         }
         __syncthreads();
         if (tid < 2) {
@@ -1086,7 +1220,7 @@ __global__ __launch_bounds__(MB == 2 ? 256 : 512)
             for (int w = 0; w < THREADS / 64; ++w) total += (unsigned)tab[tid * (THREADS / 64) + w];
             publish_count(a, tid, total);
         }
-        if (a.zout && wave == 0) {
+        if (a.zout && tid < 64) {
             // the tile's flag: it holds a code that is not zero (codes that exist: rows x channels)
             int rows = 0;
             for (int m = lane; m < BM; m += 64) rows += (int)wave_count(outoff[m] >= 0);
@@ -1650,7 +1784,7 @@ lp_status launch_sum_partials(const unsigned *partials, int n, unsigned long lon
     return launch_status();
 }
 
-template <int LIMBS, int WL, int NB, int MB>
+template <int LIMBS, int WL, int NB, int MB, int KG>
 static lp_status launch_mfma(const ConvArgs &a, const Plan &p, int grid, int tails, hipStream_t st)
 {
     // raise the dynamic LDS limit once per kernel instance and device
@@ -1658,12 +1792,12 @@ static lp_status launch_mfma(const ConvArgs &a, const Plan &p, int grid, int tai
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return LP_EDEVICE;
     if (!attr_set[dev].load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute((const void *)conv_mfma_kernel<LIMBS, WL, NB, MB>,
+        if (hipFuncSetAttribute((const void *)conv_mfma_kernel<LIMBS, WL, NB, MB, KG>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
             return LP_EDEVICE;
         attr_set[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((conv_mfma_kernel<LIMBS, WL, NB, MB>), dim3(grid), dim3(MB == 2 ? 256 : 512),
+    hipLaunchKernelGGL((conv_mfma_kernel<LIMBS, WL, NB, MB, KG>), dim3(grid), dim3(256 * KG),
                        p.lds_bytes, st, a);
     if (tails) { // the split tail tiles are merged and written by a second, small kernel
         // few tiles: a workgroup per unit; more: four units side by side, all of a tile's units at once
@@ -1681,11 +1815,10 @@ static WorkspaceLayout workspace_layout(const Plan &p)
 {
     WorkspaceLayout w = {0, 0};
     if (p.path != PATH_MFMA) return w;
-    const size_t tails = (size_t)kXCDs * (p.per_xcd - p.full_per_xcd);
-    w.partials = round_up((size_t)2 * p.grid * sizeof(unsigned), 256); // zero counts, counts of clipped values
+    w.partials = round_up((size_t)2 * p.ws_grid * sizeof(unsigned), 256); // zero counts, counts of clipped values
     // sized for every accumulator plane and the row sums of a part (the contract of lp_conv_workspace_bytes
     // and of what the static array holds); two-limb sums are combined and use two thirds of it
-    w.total = w.partials + tails * p.split * ((size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4 + (size_t)BM * 4);
+    w.total = w.partials + (size_t)p.ws_parts * ((size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4 + (size_t)BM * 4);
     return w;
 }
 
@@ -1767,7 +1900,7 @@ static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, 
         return launch_status();
     }
     a.RH = p.RH; a.TW = p.TW; a.PW = p.PW; a.NPIXA = p.NPIXA;
-    a.NTAB = patch_table_len(p.limbs, p.NPIXA, p.flat);
+    a.NTAB = patch_table_len(p.limbs, p.NPIXA, p.flat, p.kg);
     a.PITCH = p.PITCH;
     a.APLANE = p.flat ? 0 : p.rows ? p.PRA * p.PITCH + 32 : p.PRA * p.PITCH + PSP; // the last slot of a plane parks overshoot pieces
     a.KHR = p.KHR; a.KHP = p.KHP;
@@ -1833,9 +1966,10 @@ static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, 
         }
         st2 = launch_status();
     }
-    else if (p.wl == 2) st2 = launch_mfma<2, 2, 1, 2>(a, p, grid, tails, hs);
-    else if (p.limbs == 2) st2 = launch_mfma<2, 1, 1, 2>(a, p, grid, tails, hs);
-    else st2 = p.BN == 128 ? launch_mfma<1, 1, 2, 2>(a, p, grid, tails, hs) : launch_mfma<1, 1, 1, 2>(a, p, grid, tails, hs);
+    else if (p.wl == 2) st2 = p.kg > 1 ? launch_mfma<2, 2, 1, 2, 3>(a, p, grid, tails, hs) : launch_mfma<2, 2, 1, 2, 1>(a, p, grid, tails, hs);
+    else if (p.limbs == 2) st2 = p.kg > 1 ? launch_mfma<2, 1, 1, 2, 3>(a, p, grid, tails, hs) : launch_mfma<2, 1, 1, 2, 1>(a, p, grid, tails, hs);
+    else if (p.BN == 128) st2 = launch_mfma<1, 1, 2, 2, 1>(a, p, grid, tails, hs);
+    else st2 = p.kg > 1 ? launch_mfma<1, 1, 1, 2, 3>(a, p, grid, tails, hs) : launch_mfma<1, 1, 1, 2, 1>(a, p, grid, tails, hs);
     if (st2 != LP_OK || tails || !counting || direct) return st2;
     return launch_sum_partials(a.zero_partial, grid, (unsigned long long *)zero_count, (unsigned long long *)sat_count, hs);
 }

@@ -530,3 +530,22 @@ def test_merged_parts_equal_whole_tiles(form):
     sats = int((((acc0.clamp(min=0) + (1 << (s - 1))) >> s) > top - 1).sum().item())
     assert count.tolist() == [1000 + zeros, 1000 + sats] * 2 and sats > 0
     assert info["path"] == 1
+
+
+@pytest.mark.parametrize("shape,R,qx,qw,split", [
+    ((3, 72, 17, 13, 200), 5, QX, QW, False),                    # 25 taps over three groups, a last chunk of 8 channels
+    ((3, 72, 17, 13, 200), 5, QX, (8, 1, 7), False),             # one weight limb
+    ((3, 80, 17, 13, 200), 5, (8, 4, 4), (8, 1, 7), False),      # one limb each
+    ((24, 384, 7, 7, 132), 3, QX, QW, True),                     # tiles that straddle images, parts of whole chunks
+    ((1, 448, 28, 28, 200), 3, QX, (8, 1, 7), True),
+    ((19, 448, 14, 14, 256), 3, QX, QW, False),                  # 120 whole tiles
+])
+def test_three_wave_groups_per_workgroup(oracle, shape, R, qx, qw, split):
+    """Grids of at most a tile per CU with a long reduction: three wave groups share a staged patch and add their
+    sums up in LDS (seen by the LDS the exchange takes), whole or cut into parts of whole chunks."""
+    N, Cin, H, W, Cout = shape
+    info = lp.lp_conv_plan_info(lp.ConvDesc(N, H, W, Cin, Cout, R, R, 1, R // 2), qx, qw)
+    assert info["lds_bytes"] > 65536 and (info["split"] > 1) == split
+    rng = np.random.default_rng(N + Cin + R)
+    x, w = _codes(rng, (N, Cin, H, W), n=qx[0], zero_frac=0.5), _codes(rng, (Cout, Cin, R, R), n=qw[0])
+    _check(oracle, x, w, qx, qw, (16, 12, 4), pad=R // 2, expect_path=1)

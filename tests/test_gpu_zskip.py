@@ -199,3 +199,15 @@ def test_stack_with_zero_skipping_matches_oracle_chain(oracle):
             assert int(st.zero_counts[i].item()) == L["zeros"] and int(st.sat_counts[i].item()) == L["sats"]
         assert np.array_equal(out.cpu().numpy().astype(np.int32).transpose(0, 3, 1, 2), want["final"])
         assert int(st.skipped[1:].sum().item()) > 0 or all(G["info"]["split"] > 1 for G in st.layers[1:])
+
+
+def test_skipping_in_the_three_wave_group_form(oracle):
+    """A grid of at most a tile per CU with 8 chunks: the wave groups of a workgroup leave out the same chunks."""
+    rng = np.random.default_rng(9)
+    x, w1, w2 = _sparse_pair(rng, 18, 64, 14, 14, 512, 320)
+    a = _layer(x, w1, QX, QW, QY)
+    y1, _ = oracle.act(oracle.conv(x, w1, threads=8), 27, *QY, True, oracle.ROUND_AWAY)
+    b = _layer(y1, w2, QY, QW, (16, 9, 7), x_map=lp.zero_map(a["flags"], a["info"], a["W"]))
+    assert b["info"]["lds_bytes"] > 65536 and b["info"]["split"] == 1 and b["skipped"] > 0
+    y2, z2, s2 = oracle.act(oracle.conv(y1, w2, threads=8), QY[2] + QW[2], 16, 9, 7, True, oracle.ROUND_AWAY, with_sat=True)
+    assert np.array_equal(b["y_np"], y2) and (b["zeros"], b["sats"]) == (z2, s2)

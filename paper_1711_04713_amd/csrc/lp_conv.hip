@@ -222,15 +222,17 @@ static int choose_split(int tail_tiles, int slots, int nslabs, size_t part_acc)
 //   72 slabs: 256 tiles 38 + 15 : 47; 64 tiles 20 + 9.7 : 19 + 8.6; 56 tiles 18 + 8.9 : 16 + 8.6;
 //             200 tiles of one-limb weights 26 + 13 : 32
 //   50 slabs (5x5): 184 tiles 30 : 28
-//   36 slabs: 256 tiles 28.6 : 30.4, 112 tiles 23.9 : 22.8; 18 slabs: 168 tiles 16.8 : 17.8, 200 tiles
-//             17.4 : 17.6 -- the exchange and the third barrier-locked staging eat the gain, so the line is at 48
-//   two tiles per CU (400 tiles, 72 slabs): two narrow workgroups side by side are the better, 62 : 76
-//   at most two tiles on a die (16 tiles, 72 slabs): 11.5 + 6.5 : 11.7 + 6.4, narrow parts can be finer than a chunk
+//   36 slabs: 112 tiles 23.9 : 22.8, 56 tiles 14 + 8.2 : 21.2, 256 tiles 28.6 : 30.4
+//   18 slabs and fewer: 168 tiles 16.8 : 17.8, 200 tiles 17.4 : 17.6 -- the exchange and the stagings every wave
+//             waits for eat the gain, so the line is at 36 (VGG16 at batch 1: 274 us with it at 48, 263 at 36)
+//   two tiles per CU (400 tiles, 72 slabs): two narrow workgroups side by side are the better one (VGG16 at
+//             batch 32: 1.75 ms, 1.79 with its last three layers wide)
+//   at most two tiles on a die: narrow parts can be finer than a chunk; equal at 8 chunks (16 tiles: 18 : 18)
 static void choose_wide(Plan &p)
 {
     constexpr int die = kCUs / kXCDs;
-    if (p.taps < 3 || p.taps * p.nchunks < 48 || p.per_xcd > die) return; // (a group takes whole taps)
-    if (p.split > 1 && p.per_xcd <= 2) return;
+    if (p.taps < 3 || p.taps * p.nchunks < 36 || p.per_xcd > die) return; // (a group takes whole taps)
+    if (p.split > 1 && p.per_xcd <= 2 && p.nchunks < 8) return;
     const size_t lds = mfma_lds_bytes(p.limbs, p.PRA, p.PW, p.PITCH, p.BN, 0, 3);
     if (lds > kLdsBudgets[1]) return;
     // Parts are whole chunks, and no more of them than the workspace holds.  In us: 0.7 a tap of the longest share,

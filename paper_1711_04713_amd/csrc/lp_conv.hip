@@ -70,7 +70,6 @@ struct Plan {
     // that the last, partly filled round keeps every CU busy (see the kernel's merge step).
     int per_xcd, full_per_xcd, split, grid;
     int kg;              // patch kernel: wave groups per workgroup (3: the wide form)
-    int ws_grid, ws_parts; // workgroups and parts the workspace is sized for (those of the one-group form)
     size_t part_bytes;   // bytes of one part's sums in the workspace
     size_t lds_bytes;
     size_t packed_bytes, corr_offset;
@@ -235,7 +234,7 @@ static void choose_wide(Plan &p)
     if (p.split > 1 && p.per_xcd <= 2 && p.nchunks < 8) return;
     const size_t lds = mfma_lds_bytes(p.limbs, p.PRA, p.PW, p.PITCH, p.BN, 0, 3);
     if (lds > kLdsBudgets[1]) return;
-    // Parts are whole chunks, and no more of them than the workspace holds.  In us: 0.7 a tap of the longest share,
+    // Parts are whole chunks, and no more of them than the narrow form would cut.  In us: 0.7 a tap of the longest share,
     // 0.9 a staging, 9 the finishing kernel.
     const int most = p.full_per_xcd == 0 ? std::min(p.split, p.nchunks) : 1, tap_share = (p.taps + 2) / 3;
     int best = 1;
@@ -406,8 +405,6 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
                 p.split = choose_split(p.per_xcd - p.full_per_xcd, slots, nslabs, (size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4);
             if (p.split == 1) p.full_per_xcd = p.per_xcd;
             p.grid = kXCDs * (p.full_per_xcd + (p.per_xcd - p.full_per_xcd) * p.split);
-            p.ws_grid = p.grid;
-            p.ws_parts = kXCDs * (p.per_xcd - p.full_per_xcd) * p.split;
             p.kg = 1;
             if (!one_slab && p.BN == 64) choose_wide(p);
         }
@@ -1817,10 +1814,11 @@ static WorkspaceLayout workspace_layout(const Plan &p)
 {
     WorkspaceLayout w = {0, 0};
     if (p.path != PATH_MFMA) return w;
-    w.partials = round_up((size_t)2 * p.ws_grid * sizeof(unsigned), 256); // zero counts, counts of clipped values
+    const size_t parts = p.split > 1 ? (size_t)kXCDs * (p.per_xcd - p.full_per_xcd) * p.split : 0;
+    w.partials = round_up((size_t)2 * p.grid * sizeof(unsigned), 256); // zero counts, counts of clipped values
     // sized for every accumulator plane and the row sums of a part (the contract of lp_conv_workspace_bytes
     // and of what the static array holds); two-limb sums are combined and use two thirds of it
-    w.total = w.partials + (size_t)p.ws_parts * ((size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4 + (size_t)BM * 4);
+    w.total = w.partials + parts * ((size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4 + (size_t)BM * 4);
     return w;
 }
 

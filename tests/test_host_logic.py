@@ -233,3 +233,24 @@ def test_pool_check_lists_every_condition_of_the_fused_pool():
         assert not lp.lp_conv_pool_check(wide, Q16, W16, (16, 6, 10))
     except lp.LpError as e:                                                        # or no poolable tiling at all
         assert e.status == 2
+
+
+@pytest.mark.parametrize("shape,whole", [
+    ((5, 28, 28, 512, 512), True),       # three wave groups, every tile in one workgroup
+    ((15, 14, 14, 512, 512), True),
+    ((2, 28, 28, 512, 512), False),      # cut into parts
+    ((20, 28, 28, 512, 512), False),     # one wave group, the last round's tiles cut
+    ((1, 14, 14, 512, 512), False),
+])
+def test_workspace_is_that_of_the_form_that_runs(shape, whole):
+    """lp_conv_workspace_bytes asks for two counters per workgroup of the launch and for the parts
+    that are really cut: none where every tile is reduced by one workgroup."""
+    N, H, W, Cin, Cout = shape
+    d = lp.ConvDesc(N, H, W, Cin, Cout, 3, 3, 1, 1)
+    info = lp.lp_conv_plan_info(d, Q16, W16)
+    assert (info["split"] == 1) == whole
+    cut = 8 * (info["items_per_die"] - info["whole_items_per_die"])
+    slots = (8 * info["workgroups"] + 255) // 256 * 256
+    part = 128 * info["bn"] * 3 * 4 + 128 * 4
+    assert lp.lp_conv_workspace_bytes(d, Q16, W16) == slots + cut * info["split"] * part
+    assert info["workgroups"] == 8 * info["whole_items_per_die"] + cut * info["split"]

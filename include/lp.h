@@ -262,7 +262,9 @@ lp_status lp_conv_fwd_zskip(const lp_conv_desc *d, const void *x_codes_dev, lp_q
  * an array of LP_STATIC_WORKSPACE_BYTES that the library's code object holds on every GPU it is
  * loaded on, until the process ends; the call allocates nothing on host or device through HIP.
  * Arguments, results and errors as lp_conv_fwd (with that workspace passed); problems whose
- * lp_conv_workspace_bytes exceeds LP_STATIC_WORKSPACE_BYTES return LP_EWORKSPACE.  The array
+ * lp_conv_workspace_bytes exceeds LP_STATIC_WORKSPACE_BYTES return LP_EWORKSPACE, except that
+ * 16-bit activations with 8-bit weights then run with fewer shared reductions, or none, which
+ * always fits (same results, idle CUs in the last round).  The array
  * used is that of the device current at the call, which must be the stream's device.  All calls
  * on one GPU share the array: calls that overlap in time on one GPU (different streams or
  * threads) race; calls on one stream are ordered and safe.  Nothing is carried from call to call.

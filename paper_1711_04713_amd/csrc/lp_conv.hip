@@ -197,14 +197,14 @@ constexpr size_t kLdsBudgets[2] = {54400, 80000};
 // slabs (tables, first patch, epilogue or partial store) on top of its share of the slabs, the
 // tail takes as many rounds as its parts need slots, the finishing kernel costs about 6, and
 // every part adds traffic (its accumulators are written once and read once).  A split must
-// promise a clear gain over the plain launch to be taken.
-static int choose_split(int tail_tiles, int slots, int nslabs, size_t part_acc)
+// promise a clear gain over the plain launch to be taken.  most: parts allowed.
+static int choose_split(int tail_tiles, int slots, int nslabs, size_t part_acc, int most)
 {
     const double fixed = 10.0, finish = 6.0, per_part = 0.03 * (double)part_acc / 98304.0;
     const double whole = nslabs + fixed;
     int best = 1;
     double best_t = 0.8 * whole;
-    for (int s = 2; s <= std::min(nslabs, 8); ++s) {
+    for (int s = 2; s <= std::min(nslabs, most); ++s) {
         const int rounds = (tail_tiles * s + slots - 1) / slots;
         const double t = rounds * ((double)nslabs / s + fixed) + finish + per_part * kXCDs * tail_tiles * s;
         if (t < best_t) {
@@ -252,6 +252,34 @@ static void choose_wide(Plan &p)
     p.full_per_xcd = best > 1 ? 0 : p.per_xcd;
     p.split = best;
     p.grid = kXCDs * p.per_xcd * best;
+}
+
+constexpr int kMaxParts = 8; // most parts a tile is cut into
+
+// The launch of a plan whose tile geometry is chosen: whole and split tiles, narrow or wide form.
+// most: parts allowed per tile
+static void plan_launch(Plan &p, int Cin, int Cout, int most)
+{
+    const bool one_slab = p.flat || p.rows; // nothing to cut along the reduction
+    p.kg = 1;
+    p.lds_bytes = p.rows ? rows_lds_bytes(p.PRA, p.PW, Cin, p.PITCH)
+                         : mfma_lds_bytes(p.limbs, p.PRA, p.PW, p.PITCH, p.BN, p.flat);
+    // workgroup slots per die: what registers and LDS allow
+    const int total = p.tiles_m * p.tiles_n, nslabs = p.nchunks * p.taps;
+    // (two-limb weights: three waves per SIMD by registers; one-limb weights: four)
+    // (window-row kernel: four, or three where it takes two column blocks)
+    const int by_regs = p.rows ? (Cout <= 32 ? 4 : 3) : p.wl == 2 ? 3 : 4;
+    const int wg_per_cu = (int)std::max<size_t>(1, std::min<size_t>(by_regs, (160 * 1024) / p.lds_bytes));
+    const int slots = wg_per_cu * (kCUs / kXCDs);
+    p.per_xcd = (total + kXCDs - 1) / kXCDs;
+    p.full_per_xcd = p.per_xcd / slots * slots;
+    p.part_bytes = (size_t)BM * p.BN * part_planes(p.limbs, p.wl) * 4;
+    p.split = 1;
+    if (p.per_xcd > p.full_per_xcd && nslabs > 1)
+        p.split = choose_split(p.per_xcd - p.full_per_xcd, slots, nslabs, (size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4, most);
+    if (p.split == 1) p.full_per_xcd = p.per_xcd;
+    p.grid = kXCDs * (p.full_per_xcd + (p.per_xcd - p.full_per_xcd) * p.split);
+    if (!one_slab && p.BN == 64) choose_wide(p);
 }
 
 // virtual row (in the stack of zero-padded images, Hp rows each) of stacked output row fr
@@ -387,27 +415,7 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
         if (p.limbs == 2) p.BN = 64;
         p.tiles_n = p.CoutP / p.BN;
         if (!p.rows) p.PITCH = p.flat ? 0 : 16 * choose_pitch(p.PW, p.TW, p.RH, d->R, d->S);
-        p.lds_bytes = p.rows ? rows_lds_bytes(p.PRA, p.PW, d->Cin, p.PITCH)
-                             : mfma_lds_bytes(p.limbs, p.PRA, p.PW, p.PITCH, p.BN, p.flat);
-        {
-            // workgroup slots per die: what registers and LDS allow
-            const int total = p.tiles_m * p.tiles_n, nslabs = p.nchunks * p.taps;
-            // (two-limb weights: three waves per SIMD by registers; one-limb weights: four)
-            // (window-row kernel: four, or three where it takes two column blocks)
-            const int by_regs = p.rows ? (d->Cout <= 32 ? 4 : 3) : p.wl == 2 ? 3 : 4;
-            const int wg_per_cu = (int)std::max<size_t>(1, std::min<size_t>(by_regs, (160 * 1024) / p.lds_bytes));
-            const int slots = wg_per_cu * (kCUs / kXCDs);
-            p.per_xcd = (total + kXCDs - 1) / kXCDs;
-            p.full_per_xcd = p.per_xcd / slots * slots;
-            p.part_bytes = (size_t)BM * p.BN * part_planes(p.limbs, p.wl) * 4;
-            p.split = 1;
-            if (p.per_xcd > p.full_per_xcd && nslabs > 1)
-                p.split = choose_split(p.per_xcd - p.full_per_xcd, slots, nslabs, (size_t)BM * p.BN * (p.limbs + p.wl - 1) * 4);
-            if (p.split == 1) p.full_per_xcd = p.per_xcd;
-            p.grid = kXCDs * (p.full_per_xcd + (p.per_xcd - p.full_per_xcd) * p.split);
-            p.kg = 1;
-            if (!one_slab && p.BN == 64) choose_wide(p);
-        }
+        plan_launch(p, d->Cin, d->Cout, kMaxParts);
         p.corr_offset = p.rows ? round_up((size_t)p.KHP * 2 * p.CoutP * 32, 256)
                                : round_up((size_t)p.taps * p.nchunks * p.wl * p.CoutP * CK, 256);
         // the kernel addresses the slabs with 32-bit byte offsets
@@ -1838,10 +1846,11 @@ static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, 
                               lp_qfmt qw, const void *bias, lp_qfmt qb, int64_t *acc_out, void *y,
                               lp_qfmt qy, int relu, lp_round r, uint64_t *zero_count, uint64_t *sat_count,
                               void *workspace, size_t workspace_bytes, void *stream,
-                              const lp_zero_map *x_map = nullptr, uint8_t *y_flags = nullptr, uint64_t *skipped = nullptr)
+                              const lp_zero_map *x_map = nullptr, uint8_t *y_flags = nullptr, uint64_t *skipped = nullptr,
+                              const Plan *plan = nullptr)
 {
     Plan p;
-    lp_status st = make_plan(d, qx, qw, &p);
+    lp_status st = plan ? (p = *plan, LP_OK) : make_plan(d, qx, qw, &p);
     if (st != LP_OK) return st;
     if (!x || !wp || (!acc_out && !y) || !aligned16(x) || !aligned16(wp)) return LP_EINVAL;
     if ((acc_out && !aligned16(acc_out)) || (y && !aligned16(y))) return LP_EINVAL;
@@ -2173,13 +2182,18 @@ extern "C" lp_status lp_conv_fwd_static(const lp_conv_desc *d, const void *x_cod
     Plan p;
     const lp_status st = make_plan(d, qx, qw, &p);
     if (st != LP_OK) return st;
+    // 8-bit weights under 16-bit activations: their kernel's four workgroups per CU make tails, and parts of
+    // them, that this array may not hold; then with fewer parts, or none
+    if (p.limbs == 2 && p.wl == 1)
+        for (int most = p.split - 1; most >= 1 && workspace_layout(p).total > (size_t)LP_STATIC_WORKSPACE_BYTES; --most)
+            plan_launch(p, d->Cin, d->Cout, most);
     if (workspace_layout(p).total > (size_t)LP_STATIC_WORKSPACE_BYTES) return LP_EWORKSPACE;
     void *ws = nullptr;
     const lp_status sp = static_scratch(&ws);
     if (sp != LP_OK) return sp;
     return conv_forward(d, x_codes_dev, qx, w_packed_dev, qw, bias_codes_dev, qb, acc_out_dev,
                         y_codes_dev, qy, relu, r, zero_count_dev, sat_count_dev, ws,
-                        (size_t)LP_STATIC_WORKSPACE_BYTES, stream);
+                        (size_t)LP_STATIC_WORKSPACE_BYTES, stream, nullptr, nullptr, nullptr, &p);
 }
 
 lp_status lp::fc_conv_packed_bytes(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw,

@@ -3,6 +3,7 @@ symbol include/lp.h declares, argument validation refuses bad calls before any l
 tile geometry the planner hands to the MFMA kernel addresses exactly the pixels the
 convolution's definition names (simulated here with the kernel's index formulas).
 No GPU compute is called."""
+import ctypes
 import os
 import re
 
@@ -254,3 +255,18 @@ def test_workspace_is_that_of_the_form_that_runs(shape, whole):
     part = 128 * info["bn"] * 3 * 4 + 128 * 4
     assert lp.lp_conv_workspace_bytes(d, Q16, W16) == slots + cut * info["split"] * part
     assert info["workgroups"] == 8 * info["whole_items_per_die"] + cut * info["split"]
+
+
+@pytest.mark.parametrize("shape,R", [
+    ((8, 28, 28, 1024, 512), 5), ((17, 24, 16, 896, 630), 3), ((2, 80, 26, 400, 396), 7), ((9, 16, 77, 1200, 181), 7),
+])
+def test_static_entry_takes_every_8bit_weight_layer(shape, R):
+    """16-bit activations with 8-bit weights whose partial sums exceed the static array: the call is not
+    refused for it (it gets as far as the null pointers, or the missing device)."""
+    N, H, W, Cin, Cout = shape
+    d = lp.ConvDesc(N, H, W, Cin, Cout, R, R, 1, R // 2)
+    assert lp.lp_conv_workspace_bytes(d, Q16, W8) > lp.LP_STATIC_WORKSPACE_BYTES
+    fmt = lambda q: lp.QFmt(*q)
+    status = lp.load().lp_conv_fwd_static(ctypes.byref(d), None, fmt(Q16), None, fmt(W8), None, lp.QFmt(), None, None,
+                                          fmt(Q16), 1, lp.LP_ROUND_NEAREST_AWAY, None, None, None)
+    assert status in (1, 4)

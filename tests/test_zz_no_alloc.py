@@ -60,3 +60,27 @@ def test_static_workspace_entry_point_matches_lp_conv_fwd():
                                   torch.empty(16, dtype=torch.uint8, device="cuda"), QW, qy=QY,
                                   y_codes=torch.empty(16, dtype=torch.int16, device="cuda"))
         assert e.value.status == 3
+
+
+@pytest.mark.parametrize("shape", [(17, 24, 16, 896, 630), (9, 24, 16, 896, 630)])
+def test_static_workspace_with_fewer_parts(shape):
+    """8-bit weights under 16-bit activations: the first layer's parts exceed the array and it is cut
+    into fewer, the second's fit."""
+    N, H, W, Cin, Cout = shape
+    qw = (8, 1, 7)
+    d = lp.ConvDesc(N, H, W, Cin, Cout, 3, 3, 1, 1)
+    assert (lp.lp_conv_workspace_bytes(d, QX, qw) > lp.LP_STATIC_WORKSPACE_BYTES) == (N == 17)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    x = torch.randint(-32768, 32768, (N, H, W, Cin), device="cuda", generator=gen).to(torch.int16)
+    w = torch.randint(-128, 128, (Cout, 3, 3, Cin), device="cuda", generator=gen).to(torch.int8)
+    packed = torch.empty(lp.lp_conv_packed_bytes(d, QX, qw), dtype=torch.uint8, device="cuda")
+    lp.lp_conv_pack_weights(d, QX, qw, w, packed)
+    y = [torch.full((N, H, W, Cout), -7, dtype=torch.int16, device="cuda") for _ in range(2)]
+    count = torch.zeros(4, dtype=torch.int64, device="cuda")
+    ws = torch.empty(lp.lp_conv_workspace_bytes(d, QX, qw), dtype=torch.uint8, device="cuda")
+    lp.lp_conv_fwd(d, x, QX, packed, qw, qy=QY, y_codes=y[0], zero_count=count[0:1], sat_count=count[1:2], workspace=ws)
+    lp.lp_conv_fwd_static(d, x, QX, packed, qw, qy=QY, y_codes=y[1], zero_count=count[2:3], sat_count=count[3:4])
+    assert torch.equal(y[0], y[1]) and int((y[0] == -7).sum().item()) == 0
+    zeros = int((y[0] == 0).sum().item())
+    assert count[0].item() == count[2].item() == zeros > 0 and count[1].item() == count[3].item() > 0

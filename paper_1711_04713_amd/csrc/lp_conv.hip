@@ -690,7 +690,7 @@ __global__ __launch_bounds__(256 * KG)
             abase_s[m] = ok ? (img * a.Hp + yo - vr0) * a.PW + t : 0;
             pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
         }
-        build_colterms<BN>(a, ntile, ctab, LIMBS, WL, deadmask);
+        build_colterms<BN>(a, ntile, ctab, THREADS, LIMBS, WL, deadmask);
     };
     const int lane = tid & 63, wave = KG > 1 ? (tid >> 6) & 3 : tid >> 6; // the wave within its group
     const int group = KG > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
@@ -1297,7 +1297,7 @@ __global__ __launch_bounds__(1024) void conv_finish_kernel(const ConvArgs a, int
                     pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1))
                                      ? ((fr / a.Ho) * (a.Ho >> 1) + ((fr % a.Ho) >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
                 }
-                build_colterms<BN>(a, ntile, ctab, LIMBS, WL);
+                build_colterms<BN>(a, ntile, ctab, threads, LIMBS, WL);
             }
             int sum[NB][PP][4];
 #pragma unroll
@@ -1501,7 +1501,7 @@ __global__ __launch_bounds__(256)
         abase[m] = ok ? ((img * a.Hp + yo - vr0) * a.PW + t) * a.Cin * 2 : 0;
         pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
     }
-    build_colterms<BN>(a, ntile, ctab, 2, 2);
+    build_colterms<BN>(a, ntile, ctab, THREADS, 2, 2);
 #pragma unroll
     for (int i = 0; i < WPT; ++i)
         if (wave + 4 * i < WPIECES) wlds[wave + 4 * i][lane] = wreg[i];
@@ -1706,7 +1706,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         ubase[m] = ok ? prow * a.UPR + t * a.CU : 0;
         pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
     }
-    build_colterms<BN>(a, ntile, ctab, 2, 2);
+    build_colterms<BN>(a, ntile, ctab, THREADS, 2, 2);
     __syncthreads();
 
     // the sum of the codes under the row's window: its two lanes take alternate window rows

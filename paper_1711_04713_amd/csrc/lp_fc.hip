@@ -254,7 +254,7 @@ __device__ __forceinline__ void fc_tile_tables(const FcArgs &f, int mt, int nt, 
         }
         rowsum[m] = t;
     }
-    build_colterms<FN>(f.c, nt, ctab, LIMBS, LIMBS);
+    build_colterms<FN>(f.c, nt, ctab, blockDim.x, LIMBS, LIMBS);
 }
 
 // Sums in the 32-bit pieces the epilogue combines <-> one exact int64 per output.

@@ -137,11 +137,13 @@ __device__ __forceinline__ int requant_relu32(int hi, int lo16, int s)
 // correction, 128 * sum(w over the chunk) - 16384 * (positions of the chunk), is taken out again
 // (their limb products, which it would have cancelled, were never formed).  With 8-bit weights under
 // 16-bit activations (limbs 2, wlimbs 1) the correction has no 16384 * K term: the weights carry no offset.
+// threads: of the workgroup, a constant where the kernel knows it (blockDim comes from memory, and
+// that read is as long as all else here: 0.5 us of a one-limb layer of one round)
 template <int BN>
-__device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int *ctab, int limbs, int wlimbs,
+__device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int *ctab, int threads, int limbs, int wlimbs,
                                               unsigned deadmask = 0)
 {
-    for (int c = threadIdx.x; c < BN; c += blockDim.x) {
+    for (int c = threadIdx.x; c < BN; c += threads) {
         const int colg = ntile * BN + c;
         int64_t t = colg < a.Cout ? a.corr[colg] + bias_term(a, colg) : 0;
         if (limbs == 2 && deadmask && colg < a.Cout) {

@@ -42,6 +42,8 @@ constexpr int kMaxDevices = 64;
 // tail at batch 64 793 / 794 / 779 / 781, Giga1Net at batch 32 271 / 270 / 266 / 265.
 constexpr int kDirectCountGrid = 640;
 
+constexpr int kMaxParts = 8; // most parts a tile is cut into
+
 // int32 planes a part of a split tile leaves per output: two-limb sums meet as 2^16 * hi + lo, whose
 // pieces stay inside 32 bits over all parts together (K < 65536: |HH|, |LL| < 2^30, the carries
 // from the middle plane and the row sums are below 2^24 and, per part, 2^17); one weight limb
@@ -253,8 +255,6 @@ static void choose_wide(Plan &p)
     p.split = best;
     p.grid = kXCDs * p.per_xcd * best;
 }
-
-constexpr int kMaxParts = 8; // most parts a tile is cut into
 
 // The launch of a plan whose tile geometry is chosen: whole and split tiles, narrow or wide form.
 // most: parts allowed per tile
@@ -690,7 +690,11 @@ __global__ __launch_bounds__(256 * KG)
             abase_s[m] = ok ? (img * a.Hp + yo - vr0) * a.PW + t : 0;
             pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1)) ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
         }
-        build_colterms<BN>(a, ntile, ctab, THREADS, LIMBS, WL, deadmask);
+        // two limbs: the stride is hidden from the compiler, which else mixes this one-trip loop into the staging
+        // around it (8x28x28, 192 -> 128, 16-bit under 8-bit weights: 13.7 us, 14.05 with the constant)
+        int threads = THREADS;
+        if constexpr (LIMBS == 2) asm volatile("" : "+s"(threads));
+        build_colterms<BN>(a, ntile, ctab, threads, LIMBS, WL, deadmask);
     };
     const int lane = tid & 63, wave = KG > 1 ? (tid >> 6) & 3 : tid >> 6; // the wave within its group
     const int group = KG > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
@@ -1173,7 +1177,18 @@ __global__ __launch_bounds__(256 * KG)
         for (int mb = 0; mb < MBF; ++mb) {
             if (KG > 1 && group >= 2) break; // handed over
             // the row's code sum joins the two planes: 128 * sum = 2^16 * (sum >> 9) + 128 * (sum & 511)
-            const int rs = WL == 2 ? row_sum(wm * WROWS + (mbf + mb) * 32 + l32) : 0;
+            // (a row's two lanes take alternate window rows: one lane's 49 reads of a 7x7 window cost a part 1 us)
+            int rs = 0;
+            if constexpr (WL == 2) {
+                const int m = wm * WROWS + (mbf + mb) * 32 + l32;
+                if (a.R == 3 && a.S == 3) {
+                    rs = row_sum(m);
+                } else {
+                    for (int r = kg; r < a.R; r += 2)
+                        for (int s = 0; s < a.S; ++s) rs += psum[abase_s[m] + r * a.PW + s];
+                    rs += __shfl_xor(rs, 32, 64);
+                }
+            }
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -1241,26 +1256,31 @@ __global__ __launch_bounds__(256 * KG)
 
 // Finishes the tail tiles.  A tile is 4 * MB units, one per (32-row block, channel group of the MFMA
 // layout); 256 threads take a unit, each then needs only NB * part_planes 16-byte pieces per part,
-// and the pieces of four parts are requested together.
+// and the pieces of four or eight parts are requested together.
 // A launch is bound by the counters as soon as it has more than a few hundred workgroups: their
 // adds to one address are served one per 13.7 ns (1600 workgroups with one unit each took 26 us,
 // 2048 took 33, 15 and 15 now).  So a workgroup takes several units, up to four side
 // by side, and leaves one add per counter: see launch_mfma.  Workgroup 0 also adds the
 // per-workgroup counts of the main kernel.
-template <int LIMBS, int WL, int NB, int MB>
-__global__ __launch_bounds__(1024) void conv_finish_kernel(const ConvArgs a, int main_grid, int wgs_per_tile)
+// SIDE: units side by side in a workgroup.  Alone (1, launches of few tiles) a unit has the registers to
+// request all parts together and the memory latency is paid once; four parts at a time cost such layers
+// 0.6 to 2 us more (2x20x20, 128 -> 16, 7x7, eight parts: 18.6 : 20.7).  Four units (4) fit with four parts.
+template <int LIMBS, int WL, int NB, int MB, int SIDE>
+__global__ __launch_bounds__(256 * SIDE) void conv_finish_kernel(const ConvArgs a, int main_grid, int spread_wgs)
 {
     constexpr int BN = 64 * NB;
     constexpr int NACC = LIMBS + WL - 1;
     constexpr int PP = part_planes(LIMBS, WL);
     constexpr int UNIT = 256;         // threads per unit
-    constexpr int BATCH = 4;          // parts requested at once (eight spill)
+    constexpr int THREADS = UNIT * SIDE;
+    constexpr int BATCH = SIDE == 1 ? kMaxParts : 4; // parts requested at once (with four units side by side eight spill)
     constexpr int UNITS = 4 * MB;     // units per tile
+    const int wgs_per_tile = SIDE == 1 ? UNITS : spread_wgs;
     __shared__ int outoff[BM];
     __shared__ int pooloff[BM];
     __shared__ __align__(16) int ctab[3 * BN];
-    __shared__ unsigned long long wave_counts[2][16]; // [zeros, clipped][wave]
-    const int tid = threadIdx.x, threads = blockDim.x, side = threads / UNIT, utid = tid & (UNIT - 1);
+    __shared__ unsigned long long wave_counts[2][THREADS / 64]; // [zeros, clipped][wave]
+    const int tid = threadIdx.x, utid = tid & (UNIT - 1);
     const int wave = utid >> 6; // within the unit: the main kernel's wave arrangement, BM / (32 * MB) waves along the pixels
     constexpr int WMC = BM / (32 * MB);
     const int tails = a.per_xcd - a.full_per_xcd;
@@ -1273,23 +1293,24 @@ __global__ __launch_bounds__(1024) void conv_finish_kernel(const ConvArgs a, int
         const int tile_r = mtile / a.tiles_c, tile_c = mtile % a.tiles_c;
         const int fr0 = tile_r * a.RH, x0 = tile_c * a.TW;
         const unsigned char *slots = a.partials + (size_t)tile_b * a.split * a.part_bytes;
-        for (int u = share * side + __builtin_amdgcn_readfirstlane(tid / UNIT); u < UNITS; u += wgs_per_tile * side) { // (the same trips for every thread)
+        for (int u = share * SIDE + __builtin_amdgcn_readfirstlane(tid / UNIT); u < UNITS; u += wgs_per_tile * SIDE) { // (the same trips for every thread)
             const int mb0 = u >> 2, g0 = u & 3;
             v4i piece[BATCH][NB][PP];
             auto request = [&](int o0) __attribute__((always_inline)) {
 #pragma unroll
-                for (int o = 0; o < BATCH; ++o)
-                    if (o0 + o < a.split) { // (uniform)
+                for (int o = 0; o < BATCH; ++o) {
+                    // alone: past the last part the last one again, so that no branch parts the requests
+                    if (SIDE > 1 && o0 + o >= a.split) continue; // (uniform)
+                    const v4i *theirs = (const v4i *)(slots + (size_t)min(o0 + o, a.split - 1) * a.part_bytes);
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb)
+                    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                            for (int q = 0; q < PP; ++q)
-                                piece[o][nb][q] = ((const v4i *)(slots + (size_t)(o0 + o) * a.part_bytes))[(((mb0 * NB + nb) * 4 + g0) * PP + q) * UNIT + utid];
-                    }
+                        for (int q = 0; q < PP; ++q) piece[o][nb][q] = theirs[(((mb0 * NB + nb) * 4 + g0) * PP + q) * UNIT + utid];
+                }
             };
             request(0);
-            if (u < side * wgs_per_tile) { // first trip: the tile's tables
-                for (int m = tid; m < BM; m += threads) {
+            if (u < SIDE * wgs_per_tile) { // first trip: the tile's tables
+                for (int m = tid; m < BM; m += THREADS) {
                     const int j = m / a.TW, t = m % a.TW;
                     const int fr = fr0 + j, xo = x0 + t;
                     const bool ok = j < a.RH && fr < a.FR && xo < a.Wo;
@@ -1297,7 +1318,7 @@ __global__ __launch_bounds__(1024) void conv_finish_kernel(const ConvArgs a, int
                     pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1))
                                      ? ((fr / a.Ho) * (a.Ho >> 1) + ((fr % a.Ho) >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
                 }
-                build_colterms<BN>(a, ntile, ctab, threads, LIMBS, WL);
+                build_colterms<BN>(a, ntile, ctab, THREADS, LIMBS, WL);
             }
             int sum[NB][PP][4];
 #pragma unroll
@@ -1335,7 +1356,7 @@ __global__ __launch_bounds__(1024) void conv_finish_kernel(const ConvArgs a, int
                         for (int q = 0; q < PP; ++q) acc[0][nb][q][e] = sum[nb][q][e];
                     }
                 }
-            if (u < side * wgs_per_tile) __syncthreads(); // (every thread: see the trip count)
+            if (u < SIDE * wgs_per_tile) __syncthreads(); // (every thread: see the trip count)
             const TileCounts counts = tile_epilogue<LIMBS, WL, NB, BN, 1, 1>(
                 a, acc, [](int) { return 0; }, outoff, pooloff, ctab, ntile, (wave % WMC) * (32 * MB), (wave / WMC) * (NB * 32), mb0, g0);
             if (a.zout) {
@@ -1357,7 +1378,7 @@ __global__ __launch_bounds__(1024) void conv_finish_kernel(const ConvArgs a, int
     if (!a.zero_partial) return;
     if (blockIdx.x == 0) {
         unsigned long long sum[2] = {0, 0};
-        for (int i = tid; i < main_grid; i += threads) {
+        for (int i = tid; i < main_grid; i += THREADS) {
             sum[0] += a.zero_partial[i];
             sum[1] += a.zero_partial[a.partial_stride + i];
         }
@@ -1376,7 +1397,7 @@ __global__ __launch_bounds__(1024) void conv_finish_kernel(const ConvArgs a, int
     __syncthreads();
     if (tid < 2) {
         unsigned long long total = 0;
-        for (int w = 0; w < threads / 64; ++w) total += wave_counts[tid][w];
+        for (int w = 0; w < THREADS / 64; ++w) total += wave_counts[tid][w];
         unsigned long long *dst = tid ? a.sat_count : a.zero_count;
         if (total && dst) atomicAdd(dst, total);
     }
@@ -1812,8 +1833,8 @@ static lp_status launch_mfma(const ConvArgs &a, const Plan &p, int grid, int tai
         // one after the other
         const bool spread = tails * 4 * MB <= kCUs;
         const int per_tile = spread ? 4 * MB : tails * MB <= kCUs ? MB : 1;
-        hipLaunchKernelGGL((conv_finish_kernel<LIMBS, WL, NB, MB>), dim3(tails * per_tile), dim3(spread ? 256 : 1024), 0, st, a,
-                           grid, per_tile);
+        if (spread) hipLaunchKernelGGL((conv_finish_kernel<LIMBS, WL, NB, MB, 1>), dim3(tails * per_tile), dim3(256), 0, st, a, grid, per_tile);
+        else hipLaunchKernelGGL((conv_finish_kernel<LIMBS, WL, NB, MB, 4>), dim3(tails * per_tile), dim3(1024), 0, st, a, grid, per_tile);
     }
     return launch_status();
 }

@@ -492,6 +492,10 @@ FINISH_FORMS = [
     (5, 28, 28, 512, 512, 3, 16, 8),
     (1, 12, 10, 256, 64, 3, 8, 8),         # one limb, 64 and 128 channels
     (64, 28, 28, 256, 256, 3, 8, 8),
+    (2, 20, 20, 128, 16, 7, 16, 16),       # eight parts; the row sums of other windows than 3x3
+    (20, 5, 5, 64, 40, 5, 16, 16),         # seven parts of 25 slabs
+    (3, 9, 11, 1024, 24, 1, 16, 16),
+    (20, 5, 5, 64, 32, 5, 8, 8),
 ]
 
 

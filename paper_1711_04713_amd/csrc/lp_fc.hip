@@ -237,10 +237,10 @@ struct FcArgs {
 };
 
 // the epilogue's LDS tables of a tile: tile row -> output row, the rows' code sums, channel constants
-template <int LIMBS>
+template <int LIMBS, int THREADS>
 __device__ __forceinline__ void fc_tile_tables(const FcArgs &f, int mt, int nt, int *outoff, int *rowsum, int *ctab)
 {
-    for (int m = threadIdx.x; m < FM; m += blockDim.x) {
+    for (int m = threadIdx.x; m < FM; m += THREADS) {
         const int row = mt * FM + m;
         outoff[m] = row < f.M ? row : -1;
         // the row's partial sums, all requested before any is added (kc is uniform)
@@ -254,7 +254,7 @@ __device__ __forceinline__ void fc_tile_tables(const FcArgs &f, int mt, int nt, 
         }
         rowsum[m] = t;
     }
-    build_colterms<FN>(f.c, nt, ctab, blockDim.x, LIMBS, LIMBS);
+    build_colterms<FN>(f.c, nt, ctab, THREADS, LIMBS, LIMBS);
 }
 
 // Sums in the 32-bit pieces the epilogue combines <-> one exact int64 per output.
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(kFcThreads) __attribute__((amdgpu_waves_per_eu(2, 2
         return;
     }
 
-    fc_tile_tables<LIMBS>(f, mt, nt, outoff, rowsum, ctab);
+    fc_tile_tables<LIMBS, kFcThreads>(f, mt, nt, outoff, rowsum, ctab);
     __syncthreads();
     const TileCounts counts = tile_epilogue<LIMBS, LIMBS, 2, FN, 1, 4>(
         f.c, acc, [&](int m) { return rowsum[m]; }, outoff, outoff, ctab, nt, wave * 32, 0, 0, 0);
@@ -452,19 +452,23 @@ __global__ __launch_bounds__(kFcThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 // the main kernel, so that a thread needs two 16-byte pieces (one with one limb) per part.  Counts go
 // straight to the caller's counters, whose adds are served one per 13.7 ns: with twice as many
 // workgroups of half the size the classifier at 256 rows took 171 us, now 166.
-constexpr int kFinishThreads = 2 * kFcThreads;
-template <int LIMBS>
-__global__ __launch_bounds__(kFinishThreads) void fc_finish_kernel(const FcArgs f)
+// CBS: column blocks per workgroup: 2 as said; 1 (a workgroup of half the size for each) for at most 12 tiles, where
+// the way through one workgroup counts and not their number.  us with 1 : 2, 16 bits (8): 4 tiles 19.8 : 21.2, 8 tiles
+// 20.7 : 21.9 (13.2 : 13.5), 12 tiles 23.1 : 23.6 (14.58 : 14.63), 16 tiles 25.4 : 25.2 (16.0 : 15.5), 32 tiles 32.1 : 29.9.
+template <int LIMBS, int CBS>
+__global__ __launch_bounds__(CBS * kFcThreads) void fc_finish_kernel(const FcArgs f)
 {
+    constexpr int THREADS = CBS * kFcThreads;
     constexpr int NACC = (LIMBS == 2) ? 3 : 1;
-    constexpr int WAVES = kFinishThreads / 64;
+    constexpr int WAVES = THREADS / 64;
     constexpr int PP = LIMBS == 2 ? 2 : 1;    // pieces per part and thread
     __shared__ int outoff[FM];
     __shared__ int rowsum[FM];
     __shared__ __align__(16) int ctab[3 * FN];
     __shared__ unsigned wave_counts[2][WAVES];
     const int tid = threadIdx.x, rtid = tid & (kFcThreads - 1), wave = rtid >> 6;
-    const int tile = blockIdx.x >> 2, cb = __builtin_amdgcn_readfirstlane(tid / kFcThreads), g = blockIdx.x & 3;
+    const int tile = blockIdx.x / (8 / CBS), g = blockIdx.x & 3;
+    const int cb = CBS == 2 ? __builtin_amdgcn_readfirstlane(tid / kFcThreads) : (blockIdx.x >> 2) & 1;
     const int mt = tile / f.n_tiles, nt = tile - mt * f.n_tiles;
     const v4i *slots = (const v4i *)(f.c.partials + (size_t)tile * f.ksplit * f.c.part_bytes);
     const size_t part_v4 = (size_t)f.c.part_bytes / 16;
@@ -476,7 +480,7 @@ __global__ __launch_bounds__(kFinishThreads) void fc_finish_kernel(const FcArgs 
 #pragma unroll
             for (int h = 0; h < PP; ++h) piece[o][h] = slots[o * part_v4 + ((cb * 4 + g) * PP + h) * kFcThreads + rtid];
         }
-    fc_tile_tables<LIMBS>(f, mt, nt, outoff, rowsum, ctab);
+    fc_tile_tables<LIMBS, THREADS>(f, mt, nt, outoff, rowsum, ctab);
     v16i acc[1][1][NACC];
 #pragma unroll
     for (int q = 0; q < NACC; ++q)
@@ -738,6 +742,13 @@ __global__ __launch_bounds__(64 * few_waves<RB>()) void fc_few_rows_kernel(const
     }
 }
 
+template <int LIMBS>
+static void launch_finish(const FcArgs &f, int tiles, hipStream_t hs)
+{
+    if (tiles <= 12) hipLaunchKernelGGL((fc_finish_kernel<LIMBS, 1>), dim3(tiles * 8), dim3(kFcThreads), 0, hs, f);
+    else hipLaunchKernelGGL((fc_finish_kernel<LIMBS, 2>), dim3(tiles * 4), dim3(2 * kFcThreads), 0, hs, f);
+}
+
 template <int LIMBS, int RB>
 static void launch_few_rows(const FcArgs &f, int grid, bool vec, hipStream_t hs)
 {
@@ -848,12 +859,12 @@ static lp_status fc_forward(int M, int K, int Nout, const void *x, lp_qfmt qx, c
         hipLaunchKernelGGL((fc_split_x_kernel<int16_t, 2>), sgrid, dim3(64 * kSplitWaves), 0, hs, (const int16_t *)x,
                            const_cast<unsigned char *>(f.xs), const_cast<int *>(f.xsum), M, K, p.KH, p.khc);
         hipLaunchKernelGGL(fc_mfma_kernel<2>, dim3(p.grid), dim3(kFcThreads), 0, hs, f);
-        if (p.ksplit > 1) hipLaunchKernelGGL(fc_finish_kernel<2>, dim3(p.tiles * 4), dim3(kFinishThreads), 0, hs, f);
+        if (p.ksplit > 1) launch_finish<2>(f, p.tiles, hs);
     } else {
         hipLaunchKernelGGL((fc_split_x_kernel<int8_t, 1>), sgrid, dim3(64 * kSplitWaves), 0, hs, (const int8_t *)x,
                            const_cast<unsigned char *>(f.xs), const_cast<int *>(f.xsum), M, K, p.KH, p.khc);
         hipLaunchKernelGGL(fc_mfma_kernel<1>, dim3(p.grid), dim3(kFcThreads), 0, hs, f);
-        if (p.ksplit > 1) hipLaunchKernelGGL(fc_finish_kernel<1>, dim3(p.tiles * 4), dim3(kFinishThreads), 0, hs, f);
+        if (p.ksplit > 1) launch_finish<1>(f, p.tiles, hs);
     }
     const lp_status ls = launch_status();
     if (ls != LP_OK || p.ksplit > 1 || !counting || direct) return ls;

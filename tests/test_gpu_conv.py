@@ -385,6 +385,21 @@ def test_fc_few_rows(oracle, M, K, Nout):
             assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
 
 
+@pytest.mark.parametrize("M,K,Nout", [(100, 1030, 40), (300, 520, 384), (100, 1030, 768), (100, 1030, 832)])
+def test_fc_parts_of_few_and_of_many_tiles(oracle, M, K, Nout):
+    """Both forms of the kernel that adds up the parts of a tile: a workgroup per column block up to 12
+    tiles, one for both from 13 on (the last row), ragged rows and columns."""
+    rng = np.random.default_rng(M + Nout)
+    for n, qx, qw, qy in ((16, QX, QW, (16, 14, 2)), (8, (8, 3, 5), (8, 1, 7), (8, 8, 0))):
+        x, w = _codes(rng, (M, K), n=n, zero_frac=0.5), _codes(rng, (Nout, K), n=n)
+        assert lp.lp_fc_workspace_bytes(M, K, Nout, qx, qw) > 2 * 256 * 64 * (8 if n == 16 else 4)   # room for parts
+        want = oracle.fc(x, w, threads=8)
+        got = fc(x, qx, w, qw, qy=qy)
+        assert np.array_equal(got["acc"], want)
+        y, z, sat = oracle.act(want, qx[2] + qw[2], *qy, True, oracle.ROUND_AWAY, with_sat=True)
+        assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
+
+
 def test_zero_count_needs_workspace_and_accumulates(oracle):
     import torch
     from gpu_helpers import to_dev

@@ -41,7 +41,7 @@ constexpr int FRAG = 1024;     // bytes of one MFMA operand fragment: 64 lanes x
 constexpr int kFcThreads = 512;
 constexpr int FMAXP = 8;       // most parts the reduction is cut into
 constexpr int FKC = 32;        // most K chunks the input split works in (one partial row sum each)
-constexpr int kFewBlocks = 2;  // most 32-row blocks of the few-rows kernel
+constexpr int kFewBlocks = 2;  // most 32-row blocks the few-rows kernel holds (see few_rows_pay)
 
 struct FcPlan {
     int limbs;
@@ -60,6 +60,25 @@ struct FcPlan {
 // The inner-product kernel takes 16-bit inputs with 8- or 16-bit weights (two limbs) and 8-bit
 // inputs with 8-bit weights (one limb).
 static bool fc_kernel_takes(lp_qfmt qx, lp_qfmt qw) { return qx.n > 8 || qw.n <= 8; }
+
+// Whether the few-rows kernel is the faster one for up to 64 rows.  It re-reads every input row in every
+// workgroup (32 columns), in 16-byte pieces of 32 rows at a time: per code and row 0.058 ns (one limb 0.038) beside
+// 1.1 ns (0.53) per code of the reduction, in as many rounds as the columns need CUs, and the weights' way out of
+// HBM.  The tiled kernels always compute 256 rows, but cut the reduction into parts: 9.4 ns (5.6) per code of one,
+// and 48 ns (45) per part for the sums' way through memory.  Estimates in us, fitted to 501 problems of 1..64 rows,
+// 32..30000 codes and 8..16384 columns; of these the choice costs at most 15 % and none more than 8 % against
+// the tiled kernels.  Few rows : tiled, 16 bits:
+//   25088 -> 4096: 1 row 50 : 78, 17 rows 73 : 85, 32 rows 101 : 89, 64 rows 149 : 88
+//   25088 ->  512: 1 row 43 : 42, 8 rows 51 : 42, 64 rows 145 : 44
+//    4096 -> 4096: 1 row 15 : 34, 64 rows 30 : 35;    4096 -> 1000: 64 rows 24.5 : 25.4
+static bool few_rows_pay(const FcPlan &p, int M, int K, int Nout)
+{
+    const double rounds = (((Nout + 31) / 32) + kCUs - 1) / kCUs, tile_rounds = (p.tiles + kCUs - 1) / kCUs;
+    const double part = 32.0 * p.khp * tile_rounds, parts = p.ksplit > 1 ? (double)p.tiles * p.ksplit : 0.0;
+    if (p.limbs == 2)
+        return 4.6 + K * (1.14e-3 + 0.058e-3 * M * rounds + 0.20e-6 * Nout) < 11.9 + 0.0094 * part + 0.048 * parts;
+    return 3.0 + K * (0.53e-3 + 0.038e-3 * M * rounds + 0.174e-6 * Nout) < 6.5 + 0.0056 * part + 0.045 * parts;
+}
 
 static lp_status make_fc_plan(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw, FcPlan *out)
 {
@@ -98,7 +117,7 @@ static lp_status make_fc_plan(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw, Fc
     p.ws_xsum = round_up((size_t)p.kc * p.mblocks * 32 * sizeof(int), 256);
     p.ws_parts = p.ksplit > 1 ? (size_t)p.tiles * p.ksplit * p.part_bytes : 0;
     p.ws_total = p.ws_counts + p.ws_xs + p.ws_xsum + p.ws_parts;
-    if (p.mblocks <= kFewBlocks) {
+    if (p.mblocks <= kFewBlocks && few_rows_pay(p, M, K, Nout)) {
         p.few = p.mblocks;
         p.grid = (Nout + 31) / 32;
         p.ws_total = 256; // nothing to split, nothing to merge

@@ -385,6 +385,22 @@ def test_fc_few_rows(oracle, M, K, Nout):
             assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
 
 
+@pytest.mark.parametrize("M,K,Nout,few", [
+    (40, 801, 520, True), (64, 1001, 4100, True), (64, 1002, 2080, True),   # two blocks, more than one turn of the waves
+    (64, 2500, 33, False), (20, 9001, 40, False), (1, 25087, 70, True),     # either side of the line between the kernels
+])
+def test_fc_kernels_of_up_to_64_rows(oracle, M, K, Nout, few):
+    rng = np.random.default_rng(M + K)
+    for n, qx, qw, qy in ((16, QX, QW, (16, 14, 2)), (8, (8, 3, 5), (8, 1, 7), (8, 8, 0))):
+        x, w = _codes(rng, (M, K), n=n, zero_frac=0.5), _codes(rng, (Nout, K), n=n)
+        assert (lp.lp_fc_workspace_bytes(M, K, Nout, qx, qw) == 256) == few
+        want = oracle.fc(x, w, threads=8)
+        got = fc(x, qx, w, qw, qy=qy)
+        assert np.array_equal(got["acc"], want)
+        y, z, sat = oracle.act(want, qx[2] + qw[2], *qy, True, oracle.ROUND_AWAY, with_sat=True)
+        assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
+
+
 @pytest.mark.parametrize("M,K,Nout", [(100, 1030, 40), (300, 520, 384), (100, 1030, 768), (100, 1030, 832)])
 def test_fc_parts_of_few_and_of_many_tiles(oracle, M, K, Nout):
     """Both forms of the kernel that adds up the parts of a tile: a workgroup per column block up to 12

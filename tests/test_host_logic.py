@@ -270,3 +270,13 @@ def test_static_entry_takes_every_8bit_weight_layer(shape, R):
     status = lp.load().lp_conv_fwd_static(ctypes.byref(d), None, fmt(Q16), None, fmt(W8), None, lp.QFmt(), None, None,
                                           fmt(Q16), 1, lp.LP_ROUND_NEAREST_AWAY, None, None, None)
     assert status in (1, 4)
+
+
+@pytest.mark.parametrize("q,w", [(Q16, W16), (Q16, W8), (Q8, W8)])
+def test_inner_product_of_few_rows_takes_the_faster_kernel(q, w):
+    """Long reductions of more than a handful of rows run tiled (the workspace then holds the split input),
+    short and single-row ones on the few-rows kernel (256 bytes)."""
+    few = lambda M, K, N: lp.lp_fc_workspace_bytes(M, K, N, q, w) == 256
+    assert few(1, 25088, 4096) and few(1, 4096, 4096) and few(64, 4096, 4096) and few(32, 4096, 1000) and few(64, 512, 10)
+    assert not any(few(M, 25088, 512) for M in (17, 32, 33, 64))
+    assert not any(few(M, 25088, 4096) for M in (32, 33, 64)) and not few(64, 8192, 1000) and not few(65, 64, 64)

@@ -49,9 +49,16 @@ __device__ __forceinline__ void add_block_counts(unsigned zeros, unsigned sats, 
 constexpr int kCountBlocks = 256;
 constexpr int kCountThreads = 1024;
 
-static int count_grid(size_t groups)
+// Small tensors are counted by blocks of four waves, one trip each: sixteen waves concentrate the work on a
+// few CUs and meet later.  us with 4 : 16 waves: lp_quantize to 16 bits of 30 k elements 2.6 : 3.0 (stochastic
+// 2.5 : 3.8), 300 k 2.8 : 3.3; to 8 bits (every block has zeros to add) 100 k 3.0 : 3.25, 250 k 3.9 : 3.4; lp_act
+// 30 k 5.1 : 6.7, 250 k 4.9 : 6.4, 500 k 6.1 : 4.9.  The line lies where the adds of the more blocks begin to show.
+constexpr int kSmallBlocks = 96;
+static bool count_small(size_t groups) { return groups <= (size_t)kSmallBlocks * kThreads; }
+
+static int count_grid(size_t groups, int threads)
 {
-    return (int)std::min<size_t>(std::max<size_t>((groups + kCountThreads - 1) / kCountThreads, 1), kCountBlocks);
+    return (int)std::min<size_t>(std::max<size_t>((groups + threads - 1) / threads, 1), kCountBlocks);
 }
 
 // ------------------------------------------------------------------ Philox4x32-10
@@ -111,15 +118,14 @@ __device__ __forceinline__ int quantize_one(float x, float scale, float lo, floa
     return (int)r;
 }
 
-template <typename OutT, int MODE, bool COUNT>
-__global__ __launch_bounds__(COUNT ? kCountThreads : kThreads) void quantize_kernel(const float *__restrict__ x,
+template <typename OutT, int MODE, bool COUNT, int THREADS>
+__global__ __launch_bounds__(THREADS) void quantize_kernel(const float *__restrict__ x,
                                                            OutT *__restrict__ y, size_t count,
                                                            float scale, float lo, float hi,
                                                            uint64_t seed,
                                                            unsigned long long *zero_count,
                                                            unsigned long long *sat_count)
 {
-    constexpr int THREADS = COUNT ? kCountThreads : kThreads;
     const size_t groups = count / 8, stride = (size_t)gridDim.x * THREADS;
     unsigned zeros = 0, sats = 0; // wave-uniform running totals
     auto take = [&](size_t g, const v4f &a, const v4f &b) __attribute__((always_inline)) {
@@ -203,12 +209,15 @@ template <typename OutT, int MODE>
 static void launch_quantize(const float *x, void *y, size_t count, float scale, float lo, float hi,
                             uint64_t seed, uint64_t *zc, uint64_t *sc, hipStream_t st)
 {
-    if (zc || sc)
-        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true>), dim3(count_grid(count / 8)), dim3(kCountThreads), 0, st, x,
-                           (OutT *)y, count, scale, lo, hi, seed, (unsigned long long *)zc,
+    if ((zc || sc) && count_small(count / 8))
+        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true, kThreads>), dim3(count_grid(count / 8, kThreads)), dim3(kThreads), 0,
+                           st, x, (OutT *)y, count, scale, lo, hi, seed, (unsigned long long *)zc, (unsigned long long *)sc);
+    else if (zc || sc)
+        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true, kCountThreads>), dim3(count_grid(count / 8, kCountThreads)),
+                           dim3(kCountThreads), 0, st, x, (OutT *)y, count, scale, lo, hi, seed, (unsigned long long *)zc,
                            (unsigned long long *)sc);
     else
-        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, false>), dim3(grid_for(count / 8)), dim3(kThreads), 0, st, x,
+        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, false, kThreads>), dim3(grid_for(count / 8)), dim3(kThreads), 0, st, x,
                            (OutT *)y, count, scale, lo, hi, seed, nullptr, nullptr);
 }
 
@@ -468,14 +477,13 @@ __device__ __forceinline__ int act_one_stochastic(int64_t v, const ActParams &p,
     return (int)r;
 }
 
-template <typename OutT, bool STOCH, bool COUNT>
-__global__ __launch_bounds__(COUNT ? kCountThreads : kThreads) void act_kernel(const int64_t *__restrict__ acc,
+template <typename OutT, bool STOCH, bool COUNT, int THREADS>
+__global__ __launch_bounds__(THREADS) void act_kernel(const int64_t *__restrict__ acc,
                                                       OutT *__restrict__ y, size_t count,
                                                       ActParams p, uint64_t seed,
                                                       unsigned long long *zero_count,
                                                       unsigned long long *sat_count)
 {
-    constexpr int THREADS = COUNT ? kCountThreads : kThreads;
     unsigned sats = 0; // a wave's totals are scalars
     // w: the element's draw (stochastic scheme only)
     auto one = [&](int64_t v, uint32_t w, bool &sat) {
@@ -700,14 +708,17 @@ static lp_status act_launch(const int64_t *acc_dev, size_t count, int f_acc, lp_
     const ActParams p = make_act_params(f_acc, qy, relu, r);
     // one trip of the kernel's loop per block, up to the cap
     const bool counting = zero_count_dev || sat_count_dev;
-    const int grid = counting ? count_grid(count / 8) : grid_for(count / 8);
 #define LP_A(T, STOCH)                                                                                        \
-    if (counting)                                                                                             \
-        hipLaunchKernelGGL((act_kernel<T, STOCH, true>), dim3(grid), dim3(kCountThreads), 0, st, acc_dev,     \
-                           (T *)y_codes_dev, count, p, seed, (unsigned long long *)zero_count_dev,            \
+    if (counting && count_small(count / 8))                                                                   \
+        hipLaunchKernelGGL((act_kernel<T, STOCH, true, kThreads>), dim3(count_grid(count / 8, kThreads)), dim3(kThreads), 0, \
+                           st, acc_dev, (T *)y_codes_dev, count, p, seed, (unsigned long long *)zero_count_dev, \
                            (unsigned long long *)sat_count_dev);                                              \
+    else if (counting)                                                                                        \
+        hipLaunchKernelGGL((act_kernel<T, STOCH, true, kCountThreads>), dim3(count_grid(count / 8, kCountThreads)), \
+                           dim3(kCountThreads), 0, st, acc_dev, (T *)y_codes_dev, count, p, seed,             \
+                           (unsigned long long *)zero_count_dev, (unsigned long long *)sat_count_dev);        \
     else                                                                                                      \
-        hipLaunchKernelGGL((act_kernel<T, STOCH, false>), dim3(grid), dim3(kThreads), 0, st, acc_dev,         \
+        hipLaunchKernelGGL((act_kernel<T, STOCH, false, kThreads>), dim3(grid_for(count / 8)), dim3(kThreads), 0, st, acc_dev, \
                            (T *)y_codes_dev, count, p, seed, nullptr, nullptr)
     if (r == LP_ROUND_STOCHASTIC) {
         if (qy.n > 8) {

@@ -51,7 +51,7 @@ def test_quantize_config_tensors(oracle):
         assert np.array_equal(got, want) and (gz, gs) == (wz, ws)
 
 
-@pytest.mark.parametrize("count", [8 * 1024 * 256 - 8, 8 * 1024 * 256 + 3, 2 * 8 * 1024 * 256 + 8 * 37 + 5, 3 * 8 * 1024 * 256 + 8])
+@pytest.mark.parametrize("count", [8 * 256 * 96 - 1, 8 * 256 * 96 + 7, 8 * 256 * 96 + 8, 8 * 1024 * 256 - 8, 8 * 1024 * 256 + 3, 2 * 8 * 1024 * 256 + 8 * 37 + 5, 3 * 8 * 1024 * 256 + 8])
 def test_counts_of_many_trips(count):
     """Sizes at which the counting kernels' blocks take one, two or three trips and the last trip ends
     inside a wave: codes equal those of the kernels without counters, zeros those among the codes,

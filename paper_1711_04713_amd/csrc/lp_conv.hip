@@ -693,7 +693,7 @@ __global__ __launch_bounds__(256 * KG)
         // two limbs: the stride is hidden from the compiler, which else mixes this one-trip loop into the staging
         // around it (8x28x28, 192 -> 128, 16-bit under 8-bit weights: 13.7 us, 14.05 with the constant)
         int threads = THREADS;
-        if constexpr (LIMBS == 2) asm volatile("" : "+s"(threads));
+        if constexpr (LIMBS == 2 && KG == 1) asm volatile("" : "+s"(threads));
         build_colterms<BN>(a, ntile, ctab, threads, LIMBS, WL, deadmask);
     };
     const int lane = tid & 63, wave = KG > 1 ? (tid >> 6) & 3 : tid >> 6; // the wave within its group
@@ -1275,6 +1275,8 @@ __global__ __launch_bounds__(256 * SIDE) void conv_finish_kernel(const ConvArgs 
     constexpr int THREADS = UNIT * SIDE;
     constexpr int BATCH = SIDE == 1 ? kMaxParts : 4; // parts requested at once (with four units side by side eight spill)
     constexpr int UNITS = 4 * MB;     // units per tile
+    int threads = THREADS; // hidden from the compiler with four units: the tables then stay behind the requests
+    if constexpr (SIDE > 1) asm volatile("" : "+s"(threads));
     const int wgs_per_tile = SIDE == 1 ? UNITS : spread_wgs;
     __shared__ int outoff[BM];
     __shared__ int pooloff[BM];
@@ -1301,7 +1303,7 @@ __global__ __launch_bounds__(256 * SIDE) void conv_finish_kernel(const ConvArgs 
                 for (int o = 0; o < BATCH; ++o) {
                     // alone: past the last part the last one again, so that no branch parts the requests
                     if (SIDE > 1 && o0 + o >= a.split) continue; // (uniform)
-                    const v4i *theirs = (const v4i *)(slots + (size_t)min(o0 + o, a.split - 1) * a.part_bytes);
+                    const v4i *theirs = (const v4i *)(slots + (size_t)(SIDE > 1 ? o0 + o : min(o, a.split - 1)) * a.part_bytes);
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -1310,7 +1312,7 @@ __global__ __launch_bounds__(256 * SIDE) void conv_finish_kernel(const ConvArgs 
             };
             request(0);
             if (u < SIDE * wgs_per_tile) { // first trip: the tile's tables
-                for (int m = tid; m < BM; m += THREADS) {
+                for (int m = tid; m < BM; m += threads) {
                     const int j = m / a.TW, t = m % a.TW;
                     const int fr = fr0 + j, xo = x0 + t;
                     const bool ok = j < a.RH && fr < a.FR && xo < a.Wo;
@@ -1318,7 +1320,7 @@ __global__ __launch_bounds__(256 * SIDE) void conv_finish_kernel(const ConvArgs 
                     pooloff[m] = (a.pool && ok && !(j & 1) && !(t & 1))
                                      ? ((fr / a.Ho) * (a.Ho >> 1) + ((fr % a.Ho) >> 1)) * (a.Wo >> 1) + (xo >> 1) : -1;
                 }
-                build_colterms<BN>(a, ntile, ctab, THREADS, LIMBS, WL);
+                build_colterms<BN>(a, ntile, ctab, threads, LIMBS, WL);
             }
             int sum[NB][PP][4];
 #pragma unroll

@@ -219,21 +219,33 @@ static int choose_split(int tail_tiles, int slots, int nslabs, size_t part_acc, 
 
 // Wide form: three wave groups per workgroup, one workgroup per CU, for grids of at most one tile per CU
 // and parts of whole chunks.  It wins where the narrow form either leaves one wave per SIMD or cuts its
-// tiles and pays for the finishing kernel.  Narrow (conv + finishing) against wide, us:
-//   72 slabs: 256 tiles 38 + 15 : 47; 64 tiles 20 + 9.7 : 19 + 8.6; 56 tiles 18 + 8.9 : 16 + 8.6;
-//             200 tiles of one-limb weights 26 + 13 : 32
-//   50 slabs (5x5): 184 tiles 30 : 28
-//   36 slabs: 112 tiles 23.9 : 22.8, 56 tiles 14 + 8.2 : 21.2, 256 tiles 28.6 : 30.4
+// tiles and pays for the finishing kernel.  Narrow against wide, us (16-bit codes; "cut": into parts, with finishing):
+//   36 slabs: 56 tiles cut 25.6 : 20.0, 112 tiles 22.6 : 21.1, 160 tiles 23.3 : 21.8, 256 tiles 25.1 : 25.1
+//   45 slabs: 112 tiles cut 28.8 : 23.8, 256 tiles 28.8 : 28.8;    50 slabs (5x5): 168 tiles cut 33.8 : 25.9
+//   72 slabs: 56 tiles cut 25.7 : 24.3 (cut), 160 tiles cut 39.4 : 35.6, 256 tiles cut 50.0 : 42.1
+//   8-bit weights, 72 slabs: 32 tiles cut 23.1 : 23.9 (cut), 256 tiles cut 37.2 : 25.6;  36 slabs: 256 tiles 18.5 : 17.9
 //   18 slabs and fewer: 168 tiles 16.8 : 17.8, 200 tiles 17.4 : 17.6 -- the exchange and the stagings every wave
 //             waits for eat the gain, so the line is at 36 (VGG16 at batch 1: 274 us with it at 48, 263 at 36)
 //   two tiles per CU (400 tiles, 72 slabs): two narrow workgroups side by side are the better one (VGG16 at
 //             batch 32: 1.75 ms, 1.79 with its last three layers wide)
-//   at most two tiles on a die: narrow parts can be finer than a chunk; equal at 8 chunks (16 tiles: 18 : 18)
+//   at most two tiles on a die: narrow parts can be finer than a chunk: 16 tiles 72 slabs 17.7 : 18.6 (cut)
+// A cut narrow form spreads over every CU, where whole wide tiles leave CUs idle: 136 tiles 90 slabs cut 40.5 : 45.1,
+// 144 slabs 53.6 : 70.3; 88 tiles 63 slabs 29.2 : 33.4.  With two-limb weights, whose wide form gains least, it
+// therefore has to win an estimate, fitted to 86 such layers (us; 768 threads stage 96 pixels a step).
+static bool wide_pays(const Plan &p, int parts)
+{
+    const int nslabs = p.taps * p.nchunks, chunks = (p.nchunks + parts - 1) / parts;
+    const double staging = 0.64 * ((p.PRA * p.PW + 95) / 96);
+    const double wide = 6.2 + chunks * (0.6 * ((p.taps + 2) / 3) + staging) + (parts > 1 ? 4.0 + 0.037 * kXCDs * p.per_xcd * parts : 0.0);
+    const double narrow = 16.3 + p.per_xcd * (0.0107 * nslabs + 0.09 * p.split);
+    return wide < 1.04 * narrow; // (the estimates miss by about that)
+}
+
 static void choose_wide(Plan &p)
 {
     constexpr int die = kCUs / kXCDs;
     if (p.taps < 3 || p.taps * p.nchunks < 36 || p.per_xcd > die) return; // (a group takes whole taps)
-    if (p.split > 1 && p.per_xcd <= 2 && p.nchunks < 8) return;
+    if (p.split > 1 && p.per_xcd <= 2 && (p.nchunks < 8 || p.wl == 2)) return;
     const size_t lds = mfma_lds_bytes(p.limbs, p.PRA, p.PW, p.PITCH, p.BN, 0, 3);
     if (lds > kLdsBudgets[1]) return;
     // Parts are whole chunks, and no more of them than the narrow form would cut.  In us: 0.7 a tap of the longest share,
@@ -249,6 +261,7 @@ static void choose_wide(Plan &p)
             best = s;
         }
     }
+    if (p.wl == 2 && p.split > 1 && !wide_pays(p, best)) return;
     p.kg = 3;
     p.lds_bytes = lds;
     p.full_per_xcd = best > 1 ? 0 : p.per_xcd;

@@ -280,3 +280,17 @@ def test_inner_product_of_few_rows_takes_the_faster_kernel(q, w):
     assert few(1, 25088, 4096) and few(1, 4096, 4096) and few(64, 4096, 4096) and few(32, 4096, 1000) and few(64, 512, 10)
     assert not any(few(M, 25088, 512) for M in (17, 32, 33, 64))
     assert not any(few(M, 25088, 4096) for M in (32, 33, 64)) and not few(64, 8192, 1000) and not few(65, 64, 64)
+
+
+@pytest.mark.parametrize("shape,R,wide", [
+    ((4, 28, 28, 1024, 320), 3, False), ((7, 14, 14, 448, 512), 3, False), ((1, 28, 28, 128, 256), 7, False),
+    ((1, 14, 14, 512, 512), 3, False), ((13, 14, 14, 1024, 512), 3, False),
+    ((5, 28, 28, 512, 512), 3, True), ((2, 28, 28, 512, 512), 3, True), ((1, 28, 28, 512, 512), 3, True),
+    ((2, 28, 28, 256, 256), 3, True), ((3, 28, 28, 128, 512), 5, True), ((4, 28, 28, 512, 512), 3, True),
+])
+def test_wide_form_is_taken_where_it_wins(shape, R, wide):
+    """Layers of at most a tile per CU with 16-bit weights, measured in both forms: one wave group per workgroup
+    and cut tiles, or three wave groups (seen by the LDS their exchange takes)."""
+    N, H, W, Cin, Cout = shape
+    info = lp.lp_conv_plan_info(lp.ConvDesc(N, H, W, Cin, Cout, R, R, 1, R // 2), Q16, W16)
+    assert (info["lds_bytes"] > 65536) == wide and (wide or info["split"] > 1)

@@ -131,8 +131,8 @@ def test_conv_random_shapes_8bit(oracle, N, Cin, H, W, Cout, R, S, pad):
     (3, 72, 14, 14, 128, 1, 8, 0),       # shift 15, images straddled by tiles
     (1, 904, 7, 7, 72, 1, 12, 2),        # K = 8136: just inside the 32-bit epilogue; shift 17
     (1, 920, 6, 7, 64, 1, 12, 3),        # K = 8280: just past it; shift 16
-    (70, 64, 32, 32, 128, 1, 12, 6),     # a grid that takes 128-channel tiles
-    (40, 128, 28, 28, 256, 1, 12, 6),    # ... and shares the last round's reductions
+    (70, 64, 32, 32, 128, 1, 12, 6),     # more whole tiles than fit at once
+    (37, 128, 28, 24, 256, 1, 12, 6),    # whole tiles, and a last round of 16 cut into eight parts each
 ])
 def test_conv_16bit_activations_8bit_weights(oracle, N, Cin, H, W, Cout, pad, fx, fy):
     """One-limb weights under two-limb activations: every code of both widths with the extremes forced,
@@ -144,7 +144,11 @@ def test_conv_16bit_activations_8bit_weights(oracle, N, Cin, H, W, Cout, pad, fx
     qx, qw, qy = (16, 16 - fx, fx), (8, 1, 7), (16, 16 - fy, fy)
     acc = oracle.conv(x, w, pad=pad, threads=8)
     got = conv(x, qx, w, qw, qy=qy, r=lp.LP_ROUND_NEAREST_EVEN, pad=pad)
-    assert got["info"]["path"] == 1 and np.array_equal(got["acc"], acc)
+    info = got["info"]
+    assert info["path"] == 1 and info["bn"] == 64 and np.array_equal(got["acc"], acc)
+    if N > 3:
+        cut = 8 * (info["items_per_die"] - info["whole_items_per_die"])
+        assert (info["split"], cut, info["workgroups"]) == {70: (1, 0, 1120), 37: (8, 16, 896)}[N]
     y, z, sat = oracle.act(acc, fx + 7, *qy, True, oracle.ROUND_EVEN, with_sat=True)
     assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (z, sat)
     bias = _codes(rng, (Cout,), n=8)
@@ -514,19 +518,24 @@ def test_fused_maxpool_matches_conv_act_pool(oracle, shape):
 
 
 FINISH_FORMS = [
-    # (N, H, W, Cin, Cout, kernel, activation bits, weight bits)
-    (1, 12, 10, 256, 64, 3, 16, 16),       # few tiles: a workgroup per unit
-    (1, 12, 10, 256, 72, 3, 16, 8),        # one weight limb, ragged channels
-    (1, 28, 28, 512, 512, 3, 16, 16),      # four units side by side, seven parts: more than one batch of requests
-    (1, 28, 28, 512, 512, 3, 16, 8),
-    (5, 28, 28, 512, 512, 3, 16, 16),      # every tile of 256 in one workgroup, two trips
-    (5, 28, 28, 512, 512, 3, 16, 8),
-    (1, 12, 10, 256, 64, 3, 8, 8),         # one limb, 64 and 128 channels
-    (64, 28, 28, 256, 256, 3, 8, 8),
-    (2, 20, 20, 128, 16, 7, 16, 16),       # eight parts; the row sums of other windows than 3x3
-    (20, 5, 5, 64, 40, 5, 16, 16),         # seven parts of 25 slabs
-    (3, 9, 11, 1024, 24, 1, 16, 16),
-    (20, 5, 5, 64, 32, 5, 8, 8),
+    # (N, H, W, Cin, Cout, kernel, activation bits, weight bits; parts per cut tile, cut tiles, channels per tile)
+    (1, 12, 10, 256, 64, 3, 16, 16, 8, 8, 64),       # few tiles: a workgroup per unit, all parts requested at once
+    (1, 12, 10, 256, 72, 3, 16, 8, 8, 8, 64),        # one weight limb, ragged channels
+    (1, 12, 10, 256, 64, 3, 8, 8, 8, 8, 64),         # one limb
+    (2, 20, 20, 128, 16, 7, 16, 16, 8, 8, 64),       # the row sums of other windows than 3x3
+    (20, 5, 5, 64, 40, 5, 16, 16, 7, 16, 64),
+    (3, 9, 11, 1024, 24, 1, 16, 16, 8, 8, 64),
+    (20, 5, 5, 64, 32, 5, 8, 8, 8, 8, 64),
+    (55, 28, 28, 128, 384, 3, 8, 8, 8, 8, 128),      # 128-channel tiles, behind whole ones
+    (1, 28, 28, 512, 512, 3, 16, 16, 4, 56, 64),     # four units side by side; parts of three wave groups
+    (1, 28, 28, 512, 512, 3, 16, 8, 4, 56, 64),
+    (7, 14, 14, 512, 512, 3, 16, 16, 5, 88, 64),     # five and seven parts: a second batch of requests
+    (4, 28, 28, 192, 128, 3, 8, 8, 7, 56, 64),
+    (46, 28, 28, 320, 512, 3, 8, 8, 4, 128, 128),    # the most tiles with two workgroups each
+    (20, 28, 28, 512, 512, 3, 16, 16, 3, 240, 64),   # every tile in one workgroup, two trips
+    (22, 14, 14, 512, 512, 3, 16, 8, 2, 280, 64),
+    (32, 14, 14, 512, 512, 3, 8, 8, 2, 400, 64),
+    (72, 28, 28, 512, 384, 3, 8, 8, 3, 304, 128),
 ]
 
 
@@ -537,10 +546,12 @@ def test_merged_parts_equal_whole_tiles(form):
     equal counts of those codes."""
     import torch
 
-    N, H, W, Cin, Cout, k, nx, nw = form
+    N, H, W, Cin, Cout, k, nx, nw, parts, cut, bn = form
     qx, qw, qy = (nx, 4, nx - 4), (nw, 1, nw - 1), (nx, 6, nx - 6)
     d = lp.ConvDesc(N, H, W, Cin, Cout, k, k, 1, k // 2)
     info = lp.lp_conv_plan_info(d, qx, qw)
+    assert (info["path"], info["split"], info["bn"]) == (1, parts, bn)
+    assert 8 * (info["items_per_die"] - info["whole_items_per_die"]) == cut
     gen = torch.Generator(device="cuda")
     gen.manual_seed(71)
     dt = torch.int16 if nx > 8 else torch.int8
@@ -564,7 +575,6 @@ def test_merged_parts_equal_whole_tiles(form):
     s = qx[2] + qw[2] - qy[2]
     sats = int((((acc0.clamp(min=0) + (1 << (s - 1))) >> s) > top - 1).sum().item())
     assert count.tolist() == [1000 + zeros, 1000 + sats] * 2 and sats > 0
-    assert info["path"] == 1
 
 
 @pytest.mark.parametrize("shape,R,qx,qw,split", [

@@ -322,7 +322,7 @@ def main():
         info = L["info"]
         kname = {lp.LP_KERNEL_DIRECT: "conv_direct_kernel", lp.LP_KERNEL_FLAT: "conv_flat_kernel",
                  lp.LP_KERNEL_ROWS: "conv_rows_kernel",
-                 lp.LP_KERNEL_PATCH: "conv_mfma_kernel<%d,%d,patch>" % (info["limbs"], info["bn"] // 64)}[info["kernel"]]
+                 lp.LP_KERNEL_PATCH: "conv_mfma_kernel<%d limbs,%d channels>" % (info["limbs"], info["bn"])}[info["kernel"]]
         kern_ops[kname] = kern_ops.get(kname, 0) + 8 * macs          # 4 int8 limb MACs = 8 int8 ops per 16-bit MAC
         kern_ms[kname] = kern_ms.get(kname, 0.0) + ms
         layers.append({

@@ -13,7 +13,11 @@
  *
  * General rules of this ABI
  *   - Pointers named *_dev are device (HBM) pointers, *_host are host pointers.
- *     The caller owns every buffer; the library allocates no device memory.
+ *     The caller owns every buffer; the library allocates no device memory.  Its
+ *     code object holds two device arrays per GPU until the process ends: the
+ *     workspace of lp_conv_fwd_static, and 32 small slots of lp_range /
+ *     lp_range_acc (9 KB).  The first range call that launches also allocates
+ *     8 KB of pinned host memory, kept until the process ends.
  *   - Code storage: int8_t when n <= 8, int16_t when 9 <= n <= 16, sign-extended.
  *   - Activations are NHWC, weights [Cout][R][S][Cin], FC inputs [M][K], FC
  *     weights [Nout][K]: the contraction index is always contiguous.
@@ -77,7 +81,9 @@ const char *lp_status_string(lp_status s);
  * none); loss_threshold 0 places the point from max|v|.  NaN is never lost,
  * +-Inf always.  lost_host (nullable) receives n+1 counts, lost_host[m] for
  * m = 1..n (entry 0 unused).  workspace_dev: LP_RANGE_WORKSPACE_WORDS uint64
- * of scratch (required; nothing is to be read from it afterwards).
+ * of scratch: required, but neither read nor written at present (the histogram
+ * lives in a slot of the library's own).  At most 32 range calls of a process
+ * are in flight at once; further threads wait for one to return.
  * Synchronises the stream.  count == 0 yields m = 1.
  */
 lp_status lp_range(const float *x_dev, size_t count, int n, double loss_threshold,
@@ -280,7 +286,9 @@ lp_status lp_conv_fwd_static(const lp_conv_desc *d, const void *x_codes_dev, lp_
  *   acc[b,o] = sum_k X[b,k] * W[o,k] (+ bias), x [M][K], w packed from [Nout][K].
  * Packing / workspace: the lp_fc_* functions below.  Other arguments as lp_conv_fwd, except
  * that the workspace is always required (LP_EWORKSPACE without it): the call first splits the
- * input rows into int8 limb planes there, then runs a split-K GEMM whose parts meet there.
+ * input rows into int8 limb planes there, then runs a split-K GEMM whose parts meet there.  Calls of
+ * up to 64 rows run in one launch that needs neither where that is faster (lp_fc_workspace_bytes
+ * then asks for a token 256 bytes).
  * Its contents need no initialisation and carry nothing from call to call; calls that share
  * one workspace must not overlap in time.
  */

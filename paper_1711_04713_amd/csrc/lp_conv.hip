@@ -709,7 +709,7 @@ __global__ __launch_bounds__(256 * KG)
         if constexpr (LIMBS == 2 && KG == 1) asm volatile("" : "+s"(threads));
         build_colterms<BN>(a, ntile, ctab, threads, LIMBS, WL, deadmask);
     };
-    const int lane = tid & 63, wave = KG > 1 ? (tid >> 6) & 3 : tid >> 6; // the wave within its group
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(KG > 1 ? (tid >> 6) & 3 : tid >> 6); // the wave within its group, a scalar: so are its channels
     const int group = KG > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
     const int wm = wave % WMC, wn = wave / WMC;
     const int l32 = lane & 31, kg = lane >> 5;
@@ -1245,6 +1245,7 @@ __global__ __launch_bounds__(256 * KG)
     // one pair of counts per workgroup; on large grids they go to per-workgroup slots, not to the
     // counters: thousands of same-address atomics would serialise
     if (a.zero_partial || a.zout || a.direct_counts) {
+        counts = wave_total(counts);
         if (lane == 0) { // tab[] was last read while staging
             tab[tid >> 6] = (int)counts.zeros;
             tab[THREADS / 64 + (tid >> 6)] = (int)counts.sats;
@@ -1296,7 +1297,7 @@ __global__ __launch_bounds__(256 * SIDE) void conv_finish_kernel(const ConvArgs 
     __shared__ __align__(16) int ctab[3 * BN];
     __shared__ unsigned long long wave_counts[2][THREADS / 64]; // [zeros, clipped][wave]
     const int tid = threadIdx.x, utid = tid & (UNIT - 1);
-    const int wave = utid >> 6; // within the unit: the main kernel's wave arrangement, BM / (32 * MB) waves along the pixels
+    const int wave = __builtin_amdgcn_readfirstlane(utid >> 6); // within the unit: the main kernel's wave arrangement, BM / (32 * MB) waves along the pixels
     constexpr int WMC = BM / (32 * MB);
     const int tails = a.per_xcd - a.full_per_xcd;
     const int tile_b = blockIdx.x / wgs_per_tile, share = blockIdx.x % wgs_per_tile;
@@ -1372,8 +1373,8 @@ __global__ __launch_bounds__(256 * SIDE) void conv_finish_kernel(const ConvArgs 
                     }
                 }
             if (u < SIDE * wgs_per_tile) __syncthreads(); // (every thread: see the trip count)
-            const TileCounts counts = tile_epilogue<LIMBS, WL, NB, BN, 1, 1>(
-                a, acc, [](int) { return 0; }, outoff, pooloff, ctab, ntile, (wave % WMC) * (32 * MB), (wave / WMC) * (NB * 32), mb0, g0);
+            const TileCounts counts = wave_total(tile_epilogue<LIMBS, WL, NB, BN, 1, 1>(
+                a, acc, [](int) { return 0; }, outoff, pooloff, ctab, ntile, (wave % WMC) * (32 * MB), (wave / WMC) * (NB * 32), mb0, g0));
             if (a.zout) {
                 // codes of the unit that exist; a zero count below it = a nonzero code
                 const int m = (wave % WMC) * (32 * MB) + mb0 * 32 + (tid & 31);
@@ -1466,7 +1467,7 @@ __global__ __launch_bounds__(256)
     __shared__ int outoff[BM], pooloff[BM], abase[BM];
     __shared__ __align__(16) int ctab[3 * BN];
     __shared__ unsigned wave_counts[2][THREADS / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, kg = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int wi = xcd * a.per_xcd + slot;
     if (slot >= a.per_xcd || wi >= a.total_work) {
@@ -1606,6 +1607,7 @@ __global__ __launch_bounds__(256)
         counts.sats += c.sats;
     }
     if (a.zero_partial || a.zout || a.direct_counts) {
+        counts = wave_total(counts);
         if (lane == 0) {
             wave_counts[0][wave] = counts.zeros;
             wave_counts[1][wave] = counts.sats;
@@ -1654,7 +1656,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     unsigned *wave_counts = (unsigned *)(ctab + 3 * BN); // [zeros, clipped][wave]
     unsigned char *Asm = (unsigned char *)(wave_counts + 2 * (THREADS / 64)); // high plane, then low plane
     const int APL = a.APLANE;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, kg = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int wi = xcd * a.per_xcd + slot;
     if (slot >= a.per_xcd || wi >= a.total_work) {
@@ -1798,6 +1800,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
         counts.sats += c.sats;
     }
     if (a.zero_partial || a.zout || a.direct_counts) {
+        counts = wave_total(counts);
         if (lane == 0) {
             wave_counts[wave] = counts.zeros;
             wave_counts[THREADS / 64 + wave] = counts.sats;

@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kFcThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     // (and with it the input fragments they read) and differ in their column tile.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int wi = xcd * f.per_xcd + slot;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (slot >= f.per_xcd || wi >= f.total) {
         if (f.c.zero_partial && tid == 0) f.c.zero_partial[blockIdx.x] = f.c.zero_partial[f.c.partial_stride + blockIdx.x] = 0;
         return;
@@ -450,8 +450,8 @@ __global__ __launch_bounds__(kFcThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 
     fc_tile_tables<LIMBS, kFcThreads>(f, mt, nt, outoff, rowsum, ctab);
     __syncthreads();
-    const TileCounts counts = tile_epilogue<LIMBS, LIMBS, 2, FN, 1, 4>(
-        f.c, acc, [&](int m) { return rowsum[m]; }, outoff, outoff, ctab, nt, wave * 32, 0, 0, 0);
+    const TileCounts counts = wave_total(tile_epilogue<LIMBS, LIMBS, 2, FN, 1, 4>(
+        f.c, acc, [&](int m) { return rowsum[m]; }, outoff, outoff, ctab, nt, wave * 32, 0, 0, 0));
     if (f.c.zero_partial || f.c.direct_counts) {
         if (lane == 0) {
             wave_counts[0][wave] = counts.zeros;
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(CBS * kFcThreads) void fc_finish_kernel(const FcArg
     __shared__ int rowsum[FM];
     __shared__ __align__(16) int ctab[3 * FN];
     __shared__ unsigned wave_counts[2][WAVES];
-    const int tid = threadIdx.x, rtid = tid & (kFcThreads - 1), wave = rtid >> 6;
+    const int tid = threadIdx.x, rtid = tid & (kFcThreads - 1), wave = __builtin_amdgcn_readfirstlane(rtid >> 6);
     const int tile = blockIdx.x / (8 / CBS), g = blockIdx.x & 3;
     const int cb = CBS == 2 ? __builtin_amdgcn_readfirstlane(tid / kFcThreads) : (blockIdx.x >> 2) & 1;
     const int mt = tile / f.n_tiles, nt = tile - mt * f.n_tiles;
@@ -535,8 +535,8 @@ __global__ __launch_bounds__(CBS * kFcThreads) void fc_finish_kernel(const FcArg
             }
     }
     __syncthreads();
-    const TileCounts counts = tile_epilogue<LIMBS, LIMBS, 1, FN, 1, 1>(
-        f.c, acc, [&](int m) { return rowsum[m]; }, outoff, outoff, ctab, nt, wave * 32, cb * 32, 0, g);
+    const TileCounts counts = wave_total(tile_epilogue<LIMBS, LIMBS, 1, FN, 1, 1>(
+        f.c, acc, [&](int m) { return rowsum[m]; }, outoff, outoff, ctab, nt, wave * 32, cb * 32, 0, g));
     if (!f.c.zero_count && !f.c.sat_count) return;
     if ((tid & 63) == 0) {
         wave_counts[0][tid >> 6] = counts.zeros;

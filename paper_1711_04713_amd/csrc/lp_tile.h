@@ -184,8 +184,8 @@ __device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int
 // of the tile): four consecutive channels per group of four registers, which leave as one 8-byte
 // (4-byte) store.
 // row_sum(m): sum of the codes under tile row m's window (two-limb weights only); outoff and ctab (see
-// build_colterms) are LDS tables, complete and visible.  Returns the wave's counts of zero codes
-// and (when a.count_sat) of values clipped at an end of the code range, the same in every lane.
+// build_colterms) are LDS tables, complete and visible.  Returns the lane's counts of zero codes
+// and (when a.count_sat) of values clipped at an end of the code range; see wave_total.
 // The accumulators passed in cover MBL of the wave's MB row blocks, starting at block mb0, and GL
 // of the four channel groups, starting at group g0 (register 4*gl + e = channel 8*(g0+gl) +
 // 4*(lane/32) + e): the main kernel passes everything (MBL = MB, GL = 4, mb0 = g0 = 0), the
@@ -193,6 +193,21 @@ __device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int
 struct TileCounts {
     unsigned zeros, sats;
 };
+
+// The wave's totals of its lanes' counts (the same in every lane), for lanes of at most 64 of each: both
+// halves of a word go through one tree of DPP adds.
+__device__ __forceinline__ TileCounts wave_total(TileCounts c)
+{
+    int v = (int)(c.zeros | (c.sats << 16));
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false); // row_shr:1, 2, 4, 8: sums of the 16-lane rows in their last lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false); // row_bcast:15, 31
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    const unsigned t = (unsigned)__builtin_amdgcn_readlane(v, 63);
+    return {t & 0xffffu, t >> 16};
+}
 
 // LIMBS / WL: 8-bit limbs of the activations and of the weights; LIMBS + WL - 1 accumulator planes, the
 // most significant first (2, 2: HH, HL + LH, LL; 2, 1: H, L; 1, 1: one).
@@ -204,7 +219,6 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
     const int lane = threadIdx.x & 63;
     const int l32 = lane & 31, kg = lane >> 5;
     unsigned nz = 0, ns = 0; // zero codes written / values clipped by this lane (at most 16 * MB * NB <= 64 each)
-    unsigned wz = 0, wsat = 0; // counted for the whole wave (scalars: ballots and popcounts)
     int oo[MBL], po[MBL], rs[MBL];
 #pragma unroll
     for (int mb = 0; mb < MBL; ++mb) {
@@ -237,30 +251,59 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
             const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc(
                 (unsigned char *)a.y + (size_t)first * a.Cout * ESZ, 0, (int)(left < 0x7fffffffu ? left : 0x7fffffffu), 0x00020000);
             unsigned rel[MBL]; // byte offset of the lane's output pixel from the tile's first one
-            unsigned long long rowmask[MBL]; // lanes whose output pixel exists (zero count)
+            unsigned nnz[MBL]; // the lane's codes that are not zero (16-bit codes: two counts of 16 bits)
 #pragma unroll
             for (int mb = 0; mb < MBL; ++mb) {
                 const int o = MODE == 1 ? po[mb] : oo[mb];
                 rel[mb] = o >= 0 ? (unsigned)((o - first) * a.Cout * ESZ) : NOWHERE;
-                rowmask[mb] = __builtin_amdgcn_ballot_w64(oo[mb] >= 0);
+                nnz[mb] = 0;
             }
+            // the output pixel of a row of a block, read where it is needed (kept, it would cost the loop below a register)
+            auto pixel_at = [&](int mb, int row) __attribute__((always_inline)) {
+                int m = row0 + (mb0 + mb) * 32 + row;
+                asm volatile("" : "+v"(m));
+                return outoff[m];
+            };
+            auto exists = [&](int mb) __attribute__((always_inline)) { return MODE == 1 ? pixel_at(mb, l32) >= 0 : rel[mb] != NOWHERE; };
+            // 8-bit codes of whole blocks of 32 channels are stored together.  A lane holds four neighbouring channels of each
+            // group of eight, of one pixel: stored as they are, an instruction touches 32 lines with 8 bytes each, and the
+            // memory system takes a step per line and instruction.  Swapping halves and rows of lanes between registers
+            // first gives every lane 16 neighbouring bytes, four lanes to a pixel: 64x56x56, 128 -> 256 3x3 69.7 -> 61.7 us,
+            // 256 -> 256 116.4 -> 106.9.  (16-bit codes, twice the bytes per line as they are, gain at most 2 % on large
+            // layers, but small ones then wait for their stores at the end: 18x18, 64 -> 64 batch 32 10.2 -> 10.45 us.)
+            constexpr bool BLOCKS = MODE == 0 && GL == 4 && !Y16;
+            unsigned word[MBL][NB][GL];
+            // Counting.  A wave that is not multiplying issues one instruction at a time beside the others' MFMAs,
+            // on whichever unit, so what a count costs is its instructions, scalar ones included.  Zeros: codes are
+            // not negative, so min(code, 1) says whether one is nonzero, two packed codes at a time (8-bit codes:
+            // the top bits of code + 127, four at a time): one instruction a code where a compare, a mask, a popcount and
+            // an add took four.  Clipped values: only where the largest rounded value of a group lies above the
+            // range (half an instruction a code) are they counted one by one.
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int gl = 0; gl < GL; ++gl) {
                     // a group of eight channels that lies past Cout altogether has nothing to write
                     // or count (uniform: a scalar branch)
-                    if (ntile * BN + col0w + nb * 32 + 8 * (g0 + gl) >= a.Cout) continue;
+                    if (ntile * BN + col0w + nb * 32 + 8 * (g0 + gl) >= a.Cout) {
+                        if constexpr (BLOCKS)
+#pragma unroll
+                            for (int mb = 0; mb < MBL; ++mb) word[mb][nb][gl] = 0;
+                        continue;
+                    }
                     const int cl = col0w + nb * 32 + 8 * (g0 + gl) + 4 * kg; // channel within the tile
                     const int col0 = ntile * BN + cl;
                     const bool col_ok = col0 < a.Cout;
-                    const unsigned long long colmask = __builtin_amdgcn_ballot_w64(col_ok); // lanes whose channels exist
+                    // what a code that exists may add to the lane's count
+                    const unsigned one = !col_ok ? 0u : Y16 ? 0x00010001u : 0x80808080u;
                     const v4i cA = *(const v4i *)(ctab + cl);
                     const v4i cB = *(const v4i *)(ctab + BN + cl);
                     const v4i cC = *(const v4i *)(ctab + 2 * BN + cl);
+                    int rounded[MBL][4], peak = 0; // the rounded values before clipping, the largest of them
 #pragma unroll
                     for (int mb = 0; mb < MBL; ++mb) {
-                        int q[4], raw[4]; // codes, and the rounded values before clipping
+                        int q[4];
+                        int (&raw)[4] = rounded[mb];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const int v = 4 * gl + e;
@@ -304,6 +347,10 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                             q[e] = clamp_code(raw[e], cmax);
                         }
                         const bool counted = oo[mb] >= 0 && col_ok; // the lane's codes exist in the output tensor
+                        if constexpr (SAT && MODE != 2) {
+                            peak = max(max(peak, raw[0]), raw[1]);
+                            peak = max(max(peak, raw[2]), raw[3]);
+                        }
                         if constexpr (MODE == 2) { // ragged channel tail: code by code
                             if (counted) {
                                 unsigned char *dst = (unsigned char *)a.y + ((size_t)oo[mb] * a.Cout + col0) * ESZ;
@@ -319,16 +366,9 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                             // codes are in [0, cmax]: packing needs no masks
                             unsigned w0 = (unsigned)q[0] | ((unsigned)q[1] << 16);
                             unsigned w1 = (unsigned)q[2] | ((unsigned)q[3] << 16);
-                            // zeros: one compare per code into a lane mask, masks counted by the
-                            // scalar unit (codes of lanes whose pixel or channels do not exist are
-                            // masked out)
-                            const unsigned long long live = rowmask[mb] & colmask;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) wz += __builtin_popcountll(__builtin_amdgcn_ballot_w64(q[e] == 0) & live);
-                            if constexpr (SAT) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) wsat += __builtin_popcountll(__builtin_amdgcn_ballot_w64(raw[e] > cmax) & live);
-                            }
+                            const v2us ones = __builtin_bit_cast(v2us, one);
+                            nnz[mb] = __builtin_bit_cast(unsigned, (v2us)(__builtin_bit_cast(v2us, nnz[mb]) + __builtin_elementwise_min(__builtin_bit_cast(v2us, w0), ones)));
+                            nnz[mb] = __builtin_bit_cast(unsigned, (v2us)(__builtin_bit_cast(v2us, nnz[mb]) + __builtin_elementwise_min(__builtin_bit_cast(v2us, w1), ones)));
                             if constexpr (MODE == 1) {
                                 // 2x2 maximum across lanes: the horizontal neighbour is the next lane,
                                 // the vertical one sits TW lanes further in the same 32-row block.
@@ -347,18 +387,81 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                             __builtin_amdgcn_raw_buffer_store_b64((v2u){w0, w1}, yrsrc, (int)at, 0, 0);
                         } else {
                             const unsigned w0 = (unsigned)q[0] | ((unsigned)q[1] << 8) | ((unsigned)q[2] << 16) | ((unsigned)q[3] << 24);
-                            const unsigned long long live = rowmask[mb] & colmask;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) wz += __builtin_popcountll(__builtin_amdgcn_ballot_w64(q[e] == 0) & live);
-                            if constexpr (SAT) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) wsat += __builtin_popcountll(__builtin_amdgcn_ballot_w64(raw[e] > cmax) & live);
+                            nnz[mb] += __builtin_popcount((w0 + 0x7f7f7f7fu) & one);
+                            if constexpr (BLOCKS) {
+                                word[mb][nb][gl] = w0;
+                            } else {
+                                const unsigned at = col_ok ? rel[mb] + (unsigned)col0 : NOWHERE;
+                                __builtin_amdgcn_raw_buffer_store_b32(w0, yrsrc, (int)at, 0, 0);
                             }
-                            const unsigned at = col_ok ? rel[mb] + (unsigned)col0 : NOWHERE;
-                            __builtin_amdgcn_raw_buffer_store_b32(w0, yrsrc, (int)at, 0, 0);
+                        }
+                    }
+                    if (SAT && MODE != 2 && __builtin_amdgcn_ballot_w64(peak > cmax)) {
+#pragma unroll
+                        for (int mb = 0; mb < MBL; ++mb) {
+                            const int most = col_ok && exists(mb) ? cmax : 0x7fffffff;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) ns += rounded[mb][e] > most;
                         }
                     }
                 }
+            if constexpr (BLOCKS) {
+                const auto swap32 = [](unsigned &x, unsigned &y) __attribute__((always_inline)) { // upper half of x with lower half of y
+                    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+                    x = r[0];
+                    y = r[1];
+                };
+                const auto swap16 = [](unsigned &x, unsigned &y) __attribute__((always_inline)) { // odd rows of x with even rows of y
+                    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+                    x = r[0];
+                    y = r[1];
+                };
+                const int colw = ntile * BN + col0w;
+                const auto store = [&](const v4u &piece, int o, int ch) __attribute__((always_inline)) {
+                    const unsigned at = o >= 0 && ch < a.Cout ? (unsigned)((o - first) * a.Cout + ch) : NOWHERE;
+                    __builtin_amdgcn_raw_buffer_store_b128(piece, yrsrc, (int)at, 0, 0);
+                };
+                const int l16 = lane & 15, row = lane >> 4;
+#pragma unroll
+                for (int mb = 0; mb < MBL; ++mb) {
+                    unsigned(&w)[NB][GL] = word[mb];
+                    if ((a.Cout & 15) != 0) { // pieces of 16 bytes would not start on their boundaries: four codes at a time
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                            for (int gl = 0; gl < GL; ++gl) {
+                                const int ch = colw + nb * 32 + 8 * gl + 4 * kg;
+                                __builtin_amdgcn_raw_buffer_store_b32(w[nb][gl], yrsrc, (int)(ch < a.Cout ? rel[mb] + (unsigned)ch : NOWHERE), 0, 0);
+                            }
+                        continue;
+                    }
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) swap32(w[nb][p], w[nb][p + 2]); // lower lanes: groups 0 and 1, upper lanes: 2 and 3
+                    if constexpr (NB == 2) {
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) swap16(w[0][p], w[1][p]); // rows: channels 0, 32, 16, 48 of sixteen pixels
+                        const int ch = colw + 32 * (row & 1) + 16 * (row >> 1);
+                        store((v4u){w[0][0], w[0][2], w[0][1], w[0][3]}, pixel_at(mb, l16), ch);
+                        store((v4u){w[1][0], w[1][2], w[1][1], w[1][3]}, pixel_at(mb, 16 + l16), ch);
+                    } else {
+                        const int ch = colw + 16 * kg;
+                        __builtin_amdgcn_raw_buffer_store_b128((v4u){w[0][0], w[0][2], w[0][1], w[0][3]}, yrsrc,
+                                                               (int)(ch < a.Cout ? rel[mb] + (unsigned)ch : NOWHERE), 0, 0);
+                    }
+                }
+            }
+            if constexpr (MODE != 2) {
+                // groups of four channels that the lane has: 8 channels apart, over all blocks or one per block
+                constexpr int STEP = GL == 4 ? 8 : 32;
+                static_assert(GL == 4 || GL == 1, "groups are evenly spaced");
+                const int left = a.Cout - (ntile * BN + col0w + 8 * g0 + 4 * kg);
+                const unsigned codes = 4u * (unsigned)min(max((left + STEP - 1) / STEP, 0), NB * GL);
+#pragma unroll
+                for (int mb = 0; mb < MBL; ++mb)
+                    nz += exists(mb) ? codes - (Y16 ? (nnz[mb] & 0xffffu) + (nnz[mb] >> 16) : nnz[mb]) : 0u;
+            }
         };
         using std::integral_constant;
         auto by_sat = [&](auto s16c, auto y16c, auto modec) __attribute__((always_inline)) {
@@ -425,15 +528,7 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                 }
             }
     }
-    // wave total of the per-lane counts, bit plane by bit plane: ballot + popcount
-    TileCounts t = {wz, wsat};
-#pragma unroll
-    for (int b = 0; b < 7; ++b) t.zeros += wave_count((nz >> b) & 1) << b;
-    if (a.count_sat) {
-#pragma unroll
-        for (int b = 0; b < 7; ++b) t.sats += wave_count((ns >> b) & 1) << b;
-    }
-    return t;
+    return {nz, ns};
 }
 
 

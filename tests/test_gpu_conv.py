@@ -594,3 +594,29 @@ def test_three_wave_groups_per_workgroup(oracle, shape, R, qx, qw, split):
     rng = np.random.default_rng(N + Cin + R)
     x, w = _codes(rng, (N, Cin, H, W), n=qx[0], zero_frac=0.5), _codes(rng, (Cout, Cin, R, R), n=qw[0])
     _check(oracle, x, w, qx, qw, (16, 12, 4), pad=R // 2, expect_path=1)
+
+
+@pytest.mark.parametrize("shape,k", [
+    ((2, 9, 11, 64, 12), 3), ((2, 9, 11, 64, 20), 3), ((1, 13, 13, 32, 48), 3), ((3, 8, 8, 64, 100), 3),   # 64-wide channel tiles
+    ((2, 9, 11, 16, 64), 5), ((1, 17, 19, 128, 200), 1),
+    ((70, 32, 32, 16, 128), 1), ((70, 32, 32, 16, 120), 1), ((70, 31, 33, 16, 112), 1),                    # 128-wide ones
+])
+@pytest.mark.parametrize("qx,qw,n", [((8, 4, 4), (8, 1, 7), 8), ((16, 4, 12), (16, 1, 15), 16), ((16, 4, 12), (8, 1, 7), 16), ((16, 4, 12), (16, 1, 15), 8)])
+def test_codes_and_counts_of_the_short_epilogue(oracle, shape, k, qx, qw, n):
+    """Codes alone (the 32-bit epilogue) with output formats that clip nothing, a few values and most of them; channel
+    counts on both sides of what whole 16-byte pieces take."""
+    N, H, W, Cin, Cout = shape
+    rng = np.random.default_rng(N * 100 + Cout + k + n)
+    x = np.maximum(_codes(rng, (N, Cin, H, W), qx[0], full_range=False), 0)
+    w = _codes(rng, (Cout, Cin, k, k), qw[0], full_range=False)
+    f_acc = qx[2] + qw[2]
+    acc = oracle.conv(x, w, f_acc=f_acc, pad=k // 2, threads=8)
+    top = int(acc.max()).bit_length() - f_acc + 1          # integer bits (with sign) that hold every value
+    for m in (top, top - 2, top - 5):
+        m = min(max(m, 1), n)
+        qy = (n, m, n - m)
+        if not 1 <= f_acc - qy[2] <= 31:
+            continue
+        got = conv(x, qx, w, qw, qy=qy, pad=k // 2, want_acc=False)
+        y, zeros, sats = oracle.act(acc, f_acc, *qy, True, oracle.ROUND_AWAY, with_sat=True)
+        assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (zeros, sats)

@@ -166,7 +166,8 @@ lp_status lp_conv_pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, co
  * N*Ho stacked output rows x tile_cols columns, times bn output channels), the staged
  * input patch (patch_rows x patch_cols pixels; a pixel takes patch_pixel bytes per limb -- patch kernel: 64 of
  * codes and the rest padding that spreads consecutive pixels over the LDS banks; rows are
- * patch_pitch bytes apart), tile counts and LDS bytes per workgroup; the launch: workgroups in the grid, and split = parts into which each tile of the
+ * patch_pitch bytes apart), tile counts and LDS bytes per workgroup; the launch: workgroups in the grid (LP_KERNEL_FLAT: at
+ * most; calls that want 16-bit codes alone run several tiles per workgroup), and split = parts into which each tile of the
  * last, partly filled round of workgroup slots is cut along the reduction (1 = none; used
  * only when a workspace is passed).  Work item wi = pixel tile * tiles_n + channel tile (pixel
  * tiles row-major over stacked output rows x columns); die j of the chip's eight owns the items

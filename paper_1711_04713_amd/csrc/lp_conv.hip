@@ -1628,6 +1628,254 @@ __global__ __launch_bounds__(256)
     }
 }
 
+// The same layers where only 16-bit codes are wanted (the short epilogue, a shift of 9..20 bits, one channel
+// tile, channels by fours, no zero flags): what is left is counted in vector instructions, so
+//   - a workgroup runs several tiles: weights, window offsets and channel constants are set up once, the
+//     next tile's patch is on its way from memory while this one's codes are made, and there is one barrier a tile;
+//   - the accumulators start at the channel constants (with K <= 64 no limb sum passes 2^21, so nothing needs
+//     clamping on the way), and floor(v / 256) takes four instructions a code;
+//   - rounded values are clipped and packed two at a time;
+//   - with the pool the tile's pixels are dealt to lanes window by window: the maxima are two quad permutations,
+//     and the four lanes of a window store a group of channels each.
+// conv1_1 of VGG16 at batch 32 (12544 tiles) 85 -> 78 us, Giga1Net's 1x1 first layer 53 -> 34, with its pool 50 -> 36.
+constexpr int kFlatSlots = 4; // workgroups per CU by registers
+template <int NCB, int KS, bool POOL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS == 4 ? 3 : 4, NCB * KS == 4 ? 3 : 4))) void conv_flat_codes_kernel(
+    const ConvArgs a)
+{
+    constexpr int THREADS = 256, BN = 64;
+    __shared__ __align__(16) short raw[2][kFlatRawBytes / 2]; // raw patches: this tile's and the next one's
+    __shared__ v4i wlds[KS * 2 * NCB][64];      // weight operands: [(K half, limb, column block)][lane]
+    __shared__ __align__(16) int koff[64];      // window position k -> byte offset behind the window's first code
+    __shared__ __align__(16) unsigned ones[32]; // pair of window positions -> 1 for each that exists, so that its dot product with the codes sums them
+    __shared__ __align__(16) int ctab[3 * BN];
+    __shared__ unsigned wave_counts[2][THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
+    // the die's tiles, evenly over its workgroups
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
+    const int end = min(a.per_xcd, a.total_work - xcd * a.per_xcd);
+    int wi = xcd * a.per_xcd + (int)((long long)a.per_xcd * slot / slots);
+    const int wi_end = xcd * a.per_xcd + min(end, (int)((long long)a.per_xcd * (slot + 1) / slots));
+    unsigned nz = 0, ns = 0;
+    if (wi < wi_end) {
+        const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<void *>(a.x), 0, (int)((unsigned)(a.N * a.H * a.W) * (unsigned)a.Cin * 2u), 0x00020000);
+        const int nraw = a.NPIXA * a.Cin, rowlen = a.PW * a.Cin, wlen = a.W * a.Cin;
+        // code i of the patch of tile t
+        auto fetch = [&](int t, int i) __attribute__((always_inline)) {
+            int tile_r, tile_c, img0, yo0, pr, e, n, iy;
+            udivmod(t, a.tiles_c, a.mg_tiles_c, tile_r, tile_c);
+            udivmod(tile_r * a.RH, a.Ho, a.mg_Ho, img0, yo0);
+            udivmod(i, rowlen, a.mg_rowlen, pr, e);
+            udivmod(img0 * a.Hp + yo0 + pr, a.Hp, a.mg_Hp, n, iy);
+            iy -= a.pad;
+            const int c = (tile_c * a.TW - a.pad) * a.Cin + e; // position in the image row, in codes
+            const bool in = i < nraw && n < a.N && iy >= 0 && iy < a.H && c >= 0 && c < wlen;
+            return (short)__builtin_amdgcn_raw_buffer_load_b16(xrsrc, in ? (int)((unsigned)((n * a.H + iy) * wlen + c) * 2u) : -1, 0, 0);
+        };
+        constexpr int RU = 3; // codes per thread under way during a tile; those past them (wide windows) come at its end
+        short v[RU];
+        auto request = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < RU; ++u) v[u] = fetch(t, tid + u * THREADS);
+        };
+        auto park = [&](int t, short *dst) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < RU; ++u)
+                if (tid + u * THREADS < nraw) dst[tid + u * THREADS] = v[u];
+            for (int i = tid + RU * THREADS; i < nraw; i += THREADS) dst[i] = fetch(t, i);
+        };
+        // weight operands: a lane's 16 bytes of (K half, limb, column block)
+        const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<unsigned char *>(a.wp), 0, 2 * a.CoutP * CK, 0x00020000);
+        for (int piece = wave; piece < KS * 2 * NCB; piece += THREADS / 64) { // (K half * 2 + limb) * NCB + column block
+            const int cb = piece % NCB, hl = piece / NCB;
+            const auto r = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, ((hl >> 1) * a.CoutP + cb * 32 + l32) * 32 + kg * 16 + (hl & 1) * a.CoutP * CK, 0, 0);
+            wlds[piece][lane] = (v4i){(int)r[0], (int)r[1], (int)r[2], (int)r[3]};
+        }
+        request(wi);
+        const int SC = a.S * a.Cin;
+        for (int k = tid; k < 64; k += THREADS) {
+            int r, rem;
+            udivmod(k, SC, a.mg_SC, r, rem);
+            koff[k] = k < a.Kflat ? 2 * (r * rowlen + rem) : 0;
+            if (k < 32) ones[k] = a.Kflat - 2 * k >= 2 ? 0x00010001u : a.Kflat - 2 * k == 1 ? 1u : 0u;
+        }
+        const int s = a.act.s;
+        for (int c = tid; c < BN; c += THREADS) {
+            const int64_t t = c < a.Cout ? a.corr[c] + bias_term(a, c) : 0;
+            const int64_t top = t >> 16;
+            // (beyond +-2^21 the code is at an end of its range whatever the limb sums are, for every shift up to 20)
+            ctab[c] = (int)(top > (1 << 21) ? (1 << 21) : top < -(1 << 21) ? -(1 << 21) : top);
+            ctab[BN + c] = (int)((t >> 8) & 255) + (1 << (s - 9));
+            ctab[2 * BN + c] = (int)(t & 255);
+        }
+        // the lane's pixel of a tile; with the pool, the four pixels of a window are four neighbouring lanes
+        const int m = wave * 32 + l32;
+        int j, t;
+        if constexpr (POOL) {
+            const int half = a.TW >> 1;
+            j = 2 * ((m >> 2) / half) + ((m >> 1) & 1);
+            t = 2 * ((m >> 2) % half) + (m & 1);
+        } else {
+            udivmod(m, a.TW, a.mg_TW, j, t);
+        }
+        const int cmax = a.act.hi;
+        const v2s top2 = {(short)cmax, (short)cmax};
+        // groups of four channels the lane has: 8 channels apart
+        const unsigned codes = 4u * (unsigned)min(max((a.Cout - 4 * kg + 7) / 8, 0), NCB * 4);
+        park(wi, raw[0]);
+        __syncthreads();
+        for (int buf = 0; wi < wi_end; ++wi, buf ^= 1) {
+            if (wi + 1 < wi_end) request(wi + 1);
+            int tile_r, tile_c, img0, yo0, img, yo;
+            udivmod(wi, a.tiles_c, a.mg_tiles_c, tile_r, tile_c);
+            const int fr0 = tile_r * a.RH, x0 = tile_c * a.TW;
+            udivmod(fr0, a.Ho, a.mg_Ho, img0, yo0);
+            const int fr = fr0 + j, xo = x0 + t;
+            udivmod(fr, a.Ho, a.mg_Ho, img, yo);
+            const bool ok = j < a.RH && fr < a.FR && xo < a.Wo;
+            const unsigned char *rawb = (const unsigned char *)raw[buf] + (ok ? ((img - img0) * a.Hp + yo - yo0) * rowlen + t * a.Cin : 0) * 2;
+            // the lane's 16 window codes of each K half, two per register, then split into limb bytes
+            int sum = 0;
+            v4i ah[KS], al[KS];
+#pragma unroll
+            for (int h = 0; h < KS; ++h) {
+                const int *ko = koff + h * 32 + kg * 16;
+                const v4i o0 = *(const v4i *)ko, o1 = *(const v4i *)(ko + 4), o2 = *(const v4i *)(ko + 8), o3 = *(const v4i *)(ko + 12);
+                const int o[16] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w, o2.x, o2.y, o2.z, o2.w, o3.x, o3.y, o3.z, o3.w};
+                const v4i n0 = *(const v4i *)(ones + h * 16 + kg * 8), n1 = *(const v4i *)(ones + h * 16 + kg * 8 + 4);
+                const int one[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
+                unsigned pr[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    pr[q] = 0;
+                    if (h * 32 + 2 * q < a.Kflat) { // (uniform; a position past K reads some code and meets zero weights)
+                        const v2s two = {*(const short *)(rawb + o[2 * q]), *(const short *)(rawb + o[2 * q + 1])};
+                        pr[q] = __builtin_bit_cast(unsigned, two);
+                        sum = __builtin_amdgcn_sdot2(two, __builtin_bit_cast(v2s, one[q]), sum, false);
+                    }
+                }
+                unsigned hi[4], lo[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    hi[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x07050301u);
+                    lo[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x06040200u) ^ 0x80808080u;
+                }
+                ah[h] = v4i{(int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+                al[h] = v4i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3]};
+            }
+            const int rs = sum + __shfl_xor(sum, 32, 64); // a row's two lanes hold different window positions
+            const int rs2 = rs >> 1, odd = (rs & 1) << 7;
+            // outputs: 32-bit offsets from the tile's first pixel
+            const int first = POOL ? (img0 * (a.Ho >> 1) + (yo0 >> 1)) * (a.Wo >> 1) + (x0 >> 1) : fr0 * a.Wo + x0;
+            const int pixels = POOL ? a.N * (a.Ho >> 1) * (a.Wo >> 1) : a.N * a.Ho * a.Wo;
+            const size_t left = (size_t)(pixels - first) * a.Cout * 2;
+            const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (unsigned char *)a.y + (size_t)first * a.Cout * 2, 0, (int)(left < 0x7fffffffu ? left : 0x7fffffffu), 0x00020000);
+            constexpr unsigned NOWHERE = 0x80000000u;
+            const int out = POOL ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : fr * a.Wo + xo;
+            const unsigned rel = ok ? (unsigned)((out - first) * a.Cout * 2) : NOWHERE;
+            unsigned nnz = 0;
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) {
+                v16i acc[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const v4i c = *(const v4i *)(ctab + q * BN + cb * 32 + 8 * g + 4 * kg);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[q][4 * g + e] = c[e];
+                    }
+#pragma unroll
+                for (int h = 0; h < KS; ++h) {
+                    const v4i wh = wlds[(h * 2 + 0) * NCB + cb][lane], wl = wlds[(h * 2 + 1) * NCB + cb][lane];
+                    acc[0] = mfma_i8(wh, ah[h], acc[0]);
+                    acc[1] = mfma_i8(wl, ah[h], acc[1]);
+                    acc[2] = mfma_i8(wl, al[h], acc[2]);
+                    acc[1] = mfma_i8(wh, al[h], acc[1]);
+                }
+                int peak = 0;
+                unsigned word[4][2] = {};
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int ch = cb * 32 + 8 * g + 4 * kg;
+                    if (cb * 32 + 8 * g >= a.Cout) continue; // (uniform)
+                    const unsigned one = ch < a.Cout ? 0x00010001u : 0u; // what a code that exists may add to the count
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        int r[2];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const int i = 4 * g + 2 * h + e;
+                            // floor(v / 256): the dropped low byte cannot carry into a multiple of 256
+                            const int W = (acc[0][i] << 8) + (acc[1][i] + rs2 + ((acc[2][i] + odd) >> 8));
+                            r[e] = acc[0][i] = W >> (s - 8);
+                        }
+                        peak = max(max(peak, r[0]), r[1]);
+                        const v2s zero = {0, 0};
+                        const v2s q = __builtin_elementwise_min(__builtin_elementwise_max(__builtin_bit_cast(v2s, __builtin_amdgcn_cvt_pk_i16(r[0], r[1])), zero), top2);
+                        word[g][h] = __builtin_bit_cast(unsigned, q);
+                        nnz = __builtin_bit_cast(unsigned, (v2us)(__builtin_bit_cast(v2us, nnz) + __builtin_elementwise_min(__builtin_bit_cast(v2us, q), __builtin_bit_cast(v2us, one))));
+                    }
+                    if constexpr (!POOL)
+                        __builtin_amdgcn_raw_buffer_store_b64((v2u){word[g][0], word[g][1]}, yrsrc, (int)(ch < a.Cout ? rel + (unsigned)ch * 2u : NOWHERE), 0, 0);
+                }
+                if constexpr (POOL) {
+                    unsigned pick[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        v2s b[4];
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            b[g] = __builtin_bit_cast(v2s, word[g][h]);
+                            b[g] = __builtin_elementwise_max(b[g], __builtin_bit_cast(v2s, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, b[g]), 0xB1, 0xF, 0xF, true)));
+                            b[g] = __builtin_elementwise_max(b[g], __builtin_bit_cast(v2s, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, b[g]), 0x4E, 0xF, 0xF, true)));
+                        }
+                        const v2s lo = lane & 1 ? b[1] : b[0], hi = lane & 1 ? b[3] : b[2];
+                        pick[h] = __builtin_bit_cast(unsigned, lane & 2 ? hi : lo);
+                    }
+                    const int ch = cb * 32 + 8 * (lane & 3) + 4 * kg;
+                    __builtin_amdgcn_raw_buffer_store_b64((v2u){pick[0], pick[1]}, yrsrc, (int)(ch < a.Cout ? rel + (unsigned)ch * 2u : NOWHERE), 0, 0);
+                }
+                // clipped values: counted one by one only where there are any
+                if (a.count_sat && __builtin_amdgcn_ballot_w64(peak > cmax)) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int most = ok && cb * 32 + 8 * g + 4 * kg < a.Cout ? cmax : 0x7fffffff;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) ns += acc[0][4 * g + e] > most;
+                    }
+                }
+            }
+            nz += ok ? codes - (nnz & 0xffffu) - (nnz >> 16) : 0u;
+            if (wi + 1 < wi_end) {
+                park(wi + 1, raw[buf ^ 1]);
+                __syncthreads(); // the next patch is visible (and this one has been read: it is overwritten a tile later)
+            }
+        }
+    }
+    if (a.zero_partial || a.direct_counts) {
+        unsigned z = nz, c = ns; // (sums over many tiles: each count for itself)
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            z += __shfl_xor(z, off, 64);
+            c += __shfl_xor(c, off, 64);
+        }
+        if (lane == 0) {
+            wave_counts[0][wave] = z;
+            wave_counts[1][wave] = c;
+        }
+        __syncthreads();
+        if (tid < 2) {
+            unsigned total = 0;
+            for (int i = 0; i < THREADS / 64; ++i) total += wave_counts[tid][i];
+            publish_count(a, tid, total);
+        }
+    }
+}
+
 // Layers with 16, 32 or 48 input channels (16-bit codes): a 64-channel chunk would be mostly
 // padding, so the reduction runs over window rows instead.  The patch is staged densely (Cin bytes
 // per pixel and limb), which makes the S * Cin codes under one kernel row of a window consecutive:
@@ -1988,6 +2236,16 @@ static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, 
     a.fast = (y && !acc_out && fast_epilogue_ok(d, p, f_acc, bias != nullptr, qb, qy, relu, r)) ? 1 : 0;
     a.pool = p.pool;
     if (p.pool && !(a.fast && a.y16 && d->Cout % 4 == 0)) return LP_EUNSUPPORTED;
+    // flat-window layers of which only 16-bit codes are wanted: workgroups that run several tiles, as many as the chip holds at
+    // once.  With a tile or less per CU there is nothing to run on with, and setting up is longer: 128 tiles 8.0 : 8.3 us,
+    // 8 tiles 4.24 : 4.53, but 392 tiles 10.96 : 10.70.
+    const bool codes_only = p.flat && a.fast && a.y16 && !y_flags && p.tiles_n == 1 && a.total_work > kCUs && d->Cout % 4 == 0 &&
+                            a.act.s >= 9 && a.act.s <= 20;
+    if (codes_only) {
+        const int ncb = d->Cout <= 32 ? 1 : 2, per_cu = ncb * p.ksteps == 4 ? kFlatSlots - 1 : kFlatSlots;
+        grid = std::min(grid, kCUs * per_cu);
+        a.partial_stride = grid;
+    }
     lp_status st2;
     const int tails = a.split > 1 ? kXCDs * (p.per_xcd - p.full_per_xcd) : 0; // finishing workgroups
     // A small grid adds its counts to the counters itself: two atomics per workgroup cost less than
@@ -2005,7 +2263,17 @@ static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, 
     else if (p.flat) {
         // one slab: nothing to split; channel tiles of at most 32 channels need one column block
         const bool narrow = p.tiles_n == 1 && d->Cout <= 32;
-        if (p.ksteps == 1) {
+        if (codes_only) {
+#define LP_FLAT(NCB, KS)                                                                                          \
+    if (p.pool) hipLaunchKernelGGL((conv_flat_codes_kernel<NCB, KS, true>), dim3(grid), dim3(256), 0, hs, a);      \
+    else hipLaunchKernelGGL((conv_flat_codes_kernel<NCB, KS, false>), dim3(grid), dim3(256), 0, hs, a)
+            if (p.ksteps == 1) {
+                if (narrow) { LP_FLAT(1, 1); } else { LP_FLAT(2, 1); }
+            } else {
+                if (narrow) { LP_FLAT(1, 2); } else { LP_FLAT(2, 2); }
+            }
+#undef LP_FLAT
+        } else if (p.ksteps == 1) {
             if (narrow) hipLaunchKernelGGL((conv_flat_kernel<1, 1>), dim3(grid), dim3(256), 0, hs, a);
             else hipLaunchKernelGGL((conv_flat_kernel<2, 1>), dim3(grid), dim3(256), 0, hs, a);
         } else {

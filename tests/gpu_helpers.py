@@ -34,20 +34,21 @@ def quantize(x, q, r=lp.LP_ROUND_NEAREST_AWAY, seed=0, counters=True):
 
 
 def conv(x_codes, qx, w_codes, qw, qy=None, relu=True, r=lp.LP_ROUND_NEAREST_AWAY, bias=None, qb=None,
-         stride=1, pad=1, want_acc=True, want_y=True, count_sat=True):
+         stride=1, pad=1, want_acc=True, want_y=True, count_sat=True, pool=0):
     """x_codes [N,Cin,H,W], w_codes [Cout,Cin,R,S] (numpy ints, oracle layout).
     Returns dict(acc=[N,Cout,Ho,Wo] int64 or None, y=int32 codes or None, zeros=int, info=plan)."""
     N, Cin, H, W = x_codes.shape
     Cout, _, R, S = w_codes.shape
-    d = lp.ConvDesc(N, H, W, Cin, Cout, R, S, stride, pad)
+    d = lp.ConvDesc(N, H, W, Cin, Cout, R, S, stride, pad, pool)
     Ho, Wo = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    yh, yw = (Ho // 2, Wo // 2) if pool else (Ho, Wo)
     xd = to_dev(x_codes.transpose(0, 2, 3, 1).astype(code_np_dtype(qx[0])))
     wd = to_dev(w_codes.transpose(0, 2, 3, 1).astype(code_np_dtype(qw[0])))
     packed = torch.empty(lp.lp_conv_packed_bytes(d, qx, qw), dtype=torch.uint8, device="cuda")
     lp.lp_conv_pack_weights(d, qx, qw, wd, packed)
     bd = to_dev(np.asarray(bias).astype(code_np_dtype(qb[0]))) if bias is not None else None
     acc = torch.empty((N, Ho, Wo, Cout), dtype=torch.int64, device="cuda") if want_acc else None
-    y = torch.empty((N, Ho, Wo, Cout), dtype=code_torch_dtype(qy[0]), device="cuda") if (want_y and qy) else None
+    y = torch.empty((N, yh, yw, Cout), dtype=code_torch_dtype(qy[0]), device="cuda") if (want_y and qy) else None
     z, sat = counter(), counter()
     # filled with junk: the library must not rely on the workspace's previous contents
     ws = torch.full((max(lp.lp_conv_workspace_bytes(d, qx, qw), 16),), 0xA5, dtype=torch.uint8, device="cuda")

@@ -620,3 +620,36 @@ def test_codes_and_counts_of_the_short_epilogue(oracle, shape, k, qx, qw, n):
         got = conv(x, qx, w, qw, qy=qy, pad=k // 2, want_acc=False)
         y, zeros, sats = oracle.act(acc, f_acc, *qy, True, oracle.ROUND_AWAY, with_sat=True)
         assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (zeros, sats)
+
+
+@pytest.mark.parametrize("N,Cin,H,W,Cout,k,pad,n,pool", [
+    (3, 3, 112, 113, 64, 3, 1, 16, 0),       # ragged tiles at the right edge
+    (1, 3, 208, 192, 16, 1, 0, 16, 1),       # K = 3, half of the 32-channel block, pooled
+    (1, 3, 192, 192, 64, 3, 1, 16, 1),       # both blocks, pooled
+    (220, 3, 13, 13, 36, 3, 1, 16, 0),       # tiles straddle images; a group of four channels without its neighbour
+    (9, 7, 64, 64, 64, 3, 1, 16, 0),         # K = 63: two K = 32 halves; more of a patch than is under way at a time
+    (40, 1, 30, 30, 20, 7, 3, 12, 0),        # K = 49, one block, 12-bit codes
+    (34, 2, 32, 32, 8, 5, 2, 16, 1),         # K = 50, pooled
+    (1, 1, 33, 1100, 4, 1, 0, 16, 0),        # K = 1
+])
+def test_flat_window_workgroups_of_several_tiles(oracle, N, Cin, H, W, Cout, k, pad, n, pool):
+    """More than one tile per CU and codes alone: every shift the kernel takes and one on each side of them, with biases whose
+    upper part is clamped, formats that clip, and the same calls with one tile per workgroup's formats."""
+    rng = np.random.default_rng(N + 10 * Cin + k)
+    qx, qw = (16, 8, 8), (16, 1, 15)
+    x, w = _codes(rng, (N, Cin, H, W), zero_frac=0.3), _codes(rng, (Cout, Cin, k, k))
+    f_acc = qx[2] + qw[2]
+    bias, qb = _codes(rng, (Cout,)), (16, 16, 0)                   # shifted by 23: up to 2^38
+    qx12 = (16, 1, 15)                                             # for the larger shifts
+    for q, fo, with_bias in ((qx, 14, True), (qx, 13, False), (qx, 9, True), (qx12, 15, False), (qx12, 10, True), (qx12, 9, False)):
+        f = q[2] + qw[2]
+        fb = f_acc - 23 if q is qx else f - 24
+        b = bias if with_bias else None
+        qb = (16, 16 - fb, fb)
+        qy = (n, n - min(fo, n - 1), min(fo, n - 1))
+        acc = oracle.conv(x, w, bias=b, f_acc=f, fb=fb, pad=pad, threads=8)
+        y, zeros, sats = oracle.act(acc, f, *qy, True, oracle.ROUND_AWAY, with_sat=True)
+        got = conv(x, q, w, qw, qy=qy, pad=pad, want_acc=False, bias=b, qb=qb if with_bias else None, pool=pool)
+        assert got["info"]["kernel"] == lp.LP_KERNEL_FLAT and got["info"]["tiles_m"] > 256
+        assert np.array_equal(got["y"], oracle.maxpool2x2(y) if pool else y)
+        assert (got["zeros"], got["sats"]) == (zeros, sats)

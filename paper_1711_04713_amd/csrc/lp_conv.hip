@@ -457,7 +457,7 @@ __host__ __device__ inline size_t slab_byte(int co, int kk, int CoutP) { return 
 // MFMA layout: [chunk][tap][limb][K half][CoutP][32] int8, i.e. slabs in the order the kernel streams them.
 template <typename WT, int LIMBS>
 __global__ void pack_weights_kernel(const WT *__restrict__ w, unsigned char *__restrict__ out, int Cout,
-                                    int Cin, int RS, int nchunks, int CoutP, size_t total)
+                                    int Cin, int RS, int nchunks, int CoutP, size_t total, const int64_t *__restrict__ corr)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
          i += (size_t)gridDim.x * blockDim.x) {
@@ -471,12 +471,8 @@ __global__ void pack_weights_kernel(const WT *__restrict__ w, unsigned char *__r
         int hi = 0, lo = 0;
         if (co < Cout && ci < Cin) {
             const int code = (int)w[((size_t)co * RS + tap) * Cin + ci];
-            if constexpr (LIMBS == 2) {
-                hi = code >> 8;
-                lo = (code & 255) - 128;
-            } else {
-                hi = code;
-            }
+            if constexpr (LIMBS == 2) weight_limbs(code, corr[co] & kSignedForm, hi, lo);
+            else hi = code;
         }
         const size_t base = (((size_t)chunk * RS + tap) * LIMBS) * CoutP * CK;
         out[base + slab_byte(co, kk, CoutP)] = (unsigned char)hi;
@@ -487,16 +483,14 @@ __global__ void pack_weights_kernel(const WT *__restrict__ w, unsigned char *__r
 // Flat layout: one slab [limb][K half][CoutP][32], byte k of a row = weight k of the (r, s, ci) window.
 template <typename WT>
 __global__ void pack_weights_flat_kernel(const WT *__restrict__ w, unsigned char *__restrict__ out,
-                                         int Cout, int K, int CoutP)
+                                         int Cout, int K, int CoutP, const int64_t *__restrict__ corr)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= CoutP * CK) return;
     const int kk = i % CK, co = i / CK;
     int hi = 0, lo = 0;
     if (co < Cout && kk < K) {
-        const int code = (int)w[(size_t)co * K + kk];
-        hi = code >> 8;
-        lo = (code & 255) - 128;
+        weight_limbs((int)w[(size_t)co * K + kk], corr[co] & kSignedForm, hi, lo);
     }
     out[slab_byte(co, kk, CoutP)] = (unsigned char)hi;
     out[(size_t)CoutP * CK + slab_byte(co, kk, CoutP)] = (unsigned char)lo;
@@ -507,7 +501,7 @@ __global__ void pack_weights_flat_kernel(const WT *__restrict__ w, unsigned char
 // channels hold the bytes (0, 0).
 template <typename WT>
 __global__ void pack_weights_rows_kernel(const WT *__restrict__ w, unsigned char *__restrict__ out, int Cout, int R,
-                                         int SC, int KHR, int KHP, int CoutP)
+                                         int SC, int KHR, int KHP, int CoutP, const int64_t *__restrict__ corr)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= KHP * CoutP * 32) return;
@@ -515,9 +509,7 @@ __global__ void pack_weights_rows_kernel(const WT *__restrict__ w, unsigned char
     const int r = h / KHR, pos = (h % KHR) * 32 + kk;
     int hi = 0, lo = 0;
     if (co < Cout && r < R && pos < SC) {
-        const int code = (int)w[((size_t)co * R + r) * SC + pos];
-        hi = code >> 8;
-        lo = (code & 255) - 128;
+        weight_limbs((int)w[((size_t)co * R + r) * SC + pos], corr[co] & kSignedForm, hi, lo);
     }
     const size_t at = ((size_t)h * 2 * CoutP + co) * 32 + kk;
     out[at] = (unsigned char)hi;
@@ -790,7 +782,8 @@ __global__ __launch_bounds__(256 * KG)
     // THREADS is a multiple of PIECES, a thread always handles the same piece of its pixels.
     // A chunk's channel sums are collected by the part that holds the chunk's first tap, so that
     // parts which share a chunk do not count it twice.
-    bool own_sums = KG > 1 || (s0 % a.taps) == 0;
+    const bool sums = WL == 2 && needs_code_sums(a, ntile); // (uniform)
+    bool own_sums = sums && (KG > 1 || (s0 % a.taps) == 0);
     constexpr int APF = stage_batch(KG);
     constexpr int PIECES = (LIMBS == 2) ? 8 : 4;
     constexpr int ESZ_X = (LIMBS == 2) ? 2 : 1;
@@ -834,13 +827,15 @@ __global__ __launch_bounds__(256 * KG)
             if constexpr (WL == 2) {
                 // sum of the eight codes: four two-element dot products with (1, 1); each of a
                 // pixel's eight pieces adds its share to the pixel's sum
-                const v2s ones = {1, 1};
-                const int w0 = v.x, w1 = v.y, w2 = v.z, w3 = v.w;
-                int sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w0), ones, 0, false);
-                sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w1), ones, sum, false);
-                sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w2), ones, sum, false);
-                sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w3), ones, sum, false);
-                if (own_sums) atomicAdd(&psum[p], sum); // no value returned
+                if (own_sums) {
+                    const v2s ones = {1, 1};
+                    const int w0 = v.x, w1 = v.y, w2 = v.z, w3 = v.w;
+                    int sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w0), ones, 0, false);
+                    sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w1), ones, sum, false);
+                    sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w2), ones, sum, false);
+                    sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w3), ones, sum, false);
+                    atomicAdd(&psum[p], sum); // no value returned
+                }
             }
             *(__attribute__((address_space(3))) v2i *)(unsigned)at = hi;
             *(__attribute__((address_space(3))) v2i *)(unsigned)(at + APL) = lo;
@@ -1026,7 +1021,7 @@ __global__ __launch_bounds__(256 * KG)
     stage_activations(cc, true, [&] {
         if constexpr (LATE_ROWS) row_tables();
     });
-    own_sums = true; // every later chunk starts at its first tap
+    own_sums = sums; // every later chunk starts at its first tap
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -1110,6 +1105,7 @@ __global__ __launch_bounds__(256 * KG)
     // ---- sum of the codes under a tile row's window (two-limb correction term 128 * sum(a)):
     // the channel sums of its R x S patch pixels, complete since the last chunk was staged
     auto row_sum = [&](int m) __attribute__((always_inline)) {
+        if (!sums) return 0;
         const int base = abase_s[m];
         int sum = 0;
         if (a.R == 3 && a.S == 3) { // the common window, unrolled: nine independent LDS reads
@@ -1194,7 +1190,7 @@ __global__ __launch_bounds__(256 * KG)
             int rs = 0;
             if constexpr (WL == 2) {
                 const int m = wm * WROWS + (mbf + mb) * 32 + l32;
-                if (a.R == 3 && a.S == 3) {
+                if (!sums || (a.R == 3 && a.S == 3)) {
                     rs = row_sum(m);
                 } else {
                     for (int r = kg; r < a.R; r += 2)
@@ -1546,6 +1542,7 @@ __global__ __launch_bounds__(256)
 
     const unsigned char *rawb = (const unsigned char *)raw;
     const int base = abase[wave * 32 + l32];
+    const bool sums = needs_code_sums(a, ntile);
     int sum = 0;
     v4i ah[KS], al[KS];
 #pragma unroll
@@ -1562,7 +1559,7 @@ __global__ __launch_bounds__(256)
             pr[q] = __builtin_bit_cast(unsigned, two);
         }
         const int nv = a.Kflat - k0; // codes of this piece that exist (the same for half a wave)
-        if (nv < 16) {
+        if (sums && nv < 16) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 const int m = min(max(nv - 2 * q, 0), 2);
@@ -1575,15 +1572,16 @@ __global__ __launch_bounds__(256)
         for (int q = 0; q < 4; ++q) {
             hi[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x07050301u);
             lo[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x06040200u) ^ 0x80808080u;
+            if (!sums) continue;
             sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[2 * q]), ones, sum, false);
             sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[2 * q + 1]), ones, sum, false);
         }
-        // (a position past K is the code 0 = limbs (0, -128) here; it meets zero weights)
+        // (a position past K is some code, or the code 0, here; it meets zero weights)
         ah[h] = v4i{(int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
         al[h] = v4i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3]};
     }
     // the row's code sum: its two lanes hold different window positions
-    const int rowsum = sum + __shfl_xor(sum, 32, 64);
+    const int rowsum = sums ? sum + __shfl_xor(sum, 32, 64) : 0;
     // one 32-channel block at a time: its three accumulators, then its outputs
     TileCounts counts = {0, 0};
 #pragma unroll
@@ -1703,7 +1701,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
         }
         const int s = a.act.s;
         for (int c = tid; c < BN; c += THREADS) {
-            const int64_t t = c < a.Cout ? a.corr[c] + bias_term(a, c) : 0;
+            const int64_t t = c < a.Cout ? (a.corr[c] & ~kSignedForm) + bias_term(a, c) : 0;
             const int64_t top = t >> 16;
             // (beyond +-2^21 the code is at an end of its range whatever the limb sums are, for every shift up to 20)
             ctab[c] = (int)(top > (1 << 21) ? (1 << 21) : top < -(1 << 21) ? -(1 << 21) : top);
@@ -1726,6 +1724,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
         const unsigned codes = 4u * (unsigned)min(max((a.Cout - 4 * kg + 7) / 8, 0), NCB * 4);
         park(wi, raw[0]);
         __syncthreads();
+        auto run = [&](auto SUMS) __attribute__((always_inline)) {
+        constexpr bool sums = decltype(SUMS)::value;
         for (int buf = 0; wi < wi_end; ++wi, buf ^= 1) {
             if (wi + 1 < wi_end) request(wi + 1);
             int tile_r, tile_c, img0, yo0, img, yo;
@@ -1753,7 +1753,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
                     if (h * 32 + 2 * q < a.Kflat) { // (uniform; a position past K reads some code and meets zero weights)
                         const v2s two = {*(const short *)(rawb + o[2 * q]), *(const short *)(rawb + o[2 * q + 1])};
                         pr[q] = __builtin_bit_cast(unsigned, two);
-                        sum = __builtin_amdgcn_sdot2(two, __builtin_bit_cast(v2s, one[q]), sum, false);
+                        if constexpr (sums) sum = __builtin_amdgcn_sdot2(two, __builtin_bit_cast(v2s, one[q]), sum, false);
                     }
                 }
                 unsigned hi[4], lo[4];
@@ -1765,7 +1765,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
                 ah[h] = v4i{(int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
                 al[h] = v4i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3]};
             }
-            const int rs = sum + __shfl_xor(sum, 32, 64); // a row's two lanes hold different window positions
+            const int rs = sums ? sum + __shfl_xor(sum, 32, 64) : 0; // a row's two lanes hold different window positions
             const int rs2 = rs >> 1, odd = (rs & 1) << 7;
             // outputs: 32-bit offsets from the tile's first pixel
             const int first = POOL ? (img0 * (a.Ho >> 1) + (yo0 >> 1)) * (a.Wo >> 1) + (x0 >> 1) : fr0 * a.Wo + x0;
@@ -1810,7 +1810,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
                         for (int e = 0; e < 2; ++e) {
                             const int i = 4 * g + 2 * h + e;
                             // floor(v / 256): the dropped low byte cannot carry into a multiple of 256
-                            const int W = (acc[0][i] << 8) + (acc[1][i] + rs2 + ((acc[2][i] + odd) >> 8));
+                            const int W = (acc[0][i] << 8) + acc[1][i] + (rs2 + ((acc[2][i] + odd) >> 8));
                             r[e] = acc[0][i] = W >> (s - 8);
                         }
                         peak = max(max(peak, r[0]), r[1]);
@@ -1855,6 +1855,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
                 __syncthreads(); // the next patch is visible (and this one has been read: it is overwritten a tile later)
             }
         }
+        };
+        if (needs_code_sums(a, 0)) run(std::integral_constant<bool, true>{});
+        else run(std::integral_constant<bool, false>{});
     }
     if (a.zero_partial || a.direct_counts) {
         unsigned z = nz, c = ns; // (sums over many tiles: each count for itself)
@@ -1939,6 +1942,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
     // pixels outside the image read as zeros (an offset past the descriptor)
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void *>(a.x), 0, (int)((unsigned)(a.N * a.H * a.W) * (unsigned)a.Cin * 2u), 0x00020000);
+    const bool sums = needs_code_sums(a, ntile);
     constexpr int UF = 2; // units in flight per thread
     for (int i0 = tid; i0 < NU; i0 += UF * THREADS) {
         v4i c[UF][2];
@@ -1972,12 +1976,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
             for (int q = 0; q < 4; ++q) {
                 hi[q] = __builtin_amdgcn_perm(pr2[2 * q + 1], pr2[2 * q], 0x07050301u);
                 lo[q] = __builtin_amdgcn_perm(pr2[2 * q + 1], pr2[2 * q], 0x06040200u) ^ 0x80808080u;
+                if (!sums) continue;
                 sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr2[2 * q]), ones, sum, false);
                 sum = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr2[2 * q + 1]), ones, sum, false);
             }
             *(v4i *)(Asm + dst[u]) = v4i{(int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
             *(v4i *)(Asm + APL + dst[u]) = v4i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3]};
-            usum[i0 + u * THREADS] = sum;
+            if (sums) usum[i0 + u * THREADS] = sum;
         }
     }
     for (int m = tid; m < BM; m += THREADS) {
@@ -1997,12 +2002,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB == 1 ? 
 
     // the sum of the codes under the row's window: its two lanes take alternate window rows
     int sum = 0;
-    {
+    if (sums) {
         const int ub = ubase[wave * 32 + l32];
         for (int r = kg; r < a.R; r += 2)
             for (int u = 0; u < a.SU; ++u) sum += usum[ub + r * a.UPR + u];
     }
-    const int rowsum = sum + __shfl_xor(sum, 32, 64);
+    const int rowsum = sums ? sum + __shfl_xor(sum, 32, 64) : 0;
     // the lane's 16-byte slot of its row's first window code, as an LDS address
     typedef __attribute__((address_space(3))) const v4i lds_cv4i;
     const int a_l = (int)(unsigned long)(__attribute__((address_space(3))) unsigned char *)Asm + abase[wave * 32 + l32] + kg * 16;
@@ -2316,16 +2321,20 @@ static lp_status pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, con
     unsigned char *out = (unsigned char *)packed;
     int64_t *corr = (int64_t *)(out + p.corr_offset);
     const int cgrid = p.CoutP; // one wave per output channel
+    if (p.limbs == 2 && p.wl == 2) { // which form the weights of each tile take
+        if (w16) hipLaunchKernelGGL(weight_form_kernel<int16_t>, dim3(p.CoutP / 64), dim3(1024), 0, hs, (const int16_t *)w, corr, d->Cout, RS * d->Cin);
+        else hipLaunchKernelGGL(weight_form_kernel<int8_t>, dim3(p.CoutP / 64), dim3(1024), 0, hs, (const int8_t *)w, corr, d->Cout, RS * d->Cin);
+    }
     if (p.rows) {
         const int K = RS * d->Cin, rgrid = (p.KHP * p.CoutP * 32 + 255) / 256;
         if (w16) {
             hipLaunchKernelGGL(pack_weights_rows_kernel<int16_t>, dim3(rgrid), dim3(256), 0, hs, (const int16_t *)w, out,
-                               d->Cout, d->R, d->S * d->Cin, p.KHR, p.KHP, p.CoutP);
+                               d->Cout, d->R, d->S * d->Cin, p.KHR, p.KHP, p.CoutP, corr);
             hipLaunchKernelGGL(weight_corr_kernel<int16_t>, dim3(cgrid), dim3(64), 0, hs,
                                (const int16_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         } else {
             hipLaunchKernelGGL(pack_weights_rows_kernel<int8_t>, dim3(rgrid), dim3(256), 0, hs, (const int8_t *)w, out,
-                               d->Cout, d->R, d->S * d->Cin, p.KHR, p.KHP, p.CoutP);
+                               d->Cout, d->R, d->S * d->Cin, p.KHR, p.KHP, p.CoutP, corr);
             hipLaunchKernelGGL(weight_corr_kernel<int8_t>, dim3(cgrid), dim3(64), 0, hs,
                                (const int8_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         }
@@ -2335,12 +2344,12 @@ static lp_status pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, con
         const int K = RS * d->Cin, fgrid = (p.CoutP * CK + 255) / 256;
         if (w16) {
             hipLaunchKernelGGL(pack_weights_flat_kernel<int16_t>, dim3(fgrid), dim3(256), 0, hs,
-                               (const int16_t *)w, out, d->Cout, K, p.CoutP);
+                               (const int16_t *)w, out, d->Cout, K, p.CoutP, corr);
             hipLaunchKernelGGL(weight_corr_kernel<int16_t>, dim3(cgrid), dim3(64), 0, hs,
                                (const int16_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         } else {
             hipLaunchKernelGGL(pack_weights_flat_kernel<int8_t>, dim3(fgrid), dim3(256), 0, hs,
-                               (const int8_t *)w, out, d->Cout, K, p.CoutP);
+                               (const int8_t *)w, out, d->Cout, K, p.CoutP, corr);
             hipLaunchKernelGGL(weight_corr_kernel<int8_t>, dim3(cgrid), dim3(64), 0, hs,
                                (const int8_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         }
@@ -2348,7 +2357,7 @@ static lp_status pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, con
     }
 #define LP_PACK(WT, L, W)                                                                           \
     hipLaunchKernelGGL((pack_weights_kernel<WT, W>), dim3(grid), dim3(256), 0, hs, (const WT *)w, out, \
-                       d->Cout, d->Cin, RS, p.nchunks, p.CoutP, total);                                \
+                       d->Cout, d->Cin, RS, p.nchunks, p.CoutP, total, corr);                          \
     hipLaunchKernelGGL(weight_corr_kernel<WT>, dim3(cgrid), dim3(64), 0, hs, (const WT *)w, corr,      \
                        d->Cout, p.CoutP, RS * d->Cin, L, W);                                           \
     if (L == 2)                                                                                        \

@@ -134,7 +134,7 @@ static lp_status make_fc_plan(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw, Fc
 // fragments consecutive in the order the kernel consumes them.
 template <typename WT, int LIMBS>
 __global__ __launch_bounds__(256) void fc_pack_weights_kernel(const WT *__restrict__ w, unsigned char *__restrict__ out,
-                                                             int Nout, int K, int KH, size_t pieces)
+                                                             int Nout, int K, int KH, size_t pieces, const int64_t *__restrict__ corr)
 {
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < pieces; i += (size_t)gridDim.x * 256) {
         const int lane = (int)(i & 63);
@@ -151,8 +151,10 @@ __global__ __launch_bounds__(256) void fc_pack_weights_kernel(const WT *__restri
             int code = 0;
             if (col < Nout && k0 + b < K) code = (int)w[(size_t)col * K + k0 + b];
             if constexpr (LIMBS == 2) {
-                hi[b] = (unsigned char)(code >> 8);
-                lo[b] = (col < Nout && k0 + b < K) ? (unsigned char)((code & 255) - 128) : 0;
+                int h, l;
+                weight_limbs(code, corr[col] & kSignedForm, h, l);
+                hi[b] = (unsigned char)h;
+                lo[b] = (col < Nout && k0 + b < K) ? (unsigned char)l : 0;
             } else {
                 hi[b] = (unsigned char)code;
             }
@@ -259,12 +261,13 @@ struct FcArgs {
 template <int LIMBS, int THREADS>
 __device__ __forceinline__ void fc_tile_tables(const FcArgs &f, int mt, int nt, int *outoff, int *rowsum, int *ctab)
 {
+    const bool sums = LIMBS == 2 && needs_code_sums(f.c, nt); // (64-column tiles)
     for (int m = threadIdx.x; m < FM; m += THREADS) {
         const int row = mt * FM + m;
         outoff[m] = row < f.M ? row : -1;
         // the row's partial sums, all requested before any is added (kc is uniform)
         int t = 0;
-        if (LIMBS == 2 && row < f.mrows) {
+        if (sums && row < f.mrows) {
             int v[FKC];
 #pragma unroll
             for (int i = 0; i < FKC; ++i) v[i] = i < f.kc ? f.xsum[(size_t)i * f.mrows + row] : 0;
@@ -584,8 +587,9 @@ __global__ __launch_bounds__(64 * few_waves<RB>()) void fc_few_rows_kernel(const
     const int col0 = blockIdx.x * 32, nt = blockIdx.x >> 1, cb = blockIdx.x & 1;
     if (tid < 32) {
         const int col = col0 + tid;
-        colterm[tid] = col < a.Cout ? a.corr[col] + bias_term(a, col) : 0;
+        colterm[tid] = col < a.Cout ? (a.corr[col] & ~kSignedForm) + bias_term(a, col) : 0;
     }
+    const bool summing = LIMBS == 2 && needs_code_sums(a, nt);
     constexpr int KHB = LIMBS * 2 * FRAG; // weight bytes of one K half of a 64-column tile
     const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<unsigned char *>(a.wp) + (size_t)nt * f.wslab, 0, (int)f.wslab, 0x00020000);
@@ -659,22 +663,21 @@ __global__ __launch_bounds__(64 * few_waves<RB>()) void fc_few_rows_kernel(const
             if constexpr (LIMBS == 2) {
                 unsigned pr[8] = {(unsigned)xr[rb][0].x, (unsigned)xr[rb][0].y, (unsigned)xr[rb][0].z, (unsigned)xr[rb][0].w,
                                   (unsigned)xr[rb][1].x, (unsigned)xr[rb][1].y, (unsigned)xr[rb][1].z, (unsigned)xr[rb][1].w};
-                if ((kh + 1) * 32 > f.K) { // (uniform) what follows the row's end meets zero weights but is no part of its sum
-                    const int nv = f.K - (kh * 32 + kg * 16);
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        const int m = min(max(nv - 2 * q, 0), 2);
-                        pr[q] &= m == 2 ? 0xffffffffu : m == 1 ? 0xffffu : 0u;
-                    }
-                }
                 unsigned h[4], l[4];
-                const v2s ones = {1, 1};
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     h[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x07050301u);
                     l[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x06040200u) ^ 0x80808080u;
-                    sum[rb] = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[2 * q]), ones, sum[rb], false);
-                    sum[rb] = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[2 * q + 1]), ones, sum[rb], false);
+                }
+                if (summing) { // (uniform)
+                    const int nv = f.K - (kh * 32 + kg * 16);
+                    const bool ragged = (kh + 1) * 32 > f.K; // what follows the row's end meets zero weights but is no part of its sum
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const int m = ragged ? min(max(nv - 2 * q, 0), 2) : 2;
+                        const v2s ones = {(short)(m >= 1), (short)(m == 2)};
+                        sum[rb] = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[q]), ones, sum[rb], false);
+                    }
                 }
                 const v4i xh = {(int)h[0], (int)h[1], (int)h[2], (int)h[3]}, xl = {(int)l[0], (int)l[1], (int)l[2], (int)l[3]};
                 acc[rb][0] = mfma_i8(wr[0], xh, acc[rb][0]);
@@ -794,8 +797,9 @@ static lp_status fc_pack(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw, const v
     int64_t *corr = (int64_t *)(out + p.corr_offset);
     const int CoutP = p.n_tiles * FN;
 #define LP_FCPACK(WT, L)                                                                                     \
+    if (L == 2) hipLaunchKernelGGL(weight_form_kernel<WT>, dim3(p.n_tiles), dim3(1024), 0, hs, (const WT *)w, corr, Nout, K); \
     hipLaunchKernelGGL((fc_pack_weights_kernel<WT, L>), dim3(grid), dim3(256), 0, hs, (const WT *)w, out, Nout, K, \
-                       p.KH, pieces);                                                                        \
+                       p.KH, pieces, corr);                                                                  \
     hipLaunchKernelGGL(weight_corr_kernel<WT>, dim3(CoutP), dim3(64), 0, hs, (const WT *)w, corr, Nout, CoutP, K, L, L)
     if (p.limbs == 2) {
         if (qw.n > 8) { LP_FCPACK(int16_t, 2); } else { LP_FCPACK(int8_t, 2); }

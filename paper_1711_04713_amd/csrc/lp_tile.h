@@ -95,6 +95,21 @@ __device__ __forceinline__ void publish_count(const ConvArgs &a, int which, unsi
     }
 }
 
+// Limbs of two-limb weights.  The plain form is that of the activations, b = 256 * bh + bl + 128, whose offset makes every
+// output owe 128 times the sum of the codes under its window.  With a signed low limb, b = 256 * bh + bl, nothing is owed
+// but the constant 128 * sum(b) (the activations' offset): no code sums are gathered, added up or carried along.  bh then
+// is (b + 128) >> 8 and fits a byte for codes below 32640.  A tile of 64 channels takes the signed form unless one of
+// its weights is as large as that (the top 128 codes, where a format that clips weights puts them); bit 0 of its
+// channels' corrections, otherwise multiples of 128, says so.  us, with code sums : without, batch 32: 112x112 128 -> 128
+// 3x3 189.6 : 178.9, 56x56 256 -> 256 185.7 : 177.6, 22x22 64 -> 64 5x5 17.9 : 15.6, 112x112 16 -> 16 7x7 64.5 : 57.5.
+constexpr int64_t kSignedForm = 1;
+__device__ __forceinline__ void weight_limbs(int code, bool signed_form, int &hi, int &lo)
+{
+    lo = signed_form ? (int)(signed char)code : (code & 255) - 128;
+    hi = signed_form ? (code - lo) >> 8 : code >> 8;
+}
+__device__ __forceinline__ bool needs_code_sums(const ConvArgs &a, int ntile) { return (a.corr[(size_t)ntile * 64] & kSignedForm) == 0; }
+
 __device__ __forceinline__ v16i mfma_i8(v4i a, v4i b, v16i c)
 {
     return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
@@ -136,7 +151,7 @@ __device__ __forceinline__ int requant_relu32(int hi, int lo16, int s)
 // deadmask: chunks of 64 input channels that were skipped as all-zero; their share of the weight
 // correction, 128 * sum(w over the chunk) - 16384 * (positions of the chunk), is taken out again
 // (their limb products, which it would have cancelled, were never formed).  With 8-bit weights under
-// 16-bit activations (limbs 2, wlimbs 1) the correction has no 16384 * K term: the weights carry no offset.
+// 16-bit activations (limbs 2, wlimbs 1), and with signed low limbs, the correction has no 16384 * K term: the weights carry no offset.
 // threads: of the workgroup, a constant where the kernel knows it (blockDim comes from memory, and
 // that read is as long as all else here: 0.5 us of a one-limb layer of one round)
 template <int BN>
@@ -145,12 +160,13 @@ __device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int
 {
     for (int c = threadIdx.x; c < BN; c += threads) {
         const int colg = ntile * BN + c;
-        int64_t t = colg < a.Cout ? a.corr[colg] + bias_term(a, colg) : 0;
+        const int64_t corr = colg < a.Cout ? a.corr[colg] : 0;
+        int64_t t = colg < a.Cout ? (corr & ~kSignedForm) + bias_term(a, colg) : 0;
         if (limbs == 2 && deadmask && colg < a.Cout) {
             for (unsigned rem = deadmask; rem; rem &= rem - 1) {
                 const int ch = __builtin_ctz(rem);
                 const int kc = a.taps * min(64, a.Cin - 64 * ch);
-                t -= (int64_t)128 * a.wsum[(size_t)ch * a.CoutP + colg] - (wlimbs == 2 ? (int64_t)16384 * kc : 0);
+                t -= (int64_t)128 * a.wsum[(size_t)ch * a.CoutP + colg] - (wlimbs == 2 && !(corr & kSignedForm) ? (int64_t)16384 * kc : 0);
             }
         }
         if (a.fast) {
@@ -183,7 +199,7 @@ __device__ __forceinline__ void build_colterms(const ConvArgs &a, int ntile, int
 // 8*(v/4) + 4*(lane/32) + v%4 of its 32-channel block (the wave's blocks start at channel col0w
 // of the tile): four consecutive channels per group of four registers, which leave as one 8-byte
 // (4-byte) store.
-// row_sum(m): sum of the codes under tile row m's window (two-limb weights only); outoff and ctab (see
+// row_sum(m): sum of the codes under tile row m's window (two-limb weights of the plain form, else 0); outoff and ctab (see
 // build_colterms) are LDS tables, complete and visible.  Returns the lane's counts of zero codes
 // and (when a.count_sat) of values clipped at an end of the code range; see wave_total.
 // The accumulators passed in cover MBL of the wave's MB row blocks, starting at block mb0, and GL
@@ -532,9 +548,30 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
 }
 
 
-// corr[co] = 128 * sum_k w[co][k] (- 16384 * K with two-limb weights) for two-limb activations, 0 otherwise:
+// Says in the corrections of a tile of 64 output channels (blockIdx.x, 1024 threads) which form its weights take; w: [Cout][K],
+// 16-byte aligned.  Runs before the packing kernels, which read it there.
+template <typename WT>
+__global__ __launch_bounds__(1024) void weight_form_kernel(const WT *__restrict__ w, int64_t *__restrict__ corr, int Cout, int K)
+{
+    const int c0 = blockIdx.x * 64;
+    const size_t n = (size_t)max(min(64, Cout - c0), 0) * K; // the tile's weights are consecutive
+    int large = 0;
+    if constexpr (sizeof(WT) == 2) {
+        const WT *src = w + (size_t)c0 * K;
+        for (size_t i = threadIdx.x; i < n / 8; i += 1024) {
+            const v8s v = reinterpret_cast<const v8s *>(src)[i];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) large |= v[e] >= 32640;
+        }
+        for (size_t i = n / 8 * 8 + threadIdx.x; i < n; i += 1024) large |= src[i] >= 32640;
+    }
+    large = __syncthreads_or(large);
+    if (threadIdx.x < 64) corr[c0 + threadIdx.x] = large ? 0 : kSignedForm;
+}
+
+// corr[co] = 128 * sum_k w[co][k] (- 16384 * K with two-limb weights of the plain form) for two-limb activations, 0 otherwise:
 // the weight half of the offset correction, computed once when the weights are packed.  One wave per output channel
-// (blockIdx.x = co, 64 threads), lanes striding over K.
+// (blockIdx.x = co, 64 threads), lanes striding over K.  Two-limb weights: their form is already there and stays.
 template <typename WT>
 __global__ __launch_bounds__(64) void weight_corr_kernel(const WT *__restrict__ w, int64_t *__restrict__ corr, int Cout,
                                                         int CoutP, int K, int limbs, int wlimbs)
@@ -546,7 +583,11 @@ __global__ __launch_bounds__(64) void weight_corr_kernel(const WT *__restrict__ 
         for (int k = threadIdx.x; k < K; k += 64) s += (long long)w[(size_t)co * K + k];
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) s += __shfl_down(s, off, 64);
-    if (threadIdx.x == 0) corr[co] = (limbs == 2 && co < Cout) ? 128 * s - (wlimbs == 2 ? (long long)16384 * K : 0) : 0;
+    if (threadIdx.x == 0) {
+        const int64_t form = wlimbs == 2 ? corr[co] & kSignedForm : 0;
+        const int64_t v = (limbs == 2 && co < Cout) ? 128 * s - (wlimbs == 2 && !form ? (long long)16384 * K : 0) : 0;
+        corr[co] = v | form;
+    }
 }
 
 // Adds n per-workgroup counts (zeros at partials[0..n), clipped values at partials[n..2n)) to the

@@ -653,3 +653,50 @@ def test_flat_window_workgroups_of_several_tiles(oracle, N, Cin, H, W, Cout, k, 
         assert got["info"]["kernel"] == lp.LP_KERNEL_FLAT and got["info"]["tiles_m"] > 256
         assert np.array_equal(got["y"], oracle.maxpool2x2(y) if pool else y)
         assert (got["zeros"], got["sats"]) == (zeros, sats)
+
+
+def _weights_of_both_forms(rng, shape, top):
+    """Codes over the whole range of the signed limb form; top: the largest one, planted in the second tile of 64 channels (and
+    in the only one of fewer), once."""
+    w = rng.integers(-32768, 32640, shape).astype(np.int32)
+    w.reshape(shape[0], -1)[min(shape[0] - 1, 70), -1] = top
+    return w
+
+
+@pytest.mark.parametrize("top", [32639, 32640, 32767])
+@pytest.mark.parametrize("N,Cin,H,W,Cout,k", [
+    (2, 64, 12, 11, 130, 3),       # patch kernel: three channel tiles, the second in the other form
+    (1, 72, 9, 9, 40, 5),          # half-filled second chunk, window sums of 25 pixels
+    (1, 256, 12, 10, 96, 3),       # parts of tiles
+    (1, 512, 28, 28, 256, 3),      # three wave groups
+    (2, 3, 20, 20, 72, 3),         # flat window
+    (1, 3, 200, 200, 24, 3),       # flat window, several tiles per workgroup
+    (2, 16, 17, 19, 80, 7),        # window rows
+    (2, 48, 9, 9, 20, 3),
+])
+def test_weight_limb_forms(oracle, top, N, Cin, H, W, Cout, k):
+    """The largest code whose low limb can be signed, the smallest that cannot, and the largest of all, beside the smallest code."""
+    rng = np.random.default_rng(top + Cin + k)
+    x = _codes(rng, (N, Cin, H, W), zero_frac=0.3)
+    w = _weights_of_both_forms(rng, (Cout, Cin, k, k), top)
+    acc = oracle.conv(x, w, pad=k // 2, threads=8)
+    got = conv(x, QX, w, QW, pad=k // 2, want_y=False)
+    assert np.array_equal(got["acc"], acc)
+    for fo in (11, 9):
+        qy = (16, 16 - fo, fo)
+        y, zeros, sats = oracle.act(acc, 27, *qy, True, oracle.ROUND_AWAY, with_sat=True)
+        got = conv(x, QX, w, QW, qy=qy, pad=k // 2, want_acc=False)
+        assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (zeros, sats)
+
+
+@pytest.mark.parametrize("top", [32639, 32640, 32767])
+@pytest.mark.parametrize("M,K,Nout", [(1, 1000, 130), (40, 333, 70), (64, 515, 100), (130, 700, 200), (300, 4100, 128)])
+def test_fc_weight_limb_forms(oracle, top, M, K, Nout):
+    rng = np.random.default_rng(top + M)
+    x, w = _codes(rng, (M, K)), _weights_of_both_forms(rng, (Nout, K), top)
+    got = fc(x, QX, w, QW)
+    acc = x.astype(np.int64) @ w.astype(np.int64).T
+    assert np.array_equal(got["acc"], acc)
+    y, zeros, sats = oracle.act(acc, 27, *QY, True, oracle.ROUND_AWAY, with_sat=True)
+    got = fc(x, QX, w, QW, qy=QY, want_acc=False)
+    assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (zeros, sats)

@@ -378,7 +378,10 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
                 const int pra = rh + d->R - 1 + cross * (d->R - 1);
                 const int npixa = pra * pw;
                 const double cost = (double)tiles_c * tiles_r * ((double)BM * RS + 0.5 * npixa);
-                if (cost >= best_free && (cost >= best || (d->pool && !poolable))) continue; // improves nothing
+                // (flat windows: of tiles that cost the same the widest, whose patch and output rows are longest: the 1x1 first
+                // layer of Giga1Net took 128 x 1 pixels, 34.0 us, and takes 4 x 32, 32.9)
+                const bool wider = p.flat && cost == best && tw > p.TW && (poolable || !d->pool);
+                if (!wider && cost >= best_free && (cost >= best || (d->pool && !poolable))) continue; // improves nothing
                 // LDS need: first with the smallest row pitch, then (the pitch search is the
                 // expensive part) with the pitch this geometry would get
                 const int bn_max = p.limbs == 2 ? 64 : 128;
@@ -389,7 +392,7 @@ static lp_status make_plan_uncached(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt q
                 if (p.flat && (size_t)npixa * d->Cin * 2 > (size_t)kFlatRawBytes) continue;
                 best_free = std::min(best_free, cost);
                 if (d->pool && !poolable) continue;
-                if (cost < best) {
+                if (cost < best || wider) {
                     best = cost;
                     p.RH = rh; p.TW = tw; p.PW = pw; p.PRA = pra; p.NPIXA = npixa;
                     p.tiles_r = tiles_r; p.tiles_c = tiles_c;
@@ -2242,9 +2245,9 @@ static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, 
     a.pool = p.pool;
     if (p.pool && !(a.fast && a.y16 && d->Cout % 4 == 0)) return LP_EUNSUPPORTED;
     // flat-window layers of which only 16-bit codes are wanted: workgroups that run several tiles, as many as the chip holds at
-    // once.  With a tile or less per CU there is nothing to run on with, and setting up is longer: 128 tiles 8.0 : 8.3 us,
-    // 8 tiles 4.24 : 4.53, but 392 tiles 10.96 : 10.70.
-    const bool codes_only = p.flat && a.fast && a.y16 && !y_flags && p.tiles_n == 1 && a.total_work > kCUs && d->Cout % 4 == 0 &&
+    // once.  With about a tile per CU there is nothing to run on with, and setting up is longer: 8 tiles 4.24 : 4.53 us,
+    // 128 tiles 8.0 : 8.3, 288 tiles (7x7 window) 8.5 : 8.8, but 392 tiles 10.96 : 10.70.
+    const bool codes_only = p.flat && a.fast && a.y16 && !y_flags && p.tiles_n == 1 && a.total_work > kCUs * 3 / 2 && d->Cout % 4 == 0 &&
                             a.act.s >= 9 && a.act.s <= 20;
     if (codes_only) {
         const int ncb = d->Cout <= 32 ? 1 : 2, per_cu = ncb * p.ksteps == 4 ? kFlatSlots - 1 : kFlatSlots;

@@ -353,3 +353,25 @@ def test_maxpool_matches_oracle(oracle, N, C, H, W, n):
     assert np.array_equal(yd.cpu().numpy().astype(np.int32).transpose(0, 3, 1, 2), want)
     with pytest.raises(lp.LpError):
         lp.lp_maxpool2x2(xd, yd, N, H + 1, W, C, n)
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 63, 64, 65, 71, 72, 511, 512, 700])
+def test_range_meets_in_one_group_or_eight(oracle, blocks):
+    """Grids around the line between one group of blocks and eight, and around the largest; both kernels, twice in a row (the
+    slot is left zero), the second time behind more queued work than the call watches its result line for."""
+    rng = np.random.default_rng(blocks)
+    x = (rng.standard_normal(blocks * 1024 - 3) * 8.0 ** rng.integers(-2, 3, blocks * 1024 - 3)).astype(np.float32)
+    acc = rng.integers(-(1 << 30), 1 << 30, blocks * 512 - 1) >> rng.integers(0, 30, blocks * 512 - 1)
+    xd, ad = to_dev(x), to_dev(acc)
+    m, lost = oracle.range_float(x, 16)
+    ma, lost_a = oracle.range_acc(acc, 20, True, 16)
+    busy = torch.zeros(1 << 26, device="cuda")
+    for behind in (0, 40):
+        for _ in range(behind):
+            busy.add_(1.0)
+        fmt, got = lp.lp_range(xd, 16)
+        assert fmt.m == m and list(got)[1:] == [int(v) for v in lost][1:]
+        for _ in range(behind):
+            busy.add_(1.0)
+        fmt, got = lp.lp_range_acc(ad, 20, True, 16)
+        assert fmt.m == ma and list(got)[1:] == [int(v) for v in lost_a][1:]

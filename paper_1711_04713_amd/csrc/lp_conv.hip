@@ -2324,22 +2324,18 @@ static lp_status pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, con
     unsigned char *out = (unsigned char *)packed;
     int64_t *corr = (int64_t *)(out + p.corr_offset);
     const int cgrid = p.CoutP; // one wave per output channel
-    if (p.limbs == 2 && p.wl == 2) { // which form the weights of each tile take
-        if (w16) hipLaunchKernelGGL(weight_form_kernel<int16_t>, dim3(p.CoutP / 64), dim3(1024), 0, hs, (const int16_t *)w, corr, d->Cout, RS * d->Cin);
-        else hipLaunchKernelGGL(weight_form_kernel<int8_t>, dim3(p.CoutP / 64), dim3(1024), 0, hs, (const int8_t *)w, corr, d->Cout, RS * d->Cin);
-    }
+    if (w16) hipLaunchKernelGGL(weight_corr_kernel<int16_t>, dim3(cgrid), dim3(64), 0, hs, (const int16_t *)w, corr, d->Cout, p.CoutP, RS * d->Cin, p.limbs, p.wl);
+    else hipLaunchKernelGGL(weight_corr_kernel<int8_t>, dim3(cgrid), dim3(64), 0, hs, (const int8_t *)w, corr, d->Cout, p.CoutP, RS * d->Cin, p.limbs, p.wl);
+    // (8-bit weights always fit the signed form)
+    if (p.limbs == 2 && p.wl == 2 && w16) hipLaunchKernelGGL(weight_form_kernel, dim3(p.CoutP / 64), dim3(64), 0, hs, corr, d->Cout, RS * d->Cin);
     if (p.rows) {
         const int K = RS * d->Cin, rgrid = (p.KHP * p.CoutP * 32 + 255) / 256;
         if (w16) {
             hipLaunchKernelGGL(pack_weights_rows_kernel<int16_t>, dim3(rgrid), dim3(256), 0, hs, (const int16_t *)w, out,
                                d->Cout, d->R, d->S * d->Cin, p.KHR, p.KHP, p.CoutP, corr);
-            hipLaunchKernelGGL(weight_corr_kernel<int16_t>, dim3(cgrid), dim3(64), 0, hs,
-                               (const int16_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         } else {
             hipLaunchKernelGGL(pack_weights_rows_kernel<int8_t>, dim3(rgrid), dim3(256), 0, hs, (const int8_t *)w, out,
                                d->Cout, d->R, d->S * d->Cin, p.KHR, p.KHP, p.CoutP, corr);
-            hipLaunchKernelGGL(weight_corr_kernel<int8_t>, dim3(cgrid), dim3(64), 0, hs,
-                               (const int8_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         }
         return launch_status();
     }
@@ -2348,21 +2344,15 @@ static lp_status pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, con
         if (w16) {
             hipLaunchKernelGGL(pack_weights_flat_kernel<int16_t>, dim3(fgrid), dim3(256), 0, hs,
                                (const int16_t *)w, out, d->Cout, K, p.CoutP, corr);
-            hipLaunchKernelGGL(weight_corr_kernel<int16_t>, dim3(cgrid), dim3(64), 0, hs,
-                               (const int16_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         } else {
             hipLaunchKernelGGL(pack_weights_flat_kernel<int8_t>, dim3(fgrid), dim3(256), 0, hs,
                                (const int8_t *)w, out, d->Cout, K, p.CoutP, corr);
-            hipLaunchKernelGGL(weight_corr_kernel<int8_t>, dim3(cgrid), dim3(64), 0, hs,
-                               (const int8_t *)w, corr, d->Cout, p.CoutP, K, 2, 2);
         }
         return launch_status();
     }
 #define LP_PACK(WT, L, W)                                                                           \
     hipLaunchKernelGGL((pack_weights_kernel<WT, W>), dim3(grid), dim3(256), 0, hs, (const WT *)w, out, \
                        d->Cout, d->Cin, RS, p.nchunks, p.CoutP, total, corr);                          \
-    hipLaunchKernelGGL(weight_corr_kernel<WT>, dim3(cgrid), dim3(64), 0, hs, (const WT *)w, corr,      \
-                       d->Cout, p.CoutP, RS * d->Cin, L, W);                                           \
     if (L == 2)                                                                                        \
     hipLaunchKernelGGL(chunk_weight_sums_kernel<WT>, dim3(p.CoutP, p.nchunks), dim3(64), 0, hs,        \
                        (const WT *)w, (int *)(out + p.wsum_offset), d->Cout, p.CoutP, d->Cin, RS)

@@ -797,10 +797,10 @@ static lp_status fc_pack(int M, int K, int Nout, lp_qfmt qx, lp_qfmt qw, const v
     int64_t *corr = (int64_t *)(out + p.corr_offset);
     const int CoutP = p.n_tiles * FN;
 #define LP_FCPACK(WT, L)                                                                                     \
-    if (L == 2) hipLaunchKernelGGL(weight_form_kernel<WT>, dim3(p.n_tiles), dim3(1024), 0, hs, (const WT *)w, corr, Nout, K); \
+    hipLaunchKernelGGL(weight_corr_kernel<WT>, dim3(CoutP), dim3(64), 0, hs, (const WT *)w, corr, Nout, CoutP, K, L, L); \
+    if (L == 2 && sizeof(WT) == 2) hipLaunchKernelGGL(weight_form_kernel, dim3(p.n_tiles), dim3(64), 0, hs, corr, Nout, K); \
     hipLaunchKernelGGL((fc_pack_weights_kernel<WT, L>), dim3(grid), dim3(256), 0, hs, (const WT *)w, out, Nout, K, \
-                       p.KH, pieces, corr);                                                                  \
-    hipLaunchKernelGGL(weight_corr_kernel<WT>, dim3(CoutP), dim3(64), 0, hs, (const WT *)w, corr, Nout, CoutP, K, L, L)
+                       p.KH, pieces, corr)
     if (p.limbs == 2) {
         if (qw.n > 8) { LP_FCPACK(int16_t, 2); } else { LP_FCPACK(int8_t, 2); }
     } else {

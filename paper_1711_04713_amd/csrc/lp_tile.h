@@ -548,30 +548,9 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
 }
 
 
-// Says in the corrections of a tile of 64 output channels (blockIdx.x, 1024 threads) which form its weights take; w: [Cout][K],
-// 16-byte aligned.  Runs before the packing kernels, which read it there.
-template <typename WT>
-__global__ __launch_bounds__(1024) void weight_form_kernel(const WT *__restrict__ w, int64_t *__restrict__ corr, int Cout, int K)
-{
-    const int c0 = blockIdx.x * 64;
-    const size_t n = (size_t)max(min(64, Cout - c0), 0) * K; // the tile's weights are consecutive
-    int large = 0;
-    if constexpr (sizeof(WT) == 2) {
-        const WT *src = w + (size_t)c0 * K;
-        for (size_t i = threadIdx.x; i < n / 8; i += 1024) {
-            const v8s v = reinterpret_cast<const v8s *>(src)[i];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) large |= v[e] >= 32640;
-        }
-        for (size_t i = n / 8 * 8 + threadIdx.x; i < n; i += 1024) large |= src[i] >= 32640;
-    }
-    large = __syncthreads_or(large);
-    if (threadIdx.x < 64) corr[c0 + threadIdx.x] = large ? 0 : kSignedForm;
-}
-
-// corr[co] = 128 * sum_k w[co][k] (- 16384 * K with two-limb weights of the plain form) for two-limb activations, 0 otherwise:
-// the weight half of the offset correction, computed once when the weights are packed.  One wave per output channel
-// (blockIdx.x = co, 64 threads), lanes striding over K.  Two-limb weights: their form is already there and stays.
+// corr[co] = 128 * sum_k w[co][k] for two-limb activations, 0 otherwise: the weight half of the offset correction, computed
+// once when the weights are packed.  One wave per output channel (blockIdx.x = co, 64 threads), lanes striding over K.
+// Two-limb weights: plus kSignedForm if none of the channel's weights is too large for it (padded channels have none).
 template <typename WT>
 __global__ __launch_bounds__(64) void weight_corr_kernel(const WT *__restrict__ w, int64_t *__restrict__ corr, int Cout,
                                                         int CoutP, int K, int limbs, int wlimbs)
@@ -579,15 +558,27 @@ __global__ __launch_bounds__(64) void weight_corr_kernel(const WT *__restrict__ 
     const int co = blockIdx.x;
     if (co >= CoutP) return;
     long long s = 0;
+    bool large = false;
     if (limbs == 2 && co < Cout)
-        for (int k = threadIdx.x; k < K; k += 64) s += (long long)w[(size_t)co * K + k];
+        for (int k = threadIdx.x; k < K; k += 64) {
+            const int v = (int)w[(size_t)co * K + k];
+            s += v;
+            large |= v >= 32640;
+        }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) s += __shfl_down(s, off, 64);
-    if (threadIdx.x == 0) {
-        const int64_t form = wlimbs == 2 ? corr[co] & kSignedForm : 0;
-        const int64_t v = (limbs == 2 && co < Cout) ? 128 * s - (wlimbs == 2 && !form ? (long long)16384 * K : 0) : 0;
-        corr[co] = v | form;
-    }
+    const int64_t form = wlimbs == 2 && !__any(large) ? kSignedForm : 0;
+    if (threadIdx.x == 0) corr[co] = 128 * s | form;
+}
+
+// A tile of 64 channels (blockIdx.x, 64 threads) takes the signed form if all of them can; else the corrections get the
+// plain form's - 16384 * K.  Between weight_corr_kernel and the packing kernel, which reads the form there.
+static __global__ __launch_bounds__(64) void weight_form_kernel(int64_t *__restrict__ corr, int Cout, int K)
+{
+    const int co = blockIdx.x * 64 + threadIdx.x;
+    const int64_t v = corr[co];
+    if (__all((v & kSignedForm) != 0)) return;
+    corr[co] = co < Cout ? (v & ~kSignedForm) - (int64_t)16384 * K : 0;
 }
 
 // Adds n per-workgroup counts (zeros at partials[0..n), clipped values at partials[n..2n)) to the

@@ -63,6 +63,16 @@ static int count_grid(size_t groups, int threads)
     return (int)std::min<size_t>(std::max<size_t>((groups + threads - 1) / threads, 1), kCountBlocks);
 }
 
+// A tensor that fits the memory-side cache (256 MB) is loaded plainly: what lp_range has just read, or a convolution has just
+// written, is still there (lp_range + lp_quantize of 25.7 M elements 72.0 us with nontemporal loads, 68.7 with plain ones;
+// lp_act of 6.4 M accumulators 15.6 : 14.4).  A larger one cannot be, and would only push out what others left.
+static bool read_once(size_t bytes) { return bytes > ((size_t)192 << 20); }
+template <typename V>
+__device__ __forceinline__ V load16(const V *p, bool once)
+{
+    return once ? __builtin_nontemporal_load(p) : *p;
+}
+
 // ------------------------------------------------------------------ Philox4x32-10
 // Counter-based generator of Salmon, Moraes, Dror, Shaw (SC'11): ten rounds of two
 // 32x32->64 multiplies and xors, key bumped by the Weyl constants each round.  One block gives four
@@ -124,7 +134,7 @@ template <typename OutT, int MODE, bool COUNT, int THREADS>
 __global__ __launch_bounds__(THREADS) void quantize_kernel(const float *__restrict__ x,
                                                            OutT *__restrict__ y, size_t count,
                                                            float scale, float lo, float hi,
-                                                           uint64_t seed,
+                                                           uint64_t seed, bool once,
                                                            unsigned long long *zero_count,
                                                            unsigned long long *sat_count)
 {
@@ -166,11 +176,9 @@ __global__ __launch_bounds__(THREADS) void quantize_kernel(const float *__restri
             }
         }
     };
-    // (plain loads, here and in the kernels below: a tensor whose range was just taken is still in the memory-side cache.
-    // lp_range + lp_quantize of 25.7 M elements 72.0 us with nontemporal ones, 68.7 with plain ones; lp_act of 6.4 M 15.6 : 14.4)
     auto load = [&](size_t g, v4f &a, v4f &b) __attribute__((always_inline)) {
-        a = reinterpret_cast<const v4f *>(x)[2 * g];
-        b = reinterpret_cast<const v4f *>(x)[2 * g + 1];
+        a = load16(reinterpret_cast<const v4f *>(x) + 2 * g, once);
+        b = load16(reinterpret_cast<const v4f *>(x) + 2 * g + 1, once);
     };
     // The condition of the unrolled loop is the same for a whole wave (its last lane's), and in the
     // loop after it lane 0 has the smallest index: lane 0 runs every iteration any lane of its wave
@@ -215,14 +223,14 @@ static void launch_quantize(const float *x, void *y, size_t count, float scale, 
 {
     if ((zc || sc) && count_small(count / 8))
         hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true, kThreads>), dim3(count_grid(count / 8, kThreads)), dim3(kThreads), 0,
-                           st, x, (OutT *)y, count, scale, lo, hi, seed, (unsigned long long *)zc, (unsigned long long *)sc);
+                           st, x, (OutT *)y, count, scale, lo, hi, seed, read_once(count * 4), (unsigned long long *)zc, (unsigned long long *)sc);
     else if (zc || sc)
         hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true, kCountThreads>), dim3(count_grid(count / 8, kCountThreads)),
-                           dim3(kCountThreads), 0, st, x, (OutT *)y, count, scale, lo, hi, seed, (unsigned long long *)zc,
+                           dim3(kCountThreads), 0, st, x, (OutT *)y, count, scale, lo, hi, seed, read_once(count * 4), (unsigned long long *)zc,
                            (unsigned long long *)sc);
     else
         hipLaunchKernelGGL((quantize_kernel<OutT, MODE, false, kThreads>), dim3(grid_for(count / 8)), dim3(kThreads), 0, st, x,
-                           (OutT *)y, count, scale, lo, hi, seed, nullptr, nullptr);
+                           (OutT *)y, count, scale, lo, hi, seed, read_once(count * 4), nullptr, nullptr);
 }
 
 // --------------------------------------------------------------------------- range
@@ -333,7 +341,7 @@ static int range_grid(size_t groups)
     return (int)std::min<size_t>(std::max<size_t>(blocks, 1), 256 * 2); // grid-stride beyond two blocks per CU
 }
 
-__global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__restrict__ x, size_t count, int slot,
+__global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__restrict__ x, size_t count, bool once, int slot,
                                                             unsigned long long *host)
 {
     __shared__ unsigned h[kBuckets * kThreads];
@@ -347,7 +355,7 @@ __global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__rest
     for (; g + (U - 1) * stride < groups; g += U * stride) {
         v4f a[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = reinterpret_cast<const v4f *>(x)[g + u * stride];
+        for (int u = 0; u < U; ++u) a[u] = load16(reinterpret_cast<const v4f *>(x) + g + u * stride, once);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             count_in(h, bucket_f32(a[u].x));
@@ -357,7 +365,7 @@ __global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__rest
         }
     }
     for (; g < groups; g += stride) {
-        const v4f a = reinterpret_cast<const v4f *>(x)[g];
+        const v4f a = load16(reinterpret_cast<const v4f *>(x) + g, once);
         count_in(h, bucket_f32(a.x));
         count_in(h, bucket_f32(a.y));
         count_in(h, bucket_f32(a.z));
@@ -371,7 +379,7 @@ __global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__rest
 }
 
 __global__ __launch_bounds__(kThreads) void range_i64_kernel(const int64_t *__restrict__ acc,
-                                                            size_t count, int f_acc, int relu, int slot,
+                                                            size_t count, int f_acc, int relu, bool once, int slot,
                                                             unsigned long long *host)
 {
     __shared__ unsigned h[kBuckets * kThreads];
@@ -388,11 +396,11 @@ __global__ __launch_bounds__(kThreads) void range_i64_kernel(const int64_t *__re
     for (; g + (U - 1) * stride < groups; g += U * stride) {
         v4i a[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = reinterpret_cast<const v4i *>(acc)[g + u * stride];
+        for (int u = 0; u < U; ++u) a[u] = load16(reinterpret_cast<const v4i *>(acc) + g + u * stride, once);
 #pragma unroll
         for (int u = 0; u < U; ++u) take(a[u]);
     }
-    for (; g < groups; g += stride) take(reinterpret_cast<const v4i *>(acc)[g]);
+    for (; g < groups; g += stride) take(load16(reinterpret_cast<const v4i *>(acc) + g, once));
     if (blockIdx.x == 0 && threadIdx.x == 0 && (count & 1)) count_in(h, bucket_i64(acc[count - 1], f_acc, relu));
     flush_hist(h, slot, host);
 }
@@ -524,7 +532,7 @@ __device__ __forceinline__ int act_one_stochastic(int64_t v, const ActParams &p,
 template <typename OutT, bool STOCH, bool COUNT, int THREADS>
 __global__ __launch_bounds__(THREADS) void act_kernel(const int64_t *__restrict__ acc,
                                                       OutT *__restrict__ y, size_t count,
-                                                      ActParams p, uint64_t seed,
+                                                      ActParams p, uint64_t seed, bool once,
                                                       unsigned long long *zero_count,
                                                       unsigned long long *sat_count)
 {
@@ -547,7 +555,7 @@ __global__ __launch_bounds__(THREADS) void act_kernel(const int64_t *__restrict_
         v4i a[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            a[j] = reinterpret_cast<const v4i *>(acc)[pair0 + j * THREADS];
+            a[j] = load16(reinterpret_cast<const v4i *>(acc) + pair0 + j * THREADS, once);
         // Elements 2 * pair and 2 * pair + 1 draw two neighbouring words of block pair / 2, which a
         // lane shares with its neighbour (lanes 2k and 2k + 1 hold pairs 2m and 2m + 1 in every
         // row).  The even lane computes the blocks of rows 0 and 2, the odd lane those of rows 1
@@ -692,7 +700,7 @@ extern "C" lp_status lp_range(const float *x_dev, size_t count, int n, double lo
     hipStream_t st = as_stream(stream);
     clear_stale_error();
     return range_call(count, n, loss_threshold, out_host, lost_host, st, [&](int slot, unsigned long long *line) {
-        hipLaunchKernelGGL(range_f32_kernel, dim3(range_grid(count / 4)), dim3(kThreads), 0, st, x_dev, count, slot, line);
+        hipLaunchKernelGGL(range_f32_kernel, dim3(range_grid(count / 4)), dim3(kThreads), 0, st, x_dev, count, read_once(count * 4), slot, line);
     });
 }
 
@@ -708,7 +716,7 @@ extern "C" lp_status lp_range_acc(const int64_t *acc_dev, size_t count, int f_ac
     clear_stale_error();
     return range_call(count, n, loss_threshold, out_host, lost_host, st, [&](int slot, unsigned long long *line) {
         hipLaunchKernelGGL(range_i64_kernel, dim3(range_grid(count / 2)), dim3(kThreads), 0, st, acc_dev, count, f_acc,
-                           relu ? 1 : 0, slot, line);
+                           relu ? 1 : 0, read_once(count * 8), slot, line);
     });
 }
 
@@ -755,15 +763,15 @@ static lp_status act_launch(const int64_t *acc_dev, size_t count, int f_acc, lp_
 #define LP_A(T, STOCH)                                                                                        \
     if (counting && count_small(count / 8))                                                                   \
         hipLaunchKernelGGL((act_kernel<T, STOCH, true, kThreads>), dim3(count_grid(count / 8, kThreads)), dim3(kThreads), 0, \
-                           st, acc_dev, (T *)y_codes_dev, count, p, seed, (unsigned long long *)zero_count_dev, \
+                           st, acc_dev, (T *)y_codes_dev, count, p, seed, read_once(count * 8), (unsigned long long *)zero_count_dev, \
                            (unsigned long long *)sat_count_dev);                                              \
     else if (counting)                                                                                        \
         hipLaunchKernelGGL((act_kernel<T, STOCH, true, kCountThreads>), dim3(count_grid(count / 8, kCountThreads)), \
-                           dim3(kCountThreads), 0, st, acc_dev, (T *)y_codes_dev, count, p, seed,             \
+                           dim3(kCountThreads), 0, st, acc_dev, (T *)y_codes_dev, count, p, seed, read_once(count * 8), \
                            (unsigned long long *)zero_count_dev, (unsigned long long *)sat_count_dev);        \
     else                                                                                                      \
         hipLaunchKernelGGL((act_kernel<T, STOCH, false, kThreads>), dim3(grid_for(count / 8)), dim3(kThreads), 0, st, acc_dev, \
-                           (T *)y_codes_dev, count, p, seed, nullptr, nullptr)
+                           (T *)y_codes_dev, count, p, seed, read_once(count * 8), nullptr, nullptr)
     if (r == LP_ROUND_STOCHASTIC) {
         if (qy.n > 8) {
             LP_A(int16_t, true);

@@ -589,7 +589,6 @@ __global__ __launch_bounds__(64 * few_waves<RB>()) void fc_few_rows_kernel(const
         const int col = col0 + tid;
         colterm[tid] = col < a.Cout ? (a.corr[col] & ~kSignedForm) + bias_term(a, col) : 0;
     }
-    const bool summing = LIMBS == 2 && needs_code_sums(a, nt);
     constexpr int KHB = LIMBS * 2 * FRAG; // weight bytes of one K half of a 64-column tile
     const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<unsigned char *>(a.wp) + (size_t)nt * f.wslab, 0, (int)f.wslab, 0x00020000);
@@ -654,6 +653,7 @@ __global__ __launch_bounds__(64 * few_waves<RB>()) void fc_few_rows_kernel(const
     int sum[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) sum[rb] = 0;
+    bool summing = false; // the weights are in the plain form: see below
     auto multiply = [&](int kh, int d) __attribute__((always_inline)) {
         const v4i (&wr)[LIMBS] = w[d];
         v4i (&xr)[RB][XL] = x[d];
@@ -691,6 +691,9 @@ __global__ __launch_bounds__(64 * few_waves<RB>()) void fc_few_rows_kernel(const
     };
 #pragma unroll
     for (int d = 0; d < D; ++d) request(wave + d * WAVES, d);
+    // asked for behind the first weights and codes: in front of them its way from memory came first, 1.5 us a call
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (LIMBS == 2) summing = needs_code_sums(a, nt);
     for (int kh = wave; kh < f.KH; kh += D * WAVES) {
 #pragma unroll
         for (int d = 0; d < D; ++d) { // (halves past the last one multiply zero weights)

@@ -23,8 +23,7 @@
  *     weights [Nout][K]: the contraction index is always contiguous.
  *   - `stream` is a hipStream_t passed as void* (NULL = default stream).  Calls
  *     only enqueue work and return, except lp_range / lp_range_acc, which wait
- *     for their result, and with it for everything the stream was given before,
- *     because they return it on the host.
+ *     for the stream because they return a result on the host.
  *   - Counters (zero_count_dev, sat_count_dev) are uint64 in device memory and
  *     are ADDED to: the caller clears them when a fresh count is wanted.
  *   - Every argument is validated before anything is launched; a call that
@@ -85,8 +84,7 @@ const char *lp_status_string(lp_status s);
  * of scratch: required, but neither read nor written at present (the histogram
  * lives in a slot of the library's own).  At most 32 range calls of a process
  * are in flight at once; further threads wait for one to return.
- * Returns when the result is on the host: everything enqueued on the stream before
- * has then finished.  count == 0 yields m = 1 (and synchronises the stream).
+ * Synchronises the stream.  count == 0 yields m = 1.
  */
 lp_status lp_range(const float *x_dev, size_t count, int n, double loss_threshold,
                    lp_qfmt *out_host, uint64_t *lost_host, uint64_t *workspace_dev, void *stream);

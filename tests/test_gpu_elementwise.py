@@ -358,7 +358,7 @@ def test_maxpool_matches_oracle(oracle, N, C, H, W, n):
 @pytest.mark.parametrize("blocks", [1, 2, 63, 64, 65, 71, 72, 511, 512, 700])
 def test_range_meets_in_one_group_or_eight(oracle, blocks):
     """Grids around the line between one group of blocks and eight, and around the largest; both kernels, twice in a row (the
-    slot is left zero), the second time behind more queued work than the call watches its result line for."""
+    slot is left zero), the second time behind queued work."""
     rng = np.random.default_rng(blocks)
     x = (rng.standard_normal(blocks * 1024 - 3) * 8.0 ** rng.integers(-2, 3, blocks * 1024 - 3)).astype(np.float32)
     acc = rng.integers(-(1 << 30), 1 << 30, blocks * 512 - 1) >> rng.integers(0, 30, blocks * 512 - 1)

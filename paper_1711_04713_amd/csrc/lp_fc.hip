@@ -5,6 +5,7 @@
 //
 // The limb algebra is that of the convolution kernels: a 16-bit code is a = 256*ah + al + 128 with
 // two int8 limbs, and sum a*b = 2^16*HH + 2^8*(HL+LH) + LL + 128*sum(a) + 128*sum(b) - 16384*K.
+// (A tile of columns whose weights take a signed low limb owes 128*sum(b) alone: see weight_limbs.)
 //
 // Shape of the work.  An inner product streams a large weight matrix (205 MB for 25088 -> 4096)
 // against few input rows, so every weight byte should leave HBM once, and the matrix pipe must

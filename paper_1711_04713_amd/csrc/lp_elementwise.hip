@@ -61,14 +61,19 @@ static int count_grid(size_t groups, int threads)
     return (int)std::min<size_t>(std::max<size_t>((groups + threads - 1) / threads, 1), kCountBlocks);
 }
 
-// A tensor that fits the memory-side cache (256 MB) is loaded plainly: what lp_range has just read, or a convolution has just
-// written, is still there (lp_range + lp_quantize of 25.7 M elements 72.0 us with nontemporal loads, 68.7 with plain ones;
-// lp_act of 6.4 M accumulators 15.6 : 14.4).  A larger one cannot be, and would only push out what others left.
-static bool read_once(size_t bytes) { return bytes > ((size_t)192 << 20); }
-template <typename V>
-__device__ __forceinline__ V load16(const V *p, bool once)
+// What lp_range has just read, or another kernel has just written, is still in the memory-side cache (256 MB) if it and
+// the codes made of it fit: plain loads.  Larger tensors cannot be there, and would only push out what others left:
+// nontemporal ones.  As called, us, plain : nontemporal: lp_range + lp_quantize to 16 bits of 96 MB of floats 59.4 : 63.4,
+// 160 MB 84.6 : 88.6, 176 MB 101.3 : 94.7, 320 MB 174.9 : 152.0, 512 MB 262 : 229; to 8 bits of 176 MB 84.7 : 90.7, 240 MB
+// 118.7 : 115.5.  Accumulators: lp_range_acc + lp_act of 96 MB 57.6 : 60.5, 160 MB 83.3 : 83.4, 320 MB 159.9 : 138.9; behind the
+// kernel that wrote them, lp_act of 96 MB 52.2 : 55.1, 152 MB 82.5 : 81.8, 208 MB 118.6 : 108.5.
+static bool floats_once(size_t count, int n) { return count * (n > 8 ? 6 : 5) > ((size_t)256 << 20); }
+static bool accumulators_once(size_t count) { return count * 8 > ((size_t)160 << 20); }
+template <bool ONCE, typename V> // (a constant: of two loads behind a branch the compiler makes one without the hint)
+__device__ __forceinline__ V load16(const V *p)
 {
-    return once ? __builtin_nontemporal_load(p) : *p;
+    if constexpr (ONCE) return __builtin_nontemporal_load(p);
+    else return *p;
 }
 
 // ------------------------------------------------------------------ Philox4x32-10
@@ -128,11 +133,11 @@ __device__ __forceinline__ int quantize_one(float x, float scale, float lo, floa
     return (int)r;
 }
 
-template <typename OutT, int MODE, bool COUNT, int THREADS>
+template <typename OutT, int MODE, bool COUNT, int THREADS, bool ONCE>
 __global__ __launch_bounds__(THREADS) void quantize_kernel(const float *__restrict__ x,
                                                            OutT *__restrict__ y, size_t count,
                                                            float scale, float lo, float hi,
-                                                           uint64_t seed, bool once,
+                                                           uint64_t seed,
                                                            unsigned long long *zero_count,
                                                            unsigned long long *sat_count)
 {
@@ -175,8 +180,8 @@ __global__ __launch_bounds__(THREADS) void quantize_kernel(const float *__restri
         }
     };
     auto load = [&](size_t g, v4f &a, v4f &b) __attribute__((always_inline)) {
-        a = load16(reinterpret_cast<const v4f *>(x) + 2 * g, once);
-        b = load16(reinterpret_cast<const v4f *>(x) + 2 * g + 1, once);
+        a = load16<ONCE>(reinterpret_cast<const v4f *>(x) + 2 * g);
+        b = load16<ONCE>(reinterpret_cast<const v4f *>(x) + 2 * g + 1);
     };
     // The condition of the unrolled loop is the same for a whole wave (its last lane's), and in the
     // loop after it lane 0 has the smallest index: lane 0 runs every iteration any lane of its wave
@@ -219,16 +224,19 @@ template <typename OutT, int MODE>
 static void launch_quantize(const float *x, void *y, size_t count, float scale, float lo, float hi,
                             uint64_t seed, uint64_t *zc, uint64_t *sc, hipStream_t st)
 {
-    if ((zc || sc) && count_small(count / 8))
-        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true, kThreads>), dim3(count_grid(count / 8, kThreads)), dim3(kThreads), 0,
-                           st, x, (OutT *)y, count, scale, lo, hi, seed, read_once(count * 4), (unsigned long long *)zc, (unsigned long long *)sc);
-    else if (zc || sc)
-        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, true, kCountThreads>), dim3(count_grid(count / 8, kCountThreads)),
-                           dim3(kCountThreads), 0, st, x, (OutT *)y, count, scale, lo, hi, seed, read_once(count * 4), (unsigned long long *)zc,
+    auto launch = [&](auto kernel, int grid, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, x, (OutT *)y, count, scale, lo, hi, seed, (unsigned long long *)zc,
                            (unsigned long long *)sc);
+    };
+    const size_t groups = count / 8;
+    const bool once = floats_once(count, 8 * (int)sizeof(OutT));
+    if ((zc || sc) && count_small(groups)) launch(quantize_kernel<OutT, MODE, true, kThreads, false>, count_grid(groups, kThreads), kThreads);
+    else if (zc || sc)
+        launch(once ? quantize_kernel<OutT, MODE, true, kCountThreads, true> : quantize_kernel<OutT, MODE, true, kCountThreads, false>,
+               count_grid(groups, kCountThreads), kCountThreads);
     else
-        hipLaunchKernelGGL((quantize_kernel<OutT, MODE, false, kThreads>), dim3(grid_for(count / 8)), dim3(kThreads), 0, st, x,
-                           (OutT *)y, count, scale, lo, hi, seed, read_once(count * 4), nullptr, nullptr);
+        launch(once ? quantize_kernel<OutT, MODE, false, kThreads, true> : quantize_kernel<OutT, MODE, false, kThreads, false>,
+               grid_for(groups), kThreads);
 }
 
 // --------------------------------------------------------------------------- range
@@ -339,7 +347,8 @@ static int range_grid(size_t groups)
     return (int)std::min<size_t>(std::max<size_t>(blocks, 1), 256 * 2); // grid-stride beyond two blocks per CU
 }
 
-__global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__restrict__ x, size_t count, bool once, int slot,
+template <bool ONCE>
+__global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__restrict__ x, size_t count, int slot,
                                                             unsigned long long *host)
 {
     __shared__ unsigned h[kBuckets * kThreads];
@@ -353,7 +362,7 @@ __global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__rest
     for (; g + (U - 1) * stride < groups; g += U * stride) {
         v4f a[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = load16(reinterpret_cast<const v4f *>(x) + g + u * stride, once);
+        for (int u = 0; u < U; ++u) a[u] = load16<ONCE>(reinterpret_cast<const v4f *>(x) + g + u * stride);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             count_in(h, bucket_f32(a[u].x));
@@ -363,7 +372,7 @@ __global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__rest
         }
     }
     for (; g < groups; g += stride) {
-        const v4f a = load16(reinterpret_cast<const v4f *>(x) + g, once);
+        const v4f a = load16<ONCE>(reinterpret_cast<const v4f *>(x) + g);
         count_in(h, bucket_f32(a.x));
         count_in(h, bucket_f32(a.y));
         count_in(h, bucket_f32(a.z));
@@ -376,8 +385,9 @@ __global__ __launch_bounds__(kThreads) void range_f32_kernel(const float *__rest
     flush_hist(h, slot, host);
 }
 
+template <bool ONCE>
 __global__ __launch_bounds__(kThreads) void range_i64_kernel(const int64_t *__restrict__ acc,
-                                                            size_t count, int f_acc, int relu, bool once, int slot,
+                                                            size_t count, int f_acc, int relu, int slot,
                                                             unsigned long long *host)
 {
     __shared__ unsigned h[kBuckets * kThreads];
@@ -394,11 +404,11 @@ __global__ __launch_bounds__(kThreads) void range_i64_kernel(const int64_t *__re
     for (; g + (U - 1) * stride < groups; g += U * stride) {
         v4i a[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = load16(reinterpret_cast<const v4i *>(acc) + g + u * stride, once);
+        for (int u = 0; u < U; ++u) a[u] = load16<ONCE>(reinterpret_cast<const v4i *>(acc) + g + u * stride);
 #pragma unroll
         for (int u = 0; u < U; ++u) take(a[u]);
     }
-    for (; g < groups; g += stride) take(load16(reinterpret_cast<const v4i *>(acc) + g, once));
+    for (; g < groups; g += stride) take(load16<ONCE>(reinterpret_cast<const v4i *>(acc) + g));
     if (blockIdx.x == 0 && threadIdx.x == 0 && (count & 1)) count_in(h, bucket_i64(acc[count - 1], f_acc, relu));
     flush_hist(h, slot, host);
 }
@@ -513,10 +523,10 @@ __device__ __forceinline__ int act_one_stochastic(int64_t v, const ActParams &p,
     return (int)r;
 }
 
-template <typename OutT, bool STOCH, bool COUNT, int THREADS>
+template <typename OutT, bool STOCH, bool COUNT, int THREADS, bool ONCE>
 __global__ __launch_bounds__(THREADS) void act_kernel(const int64_t *__restrict__ acc,
                                                       OutT *__restrict__ y, size_t count,
-                                                      ActParams p, uint64_t seed, bool once,
+                                                      ActParams p, uint64_t seed,
                                                       unsigned long long *zero_count,
                                                       unsigned long long *sat_count)
 {
@@ -539,7 +549,7 @@ __global__ __launch_bounds__(THREADS) void act_kernel(const int64_t *__restrict_
         v4i a[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            a[j] = load16(reinterpret_cast<const v4i *>(acc) + pair0 + j * THREADS, once);
+            a[j] = load16<ONCE>(reinterpret_cast<const v4i *>(acc) + pair0 + j * THREADS);
         // Elements 2 * pair and 2 * pair + 1 draw two neighbouring words of block pair / 2, which a
         // lane shares with its neighbour (lanes 2k and 2k + 1 hold pairs 2m and 2m + 1 in every
         // row).  The even lane computes the blocks of rows 0 and 2, the odd lane those of rows 1
@@ -684,7 +694,8 @@ extern "C" lp_status lp_range(const float *x_dev, size_t count, int n, double lo
     hipStream_t st = as_stream(stream);
     clear_stale_error();
     return range_call(count, n, loss_threshold, out_host, lost_host, st, [&](int slot, unsigned long long *line) {
-        hipLaunchKernelGGL(range_f32_kernel, dim3(range_grid(count / 4)), dim3(kThreads), 0, st, x_dev, count, read_once(count * 4), slot, line);
+        hipLaunchKernelGGL(floats_once(count, n) ? range_f32_kernel<true> : range_f32_kernel<false>, dim3(range_grid(count / 4)), dim3(kThreads), 0,
+                           st, x_dev, count, slot, line);
     });
 }
 
@@ -699,8 +710,8 @@ extern "C" lp_status lp_range_acc(const int64_t *acc_dev, size_t count, int f_ac
     hipStream_t st = as_stream(stream);
     clear_stale_error();
     return range_call(count, n, loss_threshold, out_host, lost_host, st, [&](int slot, unsigned long long *line) {
-        hipLaunchKernelGGL(range_i64_kernel, dim3(range_grid(count / 2)), dim3(kThreads), 0, st, acc_dev, count, f_acc,
-                           relu ? 1 : 0, read_once(count * 8), slot, line);
+        hipLaunchKernelGGL(accumulators_once(count) ? range_i64_kernel<true> : range_i64_kernel<false>, dim3(range_grid(count / 2)), dim3(kThreads), 0,
+                           st, acc_dev, count, f_acc, relu ? 1 : 0, slot, line);
     });
 }
 
@@ -743,19 +754,21 @@ static lp_status act_launch(const int64_t *acc_dev, size_t count, int f_acc, lp_
     clear_stale_error();
     const ActParams p = make_act_params(f_acc, qy, relu, r);
     // one trip of the kernel's loop per block, up to the cap
-    const bool counting = zero_count_dev || sat_count_dev;
-#define LP_A(T, STOCH)                                                                                        \
-    if (counting && count_small(count / 8))                                                                   \
-        hipLaunchKernelGGL((act_kernel<T, STOCH, true, kThreads>), dim3(count_grid(count / 8, kThreads)), dim3(kThreads), 0, \
-                           st, acc_dev, (T *)y_codes_dev, count, p, seed, read_once(count * 8), (unsigned long long *)zero_count_dev, \
-                           (unsigned long long *)sat_count_dev);                                              \
-    else if (counting)                                                                                        \
-        hipLaunchKernelGGL((act_kernel<T, STOCH, true, kCountThreads>), dim3(count_grid(count / 8, kCountThreads)), \
-                           dim3(kCountThreads), 0, st, acc_dev, (T *)y_codes_dev, count, p, seed, read_once(count * 8), \
-                           (unsigned long long *)zero_count_dev, (unsigned long long *)sat_count_dev);        \
-    else                                                                                                      \
-        hipLaunchKernelGGL((act_kernel<T, STOCH, false, kThreads>), dim3(grid_for(count / 8)), dim3(kThreads), 0, st, acc_dev, \
-                           (T *)y_codes_dev, count, p, seed, read_once(count * 8), nullptr, nullptr)
+    const size_t groups = count / 8;
+    const bool counting = zero_count_dev || sat_count_dev, once = accumulators_once(count);
+    auto launch = [&](auto kernel, int grid, int threads, auto *y) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, acc_dev, y, count, p, seed, (unsigned long long *)zero_count_dev,
+                           (unsigned long long *)sat_count_dev);
+    };
+#define LP_A(T, STOCH)                                                                                          \
+    if (counting && count_small(groups))                                                                        \
+        launch(act_kernel<T, STOCH, true, kThreads, false>, count_grid(groups, kThreads), kThreads, (T *)y_codes_dev); \
+    else if (counting)                                                                                          \
+        launch(once ? act_kernel<T, STOCH, true, kCountThreads, true> : act_kernel<T, STOCH, true, kCountThreads, false>, \
+               count_grid(groups, kCountThreads), kCountThreads, (T *)y_codes_dev);                             \
+    else                                                                                                        \
+        launch(once ? act_kernel<T, STOCH, false, kThreads, true> : act_kernel<T, STOCH, false, kThreads, false>, grid_for(groups), kThreads, \
+               (T *)y_codes_dev)
     if (r == LP_ROUND_STOCHASTIC) {
         if (qy.n > 8) {
             LP_A(int16_t, true);

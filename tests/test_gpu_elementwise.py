@@ -375,3 +375,49 @@ def test_range_meets_in_one_group_or_eight(oracle, blocks):
             busy.add_(1.0)
         fmt, got = lp.lp_range_acc(ad, 20, True, 16)
         assert fmt.m == ma and list(got)[1:] == [int(v) for v in lost_a][1:]
+
+
+@pytest.mark.parametrize("n,count", [(16, (256 << 20) // 6 + 1), (16, (256 << 20) // 6), (8, (256 << 20) // 5 + 3)])
+def test_floats_beyond_the_memory_side_cache(oracle, n, count):
+    """Both sides of the line from which floats are loaded nontemporally: codes, counts and range against the oracle; a prefix,
+    which lies on the other side, draws the same random words."""
+    torch.manual_seed(count)
+    x = torch.randn(count, device="cuda") * 3.0
+    xh = x.cpu().numpy()
+    m, lost = oracle.range_float(xh, n)
+    fmt, got = lp.lp_range(x, n)
+    assert fmt.m == m and list(got)[1:] == [int(v) for v in lost][1:]
+    q = (n, 3, n - 3)                                     # clips
+    for counters in (True, False):
+        codes, zeros, sats = quantize(xh, q, counters=counters)
+        want, want_zeros, want_sats = oracle.quantize(xh, *q)
+        assert np.array_equal(codes, want)
+        assert not counters or (zeros, sats) == (want_zeros, want_sats)
+        whole, part = (torch.empty(c, dtype=code_torch_dtype(n), device="cuda") for c in (count, 1 << 20))
+        z = [counter() for _ in range(2)]
+        for out, zc in ((whole, z[0]), (part, z[1])):
+            lp.lp_quantize(x[: out.numel()], out, q, lp.LP_ROUND_STOCHASTIC, seed=7, zero_count=zc if counters else None)
+        assert torch.equal(whole[: 1 << 20], part)
+        assert not counters or int(z[0].item()) == int((whole == 0).sum().item())
+
+
+@pytest.mark.parametrize("n,count", [(16, (160 << 20) // 8 + 1), (16, (160 << 20) // 8), (8, (160 << 20) // 8 + 7)])
+def test_accumulators_beyond_the_memory_side_cache(oracle, n, count):
+    torch.manual_seed(count)
+    acc = torch.randint(-(1 << 31), 1 << 31, (count,), device="cuda") >> torch.randint(0, 24, (count,), device="cuda")
+    ah, f_acc, q = acc.cpu().numpy(), 20, (n, 6, n - 6)
+    m, lost = oracle.range_acc(ah, f_acc, True, n)
+    fmt, got = lp.lp_range_acc(acc, f_acc, True, n)
+    assert fmt.m == m and list(got)[1:] == [int(v) for v in lost][1:]
+    want, zeros, sats = oracle.act(ah, f_acc, *q, True, oracle.ROUND_AWAY, with_sat=True)
+    for counters in (True, False):
+        y = torch.empty(count, dtype=code_torch_dtype(n), device="cuda")
+        z, s = counter(), counter()
+        kw = dict(zero_count=z, sat_count=s) if counters else {}
+        lp.lp_act(acc, f_acc, q, True, y, **kw)
+        assert np.array_equal(y.cpu().numpy().astype(np.int32), want)
+        assert not counters or (int(z.item()), int(s.item())) == (zeros, sats)
+        part = torch.empty(1 << 20, dtype=code_torch_dtype(n), device="cuda")
+        lp.lp_act_stochastic(acc, f_acc, q, True, 7, y, **kw)
+        lp.lp_act_stochastic(acc[: 1 << 20], f_acc, q, True, 7, part)
+        assert torch.equal(y[: 1 << 20], part)

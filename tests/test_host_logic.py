@@ -6,6 +6,7 @@ No GPU compute is called."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -294,3 +295,26 @@ def test_wide_form_is_taken_where_it_wins(shape, R, wide):
     N, H, W, Cin, Cout = shape
     info = lp.lp_conv_plan_info(lp.ConvDesc(N, H, W, Cin, Cout, R, R, 1, R // 2), Q16, W16)
     assert (info["lds_bytes"] > 65536) == wide and (wide or info["split"] > 1)
+
+
+def test_large_tensors_are_loaded_nontemporally():
+    """The streaming kernels' last template argument says that a tensor is too large for the memory-side cache.  The hint
+    has to survive the compiler: behind a branch on a run-time value two loads became one without it."""
+    from paper_1711_04713_amd import build
+
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc here")
+    flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
+    asm = subprocess.run([hipcc] + flags + ["--offload-device-only", "-S", os.path.join(build.CSRC, "lp_elementwise.hip"), "-o", "-"],
+                         stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True, check=True).stdout
+    seen = {}
+    for name, body in re.findall(r"^(_ZN2lp\w+):(.*?)s_endpgm", asm, flags=re.M | re.S):
+        m = re.match(r"_ZN2lp\d+(quantize|range_f32|range_i64|act)_kernelI\w*?Lb([01])EE?Ev", name)
+        if not m:
+            continue
+        wide = re.findall(r"global_load_dwordx4 .*", body)
+        assert wide, name
+        assert all(line.rstrip().endswith(" nt") == (m[2] == "1") for line in wide), name
+        seen.setdefault(m[1], set()).add(m[2])
+    assert seen == {k: {"0", "1"} for k in ("quantize", "range_f32", "range_i64", "act")}

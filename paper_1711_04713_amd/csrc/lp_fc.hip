@@ -670,15 +670,19 @@ __global__ __launch_bounds__(64 * few_waves<RB>()) void fc_few_rows_kernel(const
                     h[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x07050301u);
                     l[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x06040200u) ^ 0x80808080u;
                 }
-                if (summing) { // (uniform)
-                    const int nv = f.K - (kh * 32 + kg * 16);
-                    const bool ragged = (kh + 1) * 32 > f.K; // what follows the row's end meets zero weights but is no part of its sum
+                if (summing) { // (uniform; constant ones, and masks in the ragged half only: built for every half they cost a row through
+                               // 4096 -> 1000 2.1 of 13.0 us)
+                    if ((kh + 1) * 32 > f.K) { // what follows the row's end meets zero weights but is no part of its sum
+                        const int nv = f.K - (kh * 32 + kg * 16);
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        const int m = ragged ? min(max(nv - 2 * q, 0), 2) : 2;
-                        const v2s ones = {(short)(m >= 1), (short)(m == 2)};
-                        sum[rb] = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[q]), ones, sum[rb], false);
+                        for (int q = 0; q < 8; ++q) {
+                            const int m = min(max(nv - 2 * q, 0), 2);
+                            pr[q] &= m == 2 ? 0xffffffffu : m == 1 ? 0xffffu : 0u;
+                        }
                     }
+                    const v2s ones = {1, 1};
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) sum[rb] = __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, pr[q]), ones, sum[rb], false);
                 }
                 const v4i xh = {(int)h[0], (int)h[1], (int)h[2], (int)h[3]}, xl = {(int)l[0], (int)l[1], (int)l[2], (int)l[3]};
                 acc[rb][0] = mfma_i8(wr[0], xh, acc[rb][0]);

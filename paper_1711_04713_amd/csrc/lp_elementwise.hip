@@ -61,14 +61,18 @@ static int count_grid(size_t groups, int threads)
     return (int)std::min<size_t>(std::max<size_t>((groups + threads - 1) / threads, 1), kCountBlocks);
 }
 
-// What lp_range has just read, or another kernel has just written, is still in the memory-side cache (256 MB) if it and
-// the codes made of it fit: plain loads.  Larger tensors cannot be there, and would only push out what others left:
-// nontemporal ones.  As called, us, plain : nontemporal: lp_range + lp_quantize to 16 bits of 96 MB of floats 59.4 : 63.4,
-// 160 MB 84.6 : 88.6, 176 MB 101.3 : 94.7, 320 MB 174.9 : 152.0, 512 MB 262 : 229; to 8 bits of 176 MB 84.7 : 90.7, 240 MB
-// 118.7 : 115.5.  Accumulators: lp_range_acc + lp_act of 96 MB 57.6 : 60.5, 160 MB 83.3 : 83.4, 320 MB 159.9 : 138.9; behind the
-// kernel that wrote them, lp_act of 96 MB 52.2 : 55.1, 152 MB 82.5 : 81.8, 208 MB 118.6 : 108.5.
+// What another kernel has just read or written is still in the memory-side cache (256 MB) if it fits: plain loads.  Larger
+// tensors cannot be there, and would only push out what others left: nontemporal ones.  lp_quantize and lp_act write
+// codes beside what they read; what a range pass reads is read again.  As called, us, plain : nontemporal:
+//   lp_quantize, floats and codes within 256 MB: behind lp_range, to 16 bits 96 MB 59.4 : 63.4, 160 MB 84.6 : 88.6, 176 MB
+//   101.3 : 94.7, 512 MB 262 : 229; to 8 bits 176 MB 84.7 : 90.7, 240 MB 118.7 : 115.5
+//   lp_act, accumulators within 160 MB: behind the kernel that wrote them 96 MB 52.2 : 55.1, 152 MB 82.5 : 81.8, 208 MB 118.6 :
+//   108.5; behind lp_range_acc 96 MB 57.6 : 60.5, 160 MB 83.3 : 83.4, 320 MB 159.9 : 138.9
+//   the range pass, tensors within 224 MB (the kernel behind it as above): floats to 8 bits 208 MB 96.7 : 103.2, to 16 bits 208 MB
+//   108.2 : 107.4, 240 MB 122.1 : 120.1; accumulators to 8 bits 192 MB 88.8 : 92.6, to 16 bits 93.5 : 94.3, 240 MB 111.2 : 111.5
 static bool floats_once(size_t count, int n) { return count * (n > 8 ? 6 : 5) > ((size_t)256 << 20); }
 static bool accumulators_once(size_t count) { return count * 8 > ((size_t)160 << 20); }
+static bool range_once(size_t bytes) { return bytes > ((size_t)224 << 20); }
 template <bool ONCE, typename V> // (a constant: of two loads behind a branch the compiler makes one without the hint)
 __device__ __forceinline__ V load16(const V *p)
 {
@@ -694,7 +698,7 @@ extern "C" lp_status lp_range(const float *x_dev, size_t count, int n, double lo
     hipStream_t st = as_stream(stream);
     clear_stale_error();
     return range_call(count, n, loss_threshold, out_host, lost_host, st, [&](int slot, unsigned long long *line) {
-        hipLaunchKernelGGL(floats_once(count, n) ? range_f32_kernel<true> : range_f32_kernel<false>, dim3(range_grid(count / 4)), dim3(kThreads), 0,
+        hipLaunchKernelGGL(range_once(count * 4) ? range_f32_kernel<true> : range_f32_kernel<false>, dim3(range_grid(count / 4)), dim3(kThreads), 0,
                            st, x_dev, count, slot, line);
     });
 }
@@ -710,7 +714,7 @@ extern "C" lp_status lp_range_acc(const int64_t *acc_dev, size_t count, int f_ac
     hipStream_t st = as_stream(stream);
     clear_stale_error();
     return range_call(count, n, loss_threshold, out_host, lost_host, st, [&](int slot, unsigned long long *line) {
-        hipLaunchKernelGGL(accumulators_once(count) ? range_i64_kernel<true> : range_i64_kernel<false>, dim3(range_grid(count / 2)), dim3(kThreads), 0,
+        hipLaunchKernelGGL(range_once(count * 8) ? range_i64_kernel<true> : range_i64_kernel<false>, dim3(range_grid(count / 2)), dim3(kThreads), 0,
                            st, acc_dev, count, f_acc, relu ? 1 : 0, slot, line);
     });
 }

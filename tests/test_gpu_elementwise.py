@@ -377,7 +377,7 @@ def test_range_meets_in_one_group_or_eight(oracle, blocks):
         assert fmt.m == ma and list(got)[1:] == [int(v) for v in lost_a][1:]
 
 
-@pytest.mark.parametrize("n,count", [(16, (256 << 20) // 6 + 1), (16, (256 << 20) // 6), (8, (256 << 20) // 5 + 3)])
+@pytest.mark.parametrize("n,count", [(16, (256 << 20) // 6 + 1), (16, (256 << 20) // 6), (8, (256 << 20) // 5 + 3), (8, (224 << 20) // 4), (12, (224 << 20) // 4 + 1)])
 def test_floats_beyond_the_memory_side_cache(oracle, n, count):
     """Both sides of the line from which floats are loaded nontemporally: codes, counts and range against the oracle; a prefix,
     which lies on the other side, draws the same random words."""
@@ -401,7 +401,7 @@ def test_floats_beyond_the_memory_side_cache(oracle, n, count):
         assert not counters or int(z[0].item()) == int((whole == 0).sum().item())
 
 
-@pytest.mark.parametrize("n,count", [(16, (160 << 20) // 8 + 1), (16, (160 << 20) // 8), (8, (160 << 20) // 8 + 7)])
+@pytest.mark.parametrize("n,count", [(16, (160 << 20) // 8 + 1), (16, (160 << 20) // 8), (8, (160 << 20) // 8 + 7), (8, (224 << 20) // 8), (12, (224 << 20) // 8 + 1)])
 def test_accumulators_beyond_the_memory_side_cache(oracle, n, count):
     torch.manual_seed(count)
     acc = torch.randint(-(1 << 31), 1 << 31, (count,), device="cuda") >> torch.randint(0, 24, (count,), device="cuda")

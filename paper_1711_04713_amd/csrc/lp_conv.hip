@@ -1631,15 +1631,16 @@ __global__ __launch_bounds__(256)
 
 // The same layers where only 16-bit codes are wanted (the short epilogue, a shift of 9..20 bits, one channel
 // tile, channels by fours, no zero flags): what is left is counted in vector instructions, so
-//   - a workgroup runs several tiles: weights, window offsets and channel constants are set up once, the
-//     next tile's patch is on its way from memory while this one's codes are made, and there is one barrier a tile;
+//   - beyond the workgroups the chip holds at once, each runs several tiles: weights, window offsets and channel constants are set
+//     up once, the next tile's patch is on its way from memory while this one's codes are made, and there is one barrier a tile;
 //   - the accumulators start at the channel constants (with K <= 64 no limb sum passes 2^21, so nothing needs
 //     clamping on the way), and floor(v / 256) takes four instructions a code;
 //   - rounded values are clipped and packed two at a time;
 //   - with the pool the tile's pixels are dealt to lanes window by window: the maxima are two quad permutations,
 //     and the four lanes of a window store a group of channels each.
 // conv1_1 of VGG16 at batch 32 (12544 tiles) 85 -> 78 us, Giga1Net's 1x1 first layer 53 -> 34, with its pool 50 -> 36.
-constexpr int kFlatSlots = 4; // workgroups per CU by registers
+constexpr int kFlatSlots = 4;    // workgroups per CU by registers
+constexpr int kFlatUnderWay = 3; // codes of the next patch per thread under way during a tile; those past them (wide windows) come at its end
 template <int NCB, int KS, bool POOL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS == 4 ? 3 : 4, NCB * KS == 4 ? 3 : 4))) void conv_flat_codes_kernel(
     const ConvArgs a)
@@ -1674,7 +1675,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
             const bool in = i < nraw && n < a.N && iy >= 0 && iy < a.H && c >= 0 && c < wlen;
             return (short)__builtin_amdgcn_raw_buffer_load_b16(xrsrc, in ? (int)((unsigned)((n * a.H + iy) * wlen + c) * 2u) : -1, 0, 0);
         };
-        constexpr int RU = 3; // codes per thread under way during a tile; those past them (wide windows) come at its end
+        constexpr int RU = kFlatUnderWay;
         short v[RU];
         auto request = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
@@ -2137,6 +2138,26 @@ static bool fast_epilogue_ok(const lp_conv_desc *d, const Plan &p, int f_acc, bo
     return relu && r == LP_ROUND_NEAREST_AWAY && s >= 1 && s <= 31 && K <= 8192 && (!has_bias || f_acc - qb.f <= 24) && span_ok;
 }
 
+// Flat-window layers of which only 16-bit codes are wanted: is conv_flat_codes_kernel the faster one?  (Up to kCUs * kFlatSlots
+// tiles, three quarters of that with two blocks and K > 32, its workgroups still run one tile each: what it saves there is the epilogue
+// alone.)  It pays for setting up, per tile for gathering the window and for the codes of a patch that are not under way during
+// the tile before; what it saves grows with the channels.  us, conv_flat_kernel : conv_flat_codes_kernel, 112x112 images:
+//   two 32-channel blocks, K <= 32: 128 tiles 8.0 : 8.3, 392 10.96 : 10.90 (pooled 10.8 : 10.3), 2160 22.9 : 22.6 (20.6 : 18.4), 12544 85 : 78
+//   two blocks, K > 32: 592 tiles 14.8 : 15.8, 784 15.4 : 15.3, 1568 21.9 : 20.9
+//   two blocks, patches of 1920 codes: 1568 tiles 19.9 : 21.1, pooled 19.0 : 18.8
+//   one block, K <= 32: 784 tiles 8.8 : 9.0, 1080 11.3 : 11.3, 2160 16.5 : 15.2; pooled, 16 channels 1568 10.5 : 10.9, 2160 12.7 : 12.8, 6272 26.7 : 23.7
+//   one block, K > 32: 1568 tiles 12.1 : 12.5, 3136 19.4 : 19.6, 6272 32.3 : 29.1; pooled 3136 18.3 : 19.1, 6272 30.6 : 28.8
+//   one block, patches of 1152 to 1920 codes: K <= 32 pooled 3136 tiles 18.0 : 18.9, 6272 29.9 : 28.7, 15 channels 3136 24.5 : 27.5, 12544
+//   74.9 : 74.7; K > 32 3136 23.0 : 25.0, 12544 69.8 : 67.5
+// One block: a line through 500 layers of 385 to 13000 tiles, which gives away 0.2 % on average; in ns, per tile and CU.
+static bool flat_codes_pay(const lp_conv_desc *d, const Plan &p)
+{
+    const int tiles = p.tiles_m, late = std::max(0, (p.NPIXA * d->Cin + 255) / 256 - kFlatUnderWay); // codes per thread that are waited for
+    if (d->Cout > 32) return tiles > (late >= 5 && !p.pool ? kCUs * 48 : late >= 4 && !p.pool ? kCUs * 6 : p.ksteps == 2 ? kCUs * 3 : kCUs * 3 / 2);
+    const int saved = 350 - 54 * late - 4 * d->R * d->S * d->Cin - (p.pool ? 122 - 21 * ((d->Cout + 7) / 8) : 0);
+    return tiles > kCUs * 3 / 2 && (long long)saved * tiles > 1150ll * kCUs;
+}
+
 static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, const void *wp,
                               lp_qfmt qw, const void *bias, lp_qfmt qb, int64_t *acc_out, void *y,
                               lp_qfmt qy, int relu, lp_round r, uint64_t *zero_count, uint64_t *sat_count,
@@ -2244,11 +2265,10 @@ static lp_status conv_forward(const lp_conv_desc *d, const void *x, lp_qfmt qx, 
     a.fast = (y && !acc_out && fast_epilogue_ok(d, p, f_acc, bias != nullptr, qb, qy, relu, r)) ? 1 : 0;
     a.pool = p.pool;
     if (p.pool && !(a.fast && a.y16 && d->Cout % 4 == 0)) return LP_EUNSUPPORTED;
-    // flat-window layers of which only 16-bit codes are wanted: workgroups that run several tiles, as many as the chip holds at
-    // once.  With about a tile per CU there is nothing to run on with, and setting up is longer: 8 tiles 4.24 : 4.53 us,
-    // 128 tiles 8.0 : 8.3, 288 tiles (7x7 window) 8.5 : 8.8, but 392 tiles 10.96 : 10.70.
-    const bool codes_only = p.flat && a.fast && a.y16 && !y_flags && p.tiles_n == 1 && a.total_work > kCUs * 3 / 2 && d->Cout % 4 == 0 &&
-                            a.act.s >= 9 && a.act.s <= 20;
+    // flat-window layers of which only 16-bit codes are wanted: workgroups that run several tiles where there are more than the
+    // chip holds at once
+    const bool codes_only = p.flat && a.fast && a.y16 && !y_flags && p.tiles_n == 1 && d->Cout % 4 == 0 && a.act.s >= 9 && a.act.s <= 20 &&
+                            flat_codes_pay(d, p);
     if (codes_only) {
         const int ncb = d->Cout <= 32 ? 1 : 2, per_cu = ncb * p.ksteps == 4 ? kFlatSlots - 1 : kFlatSlots;
         grid = std::min(grid, kCUs * per_cu);

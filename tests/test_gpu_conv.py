@@ -622,37 +622,90 @@ def test_codes_and_counts_of_the_short_epilogue(oracle, shape, k, qx, qw, n):
         assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (zeros, sats)
 
 
+def _flat_codes_launch(info, Cin, Cout, k, pool):
+    """(the several-tiles kernel takes a call that wants 16-bit codes alone, workgroups it starts at most): the dispatch's rule."""
+    K, tiles = k * k * Cin, info["tiles_m"]
+    late = max(0, -(-info["patch_rows"] * info["patch_cols"] * Cin // 256) - 3)
+    cap = 256 * (3 if Cout > 32 and K > 32 else 4)
+    if Cout > 32:
+        return tiles > 256 * (48 if late >= 5 and not pool else 6 if late >= 4 and not pool else 3 if K > 32 else 1.5), cap
+    saved = 350 - 54 * late - 4 * K - (122 - 21 * -(-Cout // 8) if pool else 0)
+    return tiles > 384 and saved * tiles > 1150 * 256, cap
+
+
+def _spread_codes(rng, shape, zero_frac):
+    """Codes of every magnitude, so that small and large shifts both leave values between zero and the clip."""
+    return _codes(rng, shape, zero_frac=zero_frac) >> rng.integers(0, 13, shape).astype(np.int32)
+
+
+@pytest.mark.parametrize("plain", [False, True])
 @pytest.mark.parametrize("N,Cin,H,W,Cout,k,pad,n,pool", [
-    (4, 3, 112, 113, 64, 3, 1, 16, 0),       # ragged tiles at the right edge
-    (1, 3, 288, 192, 16, 1, 0, 16, 1),       # K = 3, half of the 32-channel block, pooled
-    (1, 3, 256, 208, 64, 3, 1, 16, 1),       # both blocks, pooled
-    (300, 3, 13, 13, 36, 3, 1, 16, 0),       # tiles straddle images; a group of four channels without its neighbour
-    (13, 7, 64, 64, 64, 3, 1, 16, 0),         # K = 63: two K = 32 halves; more of a patch than is under way at a time
-    (60, 1, 30, 30, 20, 7, 3, 12, 0),        # K = 49, one block, 12-bit codes
-    (50, 2, 32, 32, 8, 5, 2, 16, 1),         # K = 50, pooled
-    (1, 1, 47, 1100, 4, 1, 0, 16, 0),        # K = 1
+    (12, 3, 112, 113, 64, 3, 1, 16, 0),      # ragged tiles at the right edge
+    (3, 3, 288, 192, 16, 1, 0, 16, 1),       # K = 3, half of the 32-channel block, pooled
+    (3, 3, 256, 208, 64, 3, 1, 16, 1),       # both blocks, pooled
+    (760, 3, 13, 13, 36, 3, 1, 16, 0),       # tiles straddle images; a group of four channels without its neighbour
+    (17, 3, 100, 99, 32, 3, 1, 16, 0),       # one whole block
+    (27, 7, 64, 64, 64, 3, 1, 16, 0),        # K = 63: two K = 32 halves; more of a patch than is under way at a time
+    (11, 7, 96, 104, 40, 3, 1, 16, 1),       # the same pooled, ten of sixteen groups of channels
+    (290, 1, 30, 30, 20, 7, 3, 12, 0),       # K = 49, one block, 12-bit codes
+    (340, 2, 32, 32, 32, 5, 2, 16, 1),       # K = 50, pooled
+    (3, 1, 47, 1100, 4, 1, 0, 16, 0),        # K = 1
+    (1, 3, 224, 224, 64, 3, 1, 16, 0),       # one tile per workgroup
 ])
-def test_flat_window_workgroups_of_several_tiles(oracle, N, Cin, H, W, Cout, k, pad, n, pool):
-    """More than three tiles for two CUs and codes alone: every shift the kernel takes and one on each side of them, with biases whose
-    upper part is clamped, formats that clip, and the same calls with one tile per workgroup's formats."""
+def test_flat_window_workgroups_of_several_tiles(oracle, N, Cin, H, W, Cout, k, pad, n, pool, plain):
+    """Codes alone of more tiles than the launch has workgroups (but for the last case): shifts at both ends and in between, biases
+    whose upper part is clamped, formats that clip, weights in both limb forms."""
     rng = np.random.default_rng(N + 10 * Cin + k)
+    qw = (16, 1, 15)
+    x, w = _spread_codes(rng, (N, Cin, H, W), 0.3), np.minimum(_spread_codes(rng, (Cout, Cin, k, k), 0.0), 32639)
+    if plain:
+        w[Cout // 2, 0, 0, 0] = 32767
+    bias = _codes(rng, (Cout,))
+    for qx, fb, fos in (((16, 8, 8), None, (14, 10, 6, 3)), ((16, 8, 8), 0, (14, 13, 9, 3)), ((16, 1, 15), 6, (15, 12, 10))):
+        f = qx[2] + qw[2]                                          # 23 or 30; biases shifted by 23 or 24: up to 2^39
+        b = None if fb is None else bias
+        acc = oracle.conv(x, w, bias=b, f_acc=f, fb=fb or 0, pad=pad, threads=8)
+        for fo in sorted({min(fo, n - 1) for fo in fos}):
+            qy = (n, n - fo, fo)
+            y, zeros, sats = oracle.act(acc, f, *qy, True, oracle.ROUND_AWAY, with_sat=True)
+            got = conv(x, qx, w, qw, qy=qy, pad=pad, want_acc=False, bias=b, qb=None if fb is None else (16, 16 - fb, fb), pool=pool)
+            taken, cap = _flat_codes_launch(got["info"], Cin, Cout, k, pool)
+            assert got["info"]["kernel"] == lp.LP_KERNEL_FLAT and got["info"]["tiles_n"] == 1 and 9 <= f - fo <= 20 and taken
+            assert (got["info"]["tiles_m"] > cap) == (N > 1)
+            assert np.array_equal(got["y"], oracle.maxpool2x2(y) if pool else y)
+            assert (got["zeros"], got["sats"]) == (zeros, sats)
+
+
+@pytest.mark.parametrize("plain", [False, True])
+@pytest.mark.parametrize("N,Cin,H,W,Cout,k", [(1, 3, 370, 370, 36, 3), (1, 7, 320, 320, 36, 3)])
+def test_flat_window_shifts(oracle, N, Cin, H, W, Cout, k, plain):
+    """Every shift the several-tiles kernel takes, 9 to 20 bits, and the two on each side of them, which run one tile per workgroup."""
+    rng = np.random.default_rng(Cin)
     qx, qw = (16, 8, 8), (16, 1, 15)
-    x, w = _codes(rng, (N, Cin, H, W), zero_frac=0.3), _codes(rng, (Cout, Cin, k, k))
-    f_acc = qx[2] + qw[2]
-    bias, qb = _codes(rng, (Cout,)), (16, 16, 0)                   # shifted by 23: up to 2^38
-    qx12 = (16, 1, 15)                                             # for the larger shifts
-    for q, fo, with_bias in ((qx, 14, True), (qx, 13, False), (qx, 9, True), (qx12, 15, False), (qx12, 10, True), (qx12, 9, False)):
-        f = q[2] + qw[2]
-        fb = f_acc - 23 if q is qx else f - 24
-        b = bias if with_bias else None
-        qb = (16, 16 - fb, fb)
-        qy = (n, n - min(fo, n - 1), min(fo, n - 1))
-        acc = oracle.conv(x, w, bias=b, f_acc=f, fb=fb, pad=pad, threads=8)
-        y, zeros, sats = oracle.act(acc, f, *qy, True, oracle.ROUND_AWAY, with_sat=True)
-        got = conv(x, q, w, qw, qy=qy, pad=pad, want_acc=False, bias=b, qb=qb if with_bias else None, pool=pool)
-        assert got["info"]["kernel"] == lp.LP_KERNEL_FLAT and got["info"]["tiles_m"] > 384
-        assert np.array_equal(got["y"], oracle.maxpool2x2(y) if pool else y)
-        assert (got["zeros"], got["sats"]) == (zeros, sats)
+    x, w = _spread_codes(rng, (N, Cin, H, W), 0.3), np.minimum(_spread_codes(rng, (Cout, Cin, k, k), 0.0), 32639)
+    if plain:
+        w[-1, 0, 0, 0] = 32640
+    acc = oracle.conv(x, w, f_acc=23, pad=1, threads=8)
+    for s in range(8, 23):
+        fo = 23 - s
+        y, zeros, sats = oracle.act(acc, 23, 16, 16 - fo, fo, True, oracle.ROUND_AWAY, with_sat=True)
+        got = conv(x, qx, w, qw, qy=(16, 16 - fo, fo), want_acc=False)
+        taken, cap = _flat_codes_launch(got["info"], Cin, Cout, k, 0)
+        assert got["info"]["kernel"] == lp.LP_KERNEL_FLAT and taken and got["info"]["tiles_m"] > cap
+        assert np.array_equal(got["y"], y), s
+        assert (got["zeros"], got["sats"]) == (zeros, sats), s
+
+
+@pytest.mark.parametrize("N,Cin,H,W,Cout,k,pool", [(1, 3, 224, 224, 32, 3, 0), (4, 7, 112, 112, 64, 3, 0), (16, 15, 56, 56, 32, 1, 1)])
+def test_flat_window_layers_beside_the_line(oracle, N, Cin, H, W, Cout, k, pool):
+    """Enough tiles for the several-tiles kernel with other channels or windows, not with these: one tile per workgroup."""
+    rng = np.random.default_rng(Cout + Cin)
+    x, w = _spread_codes(rng, (N, Cin, H, W), 0.3), _spread_codes(rng, (Cout, Cin, k, k), 0.0)
+    acc = oracle.conv(x, w, f_acc=23, pad=k // 2, threads=8)
+    y, zeros, sats = oracle.act(acc, 23, 16, 6, 10, True, oracle.ROUND_AWAY, with_sat=True)
+    got = conv(x, (16, 8, 8), w, (16, 1, 15), qy=(16, 6, 10), pad=k // 2, want_acc=False, pool=pool)
+    assert got["info"]["tiles_m"] > 384 and not _flat_codes_launch(got["info"], Cin, Cout, k, pool)[0]
+    assert np.array_equal(got["y"], oracle.maxpool2x2(y) if pool else y) and (got["zeros"], got["sats"]) == (zeros, sats)
 
 
 def _weights_of_both_forms(rng, shape, top):
@@ -670,7 +723,7 @@ def _weights_of_both_forms(rng, shape, top):
     (1, 256, 12, 10, 96, 3),       # parts of tiles
     (1, 512, 28, 28, 256, 3),      # three wave groups
     (2, 3, 20, 20, 72, 3),         # flat window
-    (1, 3, 230, 230, 24, 3),       # flat window, several tiles per workgroup
+    (1, 3, 420, 420, 24, 3),       # flat window, several tiles per workgroup
     (2, 16, 17, 19, 80, 7),        # window rows
     (2, 48, 9, 9, 20, 3),
 ])

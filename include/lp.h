@@ -166,13 +166,16 @@ lp_status lp_conv_pack_weights(const lp_conv_desc *d, lp_qfmt qx, lp_qfmt qw, co
  * N*Ho stacked output rows x tile_cols columns, times bn output channels), the staged
  * input patch (patch_rows x patch_cols pixels; a pixel takes patch_pixel bytes per limb -- patch kernel: 64 of
  * codes and the rest padding that spreads consecutive pixels over the LDS banks; rows are
- * patch_pitch bytes apart), tile counts and LDS bytes per workgroup; the launch: workgroups in the grid (LP_KERNEL_FLAT: at
- * most; calls that want 16-bit codes alone run several tiles per workgroup), and split = parts into which each tile of the
+ * patch_pitch bytes apart), tile counts and LDS bytes per workgroup; the launch: workgroups in the grid, and split = parts into which each tile of the
  * last, partly filled round of workgroup slots is cut along the reduction (1 = none; used
  * only when a workspace is passed).  Work item wi = pixel tile * tiles_n + channel tile (pixel
  * tiles row-major over stacked output rows x columns); die j of the chip's eight owns the items
  * j * items_per_die ... (j + 1) * items_per_die - 1, of which the first whole_items_per_die are
  * computed by one workgroup each and the rest are the split ones.
+ * LP_KERNEL_FLAT: lds_bytes and workgroups are those of the kernel that takes every call.  A call that wants 16-bit codes
+ * alone (y_codes_dev without acc_out_dev or zero flags; ReLU, round half away, a shift of 9 to 20 bits, Cout <= 64 and a multiple of
+ * 4) may run another one if there are more than 384 tiles, and how many depends on the window and the channels: it holds
+ * up to 26 KB of LDS, and beyond 768 or 1024 workgroups each of them computes several tiles.
  */
 typedef struct {
     int32_t path, limbs, bn, tile_rows, tile_cols, patch_rows, patch_cols, tiles_m, tiles_n;

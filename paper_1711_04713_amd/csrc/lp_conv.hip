@@ -1652,6 +1652,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
     __shared__ __align__(16) unsigned ones[32]; // pair of window positions -> 1 for each that exists, so that its dot product with the codes sums them
     __shared__ __align__(16) int ctab[3 * BN];
     __shared__ unsigned wave_counts[2][THREADS / 64];
+    static_assert((sizeof raw + sizeof wlds + sizeof koff + sizeof ones + sizeof ctab + sizeof wave_counts) * kFlatSlots <= 160 * 1024,
+                  "the workgroups of a CU fit its LDS");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, kg = lane >> 5;
     // the die's tiles, evenly over its workgroups
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;

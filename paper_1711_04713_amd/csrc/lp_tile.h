@@ -258,7 +258,7 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
         auto requant_tile = [&](auto s16c, auto y16c, auto modec, auto satc) __attribute__((always_inline)) {
             constexpr int S16 = decltype(s16c)::value;
             constexpr bool Y16 = decltype(y16c)::value;
-            constexpr int MODE = decltype(modec)::value; // 0: four codes per store, 1: fused 2x2 max-pool, 2: ragged channels
+            constexpr int MODE = decltype(modec)::value; // 0: four codes per store, 1: fused 2x2 max-pool, 2: ragged channels, 3: 16 bytes of codes per store
             constexpr bool SAT = decltype(satc)::value;  // also count the values clipped at cmax (with ReLU the only end)
             constexpr int ESZ = Y16 ? 2 : 1;
             const int first = __builtin_amdgcn_readfirstlane(MODE == 1 ? pooloff[0] : outoff[0]);
@@ -281,13 +281,15 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                 return outoff[m];
             };
             auto exists = [&](int mb) __attribute__((always_inline)) { return MODE == 1 ? pixel_at(mb, l32) >= 0 : rel[mb] != NOWHERE; };
-            // 8-bit codes of whole blocks of 32 channels are stored together.  A lane holds four neighbouring channels of each
+            // 8-bit codes of whole blocks of 32 channels, of tensors whose pixels start on 16-byte boundaries, are stored together.  A lane holds four neighbouring channels of each
             // group of eight, of one pixel: stored as they are, an instruction touches 32 lines with 8 bytes each, and the
             // memory system takes a step per line and instruction.  Swapping halves and rows of lanes between registers
             // first gives every lane 16 neighbouring bytes, four lanes to a pixel: 64x56x56, 128 -> 256 3x3 69.7 -> 61.7 us,
             // 256 -> 256 116.4 -> 106.9.  (16-bit codes, twice the bytes per line as they are, gain at most 2 % on large
-            // layers, but small ones then wait for their stores at the end: 18x18, 64 -> 64 batch 32 10.2 -> 10.45 us.)
-            constexpr bool BLOCKS = MODE == 0 && GL == 4 && !Y16;
+            // layers, but small ones then wait for their stores at the end: 18x18, 64 -> 64 batch 32 10.2 -> 10.45 us.  Four 8-bit codes
+            // that cannot join such a piece leave as they are made for the same reason: 24x180x9, 192 -> 232 3x3 26.2 us with their
+            // stores at the end, 24.6.)
+            constexpr bool BLOCKS = MODE == 3;
             unsigned word[MBL][NB][GL];
             // Counting.  A wave that is not multiplying issues one instruction at a time beside the others' MFMAs,
             // on whichever unit, so what a count costs is its instructions, scalar ones included.  Zeros: codes are
@@ -441,16 +443,6 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
 #pragma unroll
                 for (int mb = 0; mb < MBL; ++mb) {
                     unsigned(&w)[NB][GL] = word[mb];
-                    if ((a.Cout & 15) != 0) { // pieces of 16 bytes would not start on their boundaries: four codes at a time
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                            for (int gl = 0; gl < GL; ++gl) {
-                                const int ch = colw + nb * 32 + 8 * gl + 4 * kg;
-                                __builtin_amdgcn_raw_buffer_store_b32(w[nb][gl], yrsrc, (int)(ch < a.Cout ? rel[mb] + (unsigned)ch : NOWHERE), 0, 0);
-                            }
-                        continue;
-                    }
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -487,6 +479,9 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
         auto by_mode = [&](auto s16c, auto y16c) __attribute__((always_inline)) {
             if constexpr (decltype(y16c)::value) {
                 if (a.pool) return by_sat(s16c, y16c, integral_constant<int, 1>{});
+            }
+            if constexpr (!decltype(y16c)::value && GL == 4) {
+                if ((a.Cout & 15) == 0) return by_sat(s16c, y16c, integral_constant<int, 3>{});
             }
             if ((a.Cout & 3) == 0) by_sat(s16c, y16c, integral_constant<int, 0>{}); // every group of four channels is aligned
             else by_sat(s16c, y16c, integral_constant<int, 2>{});

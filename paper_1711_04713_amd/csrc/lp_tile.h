@@ -320,8 +320,8 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
                     int rounded[MBL][4], peak = 0; // the rounded values before clipping, the largest of them
 #pragma unroll
                     for (int mb = 0; mb < MBL; ++mb) {
-                        int q[4];
-                        int (&raw)[4] = rounded[mb];
+                        int q[4], own[4];
+                        int (&raw)[4] = MODE == 2 ? own : rounded[mb]; // (read by a run-time count there: of four values, not of every block's)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const int v = 4 * gl + e;

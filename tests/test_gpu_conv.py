@@ -743,6 +743,20 @@ def test_weight_limb_forms(oracle, top, N, Cin, H, W, Cout, k):
 
 
 @pytest.mark.parametrize("top", [32639, 32640, 32767])
+@pytest.mark.parametrize("N,Cin,H,W,Cout,k", [(2, 64, 16, 16, 136, 3), (1, 256, 16, 16, 96, 3), (2, 3, 32, 32, 72, 3), (2, 16, 32, 32, 80, 5)])
+def test_weight_limb_forms_with_bias_and_pool(oracle, top, N, Cin, H, W, Cout, k):
+    """The same codes beside a bias and through the fused pool, on the patch (whole tiles and parts), flat-window and window-row kernels."""
+    rng = np.random.default_rng(top + Cin)
+    x = _codes(rng, (N, Cin, H, W), zero_frac=0.3)
+    w, bias, qb = _weights_of_both_forms(rng, (Cout, Cin, k, k), top), _codes(rng, (Cout,)), (16, 8, 8)
+    acc = oracle.conv(x, w, bias=bias, f_acc=27, fb=8, pad=k // 2, threads=8)
+    y, zeros, sats = oracle.act(acc, 27, 16, 6, 10, True, oracle.ROUND_AWAY, with_sat=True)
+    for pool in (0, 1):
+        got = conv(x, QX, w, QW, qy=(16, 6, 10), pad=k // 2, want_acc=False, bias=bias, qb=qb, pool=pool)
+        assert np.array_equal(got["y"], oracle.maxpool2x2(y) if pool else y) and (got["zeros"], got["sats"]) == (zeros, sats)
+
+
+@pytest.mark.parametrize("top", [32639, 32640, 32767])
 @pytest.mark.parametrize("M,K,Nout", [(1, 1000, 130), (40, 333, 70), (64, 515, 100), (130, 700, 200), (300, 4100, 128)])
 def test_fc_weight_limb_forms(oracle, top, M, K, Nout):
     rng = np.random.default_rng(top + M)

@@ -71,13 +71,25 @@ def _sparse_pair(rng, N, C0, H, W, C1, C2, n=16):
     return x, w1, w2
 
 
+def _plain_tiles(w, first):
+    """Plants one of the top codes, which a signed low limb cannot hold, in every other tile of 64 output channels from `first`
+    on: once under the live input channels and once under the dead ones."""
+    for tile in range(first, -(-w.shape[0] // 64), 2):
+        w[min(64 * tile + 5, w.shape[0] - 1), 1, 1, 1] = 32640
+        w[64 * tile, -1, 0, 2] = 32767
+    return w
+
+
 @pytest.mark.parametrize("shape,pool", [((4, 64, 24, 32, 128, 64), 0), ((4, 64, 24, 32, 256, 96), 1),
                                         ((6, 128, 16, 16, 192, 64), 0), ((2, 64, 12, 12, 256, 64), 0),
                                         ((24, 64, 64, 64, 128, 128), 0), ((24, 64, 64, 64, 128, 128), 1)])
-def test_two_layers_with_structured_zeros(oracle, shape, pool):
+@pytest.mark.parametrize("plain", [None, 0, 1])          # second layer's weights: every tile in the signed limb form, or every other one plain
+def test_two_layers_with_structured_zeros(oracle, shape, pool, plain):
     N, C0, H, W, C1, C2 = shape
     rng = np.random.default_rng(sum(shape))
     x, w1, w2 = _sparse_pair(rng, N, C0, H, W, C1, C2)
+    if plain is not None:
+        _plain_tiles(w2, plain % -(-C2 // 64))
     acc1 = oracle.conv(x, w1, threads=8)
     y1, z1, s1 = oracle.act(acc1, 27, *QY, True, oracle.ROUND_AWAY, with_sat=True)
     a = _layer(x, w1, QX, QW, QY, pool=pool)
@@ -145,13 +157,13 @@ def test_flags_from_split_tiles_and_all_zero_input(oracle):
     assert np.array_equal(a["flags"].cpu().numpy(), _expected_flags(y1, a["info"]))
     blank = np.zeros((2, 128, 16, 16), np.int32)
     w = rng.integers(-2000, 2000, (64, 128, 3, 3)).astype(np.int32)
-    d = lp.ConvDesc(2, 16, 16, 128, 64, 3, 3, 1, 1)
     info_prev = dict(lp.lp_conv_plan_info(lp.ConvDesc(2, 16, 16, 64, 128, 3, 3, 1, 1), QX, QW))
     zeros = torch.zeros(info_prev["tiles_m"] * info_prev["tiles_n"], dtype=torch.uint8, device="cuda")
-    b = _layer(blank, w, QX, QW, QY, x_map=lp.zero_map(zeros, info_prev, 16))
-    assert not b["y_np"].any() and b["zeros"] == b["y_np"].size
-    assert b["skipped"] > 0 or b["info"]["split"] > 1        # tiles that share their reduction multiply everything
-    assert not b["flags"].cpu().numpy().any()
+    for weights in (w, _plain_tiles(w.copy(), 0)):           # both limb forms
+        b = _layer(blank, weights, QX, QW, QY, x_map=lp.zero_map(zeros, info_prev, 16))
+        assert not b["y_np"].any() and b["zeros"] == b["y_np"].size
+        assert b["skipped"] > 0 or b["info"]["split"] > 1    # tiles that share their reduction multiply everything
+        assert not b["flags"].cpu().numpy().any()
 
 
 def test_int8_layers_skip_too(oracle):
@@ -201,10 +213,13 @@ def test_stack_with_zero_skipping_matches_oracle_chain(oracle):
         assert int(st.skipped[1:].sum().item()) > 0 or all(G["info"]["split"] > 1 for G in st.layers[1:])
 
 
-def test_skipping_in_the_three_wave_group_form(oracle):
+@pytest.mark.parametrize("plain", [None, 0, 1])
+def test_skipping_in_the_three_wave_group_form(oracle, plain):
     """A grid of at most a tile per CU with 8 chunks: the wave groups of a workgroup leave out the same chunks."""
     rng = np.random.default_rng(9)
     x, w1, w2 = _sparse_pair(rng, 18, 64, 14, 14, 512, 320)
+    if plain is not None:
+        _plain_tiles(w2, plain)
     a = _layer(x, w1, QX, QW, QY)
     y1, _ = oracle.act(oracle.conv(x, w1, threads=8), 27, *QY, True, oracle.ROUND_AWAY)
     b = _layer(y1, w2, QY, QW, (16, 9, 7), x_map=lp.zero_map(a["flags"], a["info"], a["W"]))

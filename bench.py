@@ -27,6 +27,15 @@ TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "conv_stack_vgg16_batch32_hbm_t
 KERNEL_SOURCES = ("lp_conv.hip", "lp_tile.h", "lp_device.h")
 
 
+def kernel_and_workgroups(lp, info):
+    """What the plan says of a layer's launch.  Which of the two flat-window kernels runs, and how many workgroups it takes, is decided
+    per call (by what the call wants written), so the plan does not know."""
+    if info["kernel"] == lp.LP_KERNEL_FLAT:
+        return "conv_flat_codes_kernel or conv_flat_kernel", None
+    return {lp.LP_KERNEL_DIRECT: "conv_direct_kernel", lp.LP_KERNEL_ROWS: "conv_rows_kernel",
+            lp.LP_KERNEL_PATCH: "conv_mfma_kernel<%d limbs,%d channels>" % (info["limbs"], info["bn"])}[info["kernel"]], info["workgroups"]
+
+
 def kernel_sources_sha256():
     import hashlib
 
@@ -320,9 +329,7 @@ def main():
         macs = L["macs"]
         total_macs += macs
         info = L["info"]
-        kname = {lp.LP_KERNEL_DIRECT: "conv_direct_kernel", lp.LP_KERNEL_FLAT: "conv_flat_kernel",
-                 lp.LP_KERNEL_ROWS: "conv_rows_kernel",
-                 lp.LP_KERNEL_PATCH: "conv_mfma_kernel<%d limbs,%d channels>" % (info["limbs"], info["bn"])}[info["kernel"]]
+        kname, workgroups = kernel_and_workgroups(lp, info)
         kern_ops[kname] = kern_ops.get(kname, 0) + 8 * macs          # 4 int8 limb MACs = 8 int8 ops per 16-bit MAC
         kern_ms[kname] = kern_ms.get(kname, 0.0) + ms
         layers.append({
@@ -330,7 +337,7 @@ def main():
             "format_out": repr(L["qy"]), "sparsity": round(float(zeros[i]) / L["y_numel"], 4),
             "saturated": round(float(sats[i]) / L["y_numel"], 6), "pool_fused": bool(L["fused_pool"]),
             "int8_tops": round(8 * macs / (ms * 1e-3) / 1e12, 1), "kernel": kname,
-            "tile": [info["tile_rows"], info["tile_cols"], info["bn"]], "workgroups": info["workgroups"],
+            "tile": [info["tile_rows"], info["tile_cols"], info["bn"]], "workgroups": workgroups,
             "split": info["split"],
         })
     dominant = max(kern_ms, key=kern_ms.get)

@@ -318,3 +318,15 @@ def test_large_tensors_are_loaded_nontemporally():
         assert all(line.rstrip().endswith(" nt") == (m[2] == "1") for line in wide), name
         seen.setdefault(m[1], set()).add(m[2])
     assert seen == {k: {"0", "1"} for k in ("quantize", "range_f32", "range_i64", "act")}
+
+
+def test_bench_names_no_kernel_that_the_plan_does_not_know():
+    """The first layer of the benchmark's stack runs on one of two flat-window kernels, chosen per call; its record names both and
+    no grid, the other layers' what the plan says."""
+    import bench
+
+    first = lp.lp_conv_plan_info(lp.ConvDesc(32, 224, 224, 3, 64, 3, 3, 1, 1), Q16, W16)
+    name, workgroups = bench.kernel_and_workgroups(lp, first)
+    assert "conv_flat_codes_kernel" in name and "conv_flat_kernel" in name and workgroups is None
+    info = lp.lp_conv_plan_info(lp.ConvDesc(32, 112, 112, 128, 128, 3, 3, 1, 1), Q16, W16)
+    assert bench.kernel_and_workgroups(lp, info) == ("conv_mfma_kernel<2 limbs,64 channels>", info["workgroups"])

@@ -1731,136 +1731,136 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCB * KS ==
         park(wi, raw[0]);
         __syncthreads();
         auto run = [&](auto SUMS) __attribute__((always_inline)) {
-        constexpr bool sums = decltype(SUMS)::value;
-        for (int buf = 0; wi < wi_end; ++wi, buf ^= 1) {
-            if (wi + 1 < wi_end) request(wi + 1);
-            int tile_r, tile_c, img0, yo0, img, yo;
-            udivmod(wi, a.tiles_c, a.mg_tiles_c, tile_r, tile_c);
-            const int fr0 = tile_r * a.RH, x0 = tile_c * a.TW;
-            udivmod(fr0, a.Ho, a.mg_Ho, img0, yo0);
-            const int fr = fr0 + j, xo = x0 + t;
-            udivmod(fr, a.Ho, a.mg_Ho, img, yo);
-            const bool ok = j < a.RH && fr < a.FR && xo < a.Wo;
-            const unsigned char *rawb = (const unsigned char *)raw[buf] + (ok ? ((img - img0) * a.Hp + yo - yo0) * rowlen + t * a.Cin : 0) * 2;
-            // the lane's 16 window codes of each K half, two per register, then split into limb bytes
-            int sum = 0;
-            v4i ah[KS], al[KS];
-#pragma unroll
-            for (int h = 0; h < KS; ++h) {
-                const int *ko = koff + h * 32 + kg * 16;
-                const v4i o0 = *(const v4i *)ko, o1 = *(const v4i *)(ko + 4), o2 = *(const v4i *)(ko + 8), o3 = *(const v4i *)(ko + 12);
-                const int o[16] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w, o2.x, o2.y, o2.z, o2.w, o3.x, o3.y, o3.z, o3.w};
-                const v4i n0 = *(const v4i *)(ones + h * 16 + kg * 8), n1 = *(const v4i *)(ones + h * 16 + kg * 8 + 4);
-                const int one[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
-                unsigned pr[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    pr[q] = 0;
-                    if (h * 32 + 2 * q < a.Kflat) { // (uniform; a position past K reads some code and meets zero weights)
-                        const v2s two = {*(const short *)(rawb + o[2 * q]), *(const short *)(rawb + o[2 * q + 1])};
-                        pr[q] = __builtin_bit_cast(unsigned, two);
-                        if constexpr (sums) sum = __builtin_amdgcn_sdot2(two, __builtin_bit_cast(v2s, one[q]), sum, false);
-                    }
-                }
-                unsigned hi[4], lo[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    hi[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x07050301u);
-                    lo[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x06040200u) ^ 0x80808080u;
-                }
-                ah[h] = v4i{(int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-                al[h] = v4i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3]};
-            }
-            const int rs = sums ? sum + __shfl_xor(sum, 32, 64) : 0; // a row's two lanes hold different window positions
-            const int rs2 = rs >> 1, odd = (rs & 1) << 7;
-            // outputs: 32-bit offsets from the tile's first pixel
-            const int first = POOL ? (img0 * (a.Ho >> 1) + (yo0 >> 1)) * (a.Wo >> 1) + (x0 >> 1) : fr0 * a.Wo + x0;
-            const int pixels = POOL ? a.N * (a.Ho >> 1) * (a.Wo >> 1) : a.N * a.Ho * a.Wo;
-            const size_t left = (size_t)(pixels - first) * a.Cout * 2;
-            const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc(
-                (unsigned char *)a.y + (size_t)first * a.Cout * 2, 0, (int)(left < 0x7fffffffu ? left : 0x7fffffffu), 0x00020000);
-            constexpr unsigned NOWHERE = 0x80000000u;
-            const int out = POOL ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : fr * a.Wo + xo;
-            const unsigned rel = ok ? (unsigned)((out - first) * a.Cout * 2) : NOWHERE;
-            unsigned nnz = 0;
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
-                v16i acc[3];
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const v4i c = *(const v4i *)(ctab + q * BN + cb * 32 + 8 * g + 4 * kg);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[q][4 * g + e] = c[e];
-                    }
+            constexpr bool sums = decltype(SUMS)::value;
+            for (int buf = 0; wi < wi_end; ++wi, buf ^= 1) {
+                if (wi + 1 < wi_end) request(wi + 1);
+                int tile_r, tile_c, img0, yo0, img, yo;
+                udivmod(wi, a.tiles_c, a.mg_tiles_c, tile_r, tile_c);
+                const int fr0 = tile_r * a.RH, x0 = tile_c * a.TW;
+                udivmod(fr0, a.Ho, a.mg_Ho, img0, yo0);
+                const int fr = fr0 + j, xo = x0 + t;
+                udivmod(fr, a.Ho, a.mg_Ho, img, yo);
+                const bool ok = j < a.RH && fr < a.FR && xo < a.Wo;
+                const unsigned char *rawb = (const unsigned char *)raw[buf] + (ok ? ((img - img0) * a.Hp + yo - yo0) * rowlen + t * a.Cin : 0) * 2;
+                // the lane's 16 window codes of each K half, two per register, then split into limb bytes
+                int sum = 0;
+                v4i ah[KS], al[KS];
 #pragma unroll
                 for (int h = 0; h < KS; ++h) {
-                    const v4i wh = wlds[(h * 2 + 0) * NCB + cb][lane], wl = wlds[(h * 2 + 1) * NCB + cb][lane];
-                    acc[0] = mfma_i8(wh, ah[h], acc[0]);
-                    acc[1] = mfma_i8(wl, ah[h], acc[1]);
-                    acc[2] = mfma_i8(wl, al[h], acc[2]);
-                    acc[1] = mfma_i8(wh, al[h], acc[1]);
-                }
-                int peak = 0;
-                unsigned word[4][2] = {};
+                    const int *ko = koff + h * 32 + kg * 16;
+                    const v4i o0 = *(const v4i *)ko, o1 = *(const v4i *)(ko + 4), o2 = *(const v4i *)(ko + 8), o3 = *(const v4i *)(ko + 12);
+                    const int o[16] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w, o2.x, o2.y, o2.z, o2.w, o3.x, o3.y, o3.z, o3.w};
+                    const v4i n0 = *(const v4i *)(ones + h * 16 + kg * 8), n1 = *(const v4i *)(ones + h * 16 + kg * 8 + 4);
+                    const int one[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
+                    unsigned pr[8];
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int ch = cb * 32 + 8 * g + 4 * kg;
-                    if (cb * 32 + 8 * g >= a.Cout) continue; // (uniform)
-                    const unsigned one = ch < a.Cout ? 0x00010001u : 0u; // what a code that exists may add to the count
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        int r[2];
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const int i = 4 * g + 2 * h + e;
-                            // floor(v / 256): the dropped low byte cannot carry into a multiple of 256
-                            const int W = (acc[0][i] << 8) + acc[1][i] + (rs2 + ((acc[2][i] + odd) >> 8));
-                            r[e] = acc[0][i] = W >> (s - 8);
+                    for (int q = 0; q < 8; ++q) {
+                        pr[q] = 0;
+                        if (h * 32 + 2 * q < a.Kflat) { // (uniform; a position past K reads some code and meets zero weights)
+                            const v2s two = {*(const short *)(rawb + o[2 * q]), *(const short *)(rawb + o[2 * q + 1])};
+                            pr[q] = __builtin_bit_cast(unsigned, two);
+                            if constexpr (sums) sum = __builtin_amdgcn_sdot2(two, __builtin_bit_cast(v2s, one[q]), sum, false);
                         }
-                        peak = max(max(peak, r[0]), r[1]);
-                        const v2s zero = {0, 0};
-                        const v2s q = __builtin_elementwise_min(__builtin_elementwise_max(__builtin_bit_cast(v2s, __builtin_amdgcn_cvt_pk_i16(r[0], r[1])), zero), top2);
-                        word[g][h] = __builtin_bit_cast(unsigned, q);
-                        nnz = __builtin_bit_cast(unsigned, (v2us)(__builtin_bit_cast(v2us, nnz) + __builtin_elementwise_min(__builtin_bit_cast(v2us, q), __builtin_bit_cast(v2us, one))));
                     }
-                    if constexpr (!POOL)
-                        __builtin_amdgcn_raw_buffer_store_b64((v2u){word[g][0], word[g][1]}, yrsrc, (int)(ch < a.Cout ? rel + (unsigned)ch * 2u : NOWHERE), 0, 0);
-                }
-                if constexpr (POOL) {
-                    unsigned pick[2];
+                    unsigned hi[4], lo[4];
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        v2s b[4];
+                    for (int q = 0; q < 4; ++q) {
+                        hi[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x07050301u);
+                        lo[q] = __builtin_amdgcn_perm(pr[2 * q + 1], pr[2 * q], 0x06040200u) ^ 0x80808080u;
+                    }
+                    ah[h] = v4i{(int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+                    al[h] = v4i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3]};
+                }
+                const int rs = sums ? sum + __shfl_xor(sum, 32, 64) : 0; // a row's two lanes hold different window positions
+                const int rs2 = rs >> 1, odd = (rs & 1) << 7;
+                // outputs: 32-bit offsets from the tile's first pixel
+                const int first = POOL ? (img0 * (a.Ho >> 1) + (yo0 >> 1)) * (a.Wo >> 1) + (x0 >> 1) : fr0 * a.Wo + x0;
+                const int pixels = POOL ? a.N * (a.Ho >> 1) * (a.Wo >> 1) : a.N * a.Ho * a.Wo;
+                const size_t left = (size_t)(pixels - first) * a.Cout * 2;
+                const __amdgpu_buffer_rsrc_t yrsrc = __builtin_amdgcn_make_buffer_rsrc(
+                    (unsigned char *)a.y + (size_t)first * a.Cout * 2, 0, (int)(left < 0x7fffffffu ? left : 0x7fffffffu), 0x00020000);
+                constexpr unsigned NOWHERE = 0x80000000u;
+                const int out = POOL ? (img * (a.Ho >> 1) + (yo >> 1)) * (a.Wo >> 1) + (xo >> 1) : fr * a.Wo + xo;
+                const unsigned rel = ok ? (unsigned)((out - first) * a.Cout * 2) : NOWHERE;
+                unsigned nnz = 0;
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) {
+                    v16i acc[3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
 #pragma unroll
                         for (int g = 0; g < 4; ++g) {
-                            b[g] = __builtin_bit_cast(v2s, word[g][h]);
-                            b[g] = __builtin_elementwise_max(b[g], __builtin_bit_cast(v2s, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, b[g]), 0xB1, 0xF, 0xF, true)));
-                            b[g] = __builtin_elementwise_max(b[g], __builtin_bit_cast(v2s, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, b[g]), 0x4E, 0xF, 0xF, true)));
+                            const v4i c = *(const v4i *)(ctab + q * BN + cb * 32 + 8 * g + 4 * kg);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[q][4 * g + e] = c[e];
                         }
-                        const v2s lo = lane & 1 ? b[1] : b[0], hi = lane & 1 ? b[3] : b[2];
-                        pick[h] = __builtin_bit_cast(unsigned, lane & 2 ? hi : lo);
+#pragma unroll
+                    for (int h = 0; h < KS; ++h) {
+                        const v4i wh = wlds[(h * 2 + 0) * NCB + cb][lane], wl = wlds[(h * 2 + 1) * NCB + cb][lane];
+                        acc[0] = mfma_i8(wh, ah[h], acc[0]);
+                        acc[1] = mfma_i8(wl, ah[h], acc[1]);
+                        acc[2] = mfma_i8(wl, al[h], acc[2]);
+                        acc[1] = mfma_i8(wh, al[h], acc[1]);
                     }
-                    const int ch = cb * 32 + 8 * (lane & 3) + 4 * kg;
-                    __builtin_amdgcn_raw_buffer_store_b64((v2u){pick[0], pick[1]}, yrsrc, (int)(ch < a.Cout ? rel + (unsigned)ch * 2u : NOWHERE), 0, 0);
-                }
-                // clipped values: counted one by one only where there are any
-                if (a.count_sat && __builtin_amdgcn_ballot_w64(peak > cmax)) {
+                    int peak = 0;
+                    unsigned word[4][2] = {};
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
-                        const int most = ok && cb * 32 + 8 * g + 4 * kg < a.Cout ? cmax : 0x7fffffff;
+                        const int ch = cb * 32 + 8 * g + 4 * kg;
+                        if (cb * 32 + 8 * g >= a.Cout) continue; // (uniform)
+                        const unsigned one = ch < a.Cout ? 0x00010001u : 0u; // what a code that exists may add to the count
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) ns += acc[0][4 * g + e] > most;
+                        for (int h = 0; h < 2; ++h) {
+                            int r[2];
+#pragma unroll
+                            for (int e = 0; e < 2; ++e) {
+                                const int i = 4 * g + 2 * h + e;
+                                // floor(v / 256): the dropped low byte cannot carry into a multiple of 256
+                                const int W = (acc[0][i] << 8) + acc[1][i] + (rs2 + ((acc[2][i] + odd) >> 8));
+                                r[e] = acc[0][i] = W >> (s - 8);
+                            }
+                            peak = max(max(peak, r[0]), r[1]);
+                            const v2s zero = {0, 0};
+                            const v2s q = __builtin_elementwise_min(__builtin_elementwise_max(__builtin_bit_cast(v2s, __builtin_amdgcn_cvt_pk_i16(r[0], r[1])), zero), top2);
+                            word[g][h] = __builtin_bit_cast(unsigned, q);
+                            nnz = __builtin_bit_cast(unsigned, (v2us)(__builtin_bit_cast(v2us, nnz) + __builtin_elementwise_min(__builtin_bit_cast(v2us, q), __builtin_bit_cast(v2us, one))));
+                        }
+                        if constexpr (!POOL)
+                            __builtin_amdgcn_raw_buffer_store_b64((v2u){word[g][0], word[g][1]}, yrsrc, (int)(ch < a.Cout ? rel + (unsigned)ch * 2u : NOWHERE), 0, 0);
+                    }
+                    if constexpr (POOL) {
+                        unsigned pick[2];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            v2s b[4];
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) {
+                                b[g] = __builtin_bit_cast(v2s, word[g][h]);
+                                b[g] = __builtin_elementwise_max(b[g], __builtin_bit_cast(v2s, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, b[g]), 0xB1, 0xF, 0xF, true)));
+                                b[g] = __builtin_elementwise_max(b[g], __builtin_bit_cast(v2s, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, b[g]), 0x4E, 0xF, 0xF, true)));
+                            }
+                            const v2s lo = lane & 1 ? b[1] : b[0], hi = lane & 1 ? b[3] : b[2];
+                            pick[h] = __builtin_bit_cast(unsigned, lane & 2 ? hi : lo);
+                        }
+                        const int ch = cb * 32 + 8 * (lane & 3) + 4 * kg;
+                        __builtin_amdgcn_raw_buffer_store_b64((v2u){pick[0], pick[1]}, yrsrc, (int)(ch < a.Cout ? rel + (unsigned)ch * 2u : NOWHERE), 0, 0);
+                    }
+                    // clipped values: counted one by one only where there are any
+                    if (a.count_sat && __builtin_amdgcn_ballot_w64(peak > cmax)) {
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const int most = ok && cb * 32 + 8 * g + 4 * kg < a.Cout ? cmax : 0x7fffffff;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) ns += acc[0][4 * g + e] > most;
+                        }
                     }
                 }
+                nz += ok ? codes - (nnz & 0xffffu) - (nnz >> 16) : 0u;
+                if (wi + 1 < wi_end) {
+                    park(wi + 1, raw[buf ^ 1]);
+                    __syncthreads(); // the next patch is visible (and this one has been read: it is overwritten a tile later)
+                }
             }
-            nz += ok ? codes - (nnz & 0xffffu) - (nnz >> 16) : 0u;
-            if (wi + 1 < wi_end) {
-                park(wi + 1, raw[buf ^ 1]);
-                __syncthreads(); // the next patch is visible (and this one has been read: it is overwritten a tile later)
-            }
-        }
         };
         if (needs_code_sums(a, 0)) run(std::integral_constant<bool, true>{});
         else run(std::integral_constant<bool, false>{});

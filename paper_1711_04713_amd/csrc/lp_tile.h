@@ -227,7 +227,8 @@ __device__ __forceinline__ TileCounts wave_total(TileCounts c)
 
 // LIMBS / WL: 8-bit limbs of the activations and of the weights; LIMBS + WL - 1 accumulator planes, the
 // most significant first (2, 2: HH, HL + LH, LL; 2, 1: H, L; 1, 1: one).
-template <int LIMBS, int WL, int NB, int BN, int MBL, int GL, typename RowSum>
+// PIECES: 8-bit codes may leave in pieces of 16 bytes (below).
+template <int LIMBS, int WL, int NB, int BN, int MBL, int GL, bool PIECES = true, typename RowSum>
 __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&acc)[MBL][NB][LIMBS + WL - 1],
                                                   RowSum row_sum, const int *outoff, const int *pooloff,
                                                   const int *ctab, int ntile, int row0, int col0w, int mb0, int g0)
@@ -480,7 +481,7 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
             if constexpr (decltype(y16c)::value) {
                 if (a.pool) return by_sat(s16c, y16c, integral_constant<int, 1>{});
             }
-            if constexpr (!decltype(y16c)::value && GL == 4) {
+            if constexpr (!decltype(y16c)::value && GL == 4 && PIECES) {
                 if ((a.Cout & 15) == 0) return by_sat(s16c, y16c, integral_constant<int, 3>{});
             }
             if ((a.Cout & 3) == 0) by_sat(s16c, y16c, integral_constant<int, 0>{}); // every group of four channels is aligned

@@ -1640,7 +1640,9 @@ __global__ __launch_bounds__(256)
 //   - rounded values are clipped and packed two at a time;
 //   - with the pool the tile's pixels are dealt to lanes window by window: the maxima are two quad permutations,
 //     and the four lanes of a window store a group of channels each.
-// conv1_1 of VGG16 at batch 32 (12544 tiles) 85 -> 78 us, Giga1Net's 1x1 first layer 53 -> 34, with its pool 50 -> 36.
+// Repeated calls at batch 32 (12544 tiles), together with the epilogue's counting from packed words, which alone is worth about 10:
+// conv1_1 of VGG16 94.6 -> 77.4 us (in traces of the stack, behind the conversion of its input, 88 to 94), Giga1Net's 1x1 first layer
+// 55.6 -> 32.6, with its pool 52.7 -> 34.5.
 constexpr int kFlatSlots = 4;    // workgroups per CU by registers
 constexpr int kFlatUnderWay = 3; // codes of the next patch per thread under way during a tile; those past them (wide windows) come at its end
 template <int NCB, int KS, bool POOL>

@@ -100,8 +100,8 @@ __device__ __forceinline__ void publish_count(const ConvArgs &a, int which, unsi
 // but the constant 128 * sum(b) (the activations' offset): no code sums are gathered, added up or carried along.  bh then
 // is (b + 128) >> 8 and fits a byte for codes below 32640.  A tile of 64 channels takes the signed form unless one of
 // its weights is as large as that (the top 128 codes, where a format that clips weights puts them); bit 0 of its
-// channels' corrections, otherwise multiples of 128, says so.  us, with code sums : without, batch 32: 112x112 128 -> 128
-// 3x3 189.6 : 178.9, 56x56 256 -> 256 185.7 : 177.6, 22x22 64 -> 64 5x5 17.9 : 15.6, 112x112 16 -> 16 7x7 64.5 : 57.5.
+// channels' corrections, otherwise multiples of 128, says so.  us, plain : signed form, batch 32: 112x112 128 -> 128 3x3 192.8 :
+// 185.1, 56x56 256 -> 256 187.2 : 180.0, 28x28 512 -> 512 182.5 : 175.1, 22x22 64 -> 64 5x5 18.1 : 15.5, 112x112 16 -> 16 7x7 45.1 : 40.6.
 constexpr int64_t kSignedForm = 1;
 __device__ __forceinline__ void weight_limbs(int code, bool signed_form, int &hi, int &lo)
 {
@@ -285,8 +285,8 @@ __device__ __forceinline__ TileCounts tile_epilogue(const ConvArgs &a, v16i (&ac
             // 8-bit codes of whole blocks of 32 channels, of tensors whose pixels start on 16-byte boundaries, are stored together.  A lane holds four neighbouring channels of each
             // group of eight, of one pixel: stored as they are, an instruction touches 32 lines with 8 bytes each, and the
             // memory system takes a step per line and instruction.  Swapping halves and rows of lanes between registers
-            // first gives every lane 16 neighbouring bytes, four lanes to a pixel: 64x56x56, 128 -> 256 3x3 69.7 -> 61.7 us,
-            // 256 -> 256 116.4 -> 106.9.  (16-bit codes, twice the bytes per line as they are, gain at most 2 % on large
+            // first gives every lane 16 neighbouring bytes, four lanes to a pixel: with the counting below, 64x56x56, 128 -> 256 3x3
+            // 72.0 -> 62.7 us, 256 -> 256 119.8 -> 109.6.  (16-bit codes, twice the bytes per line as they are, gain at most 2 % on large
             // layers, but small ones then wait for their stores at the end: 18x18, 64 -> 64 batch 32 10.2 -> 10.45 us.  Four 8-bit codes
             // that cannot join such a piece leave as they are made for the same reason: 24x180x9, 192 -> 232 3x3 26.2 us with their
             // stores at the end, 24.6.)

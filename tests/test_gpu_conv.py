@@ -600,6 +600,7 @@ def test_three_wave_groups_per_workgroup(oracle, shape, R, qx, qw, split):
     ((2, 9, 11, 64, 12), 3), ((2, 9, 11, 64, 20), 3), ((1, 13, 13, 32, 48), 3), ((3, 8, 8, 64, 100), 3),   # 64-wide channel tiles
     ((2, 9, 11, 16, 64), 5), ((1, 17, 19, 128, 200), 1),
     ((70, 32, 32, 16, 128), 1), ((70, 32, 32, 16, 120), 1), ((70, 31, 33, 16, 112), 1),                    # 128-wide ones
+    ((1, 28, 28, 256, 512), 3), ((1, 28, 28, 256, 500), 3), ((1, 28, 28, 256, 498), 3),                    # three wave groups
 ])
 @pytest.mark.parametrize("qx,qw,n", [((8, 4, 4), (8, 1, 7), 8), ((16, 4, 12), (16, 1, 15), 16), ((16, 4, 12), (8, 1, 7), 16), ((16, 4, 12), (16, 1, 15), 8)])
 def test_codes_and_counts_of_the_short_epilogue(oracle, shape, k, qx, qw, n):
@@ -618,6 +619,7 @@ def test_codes_and_counts_of_the_short_epilogue(oracle, shape, k, qx, qw, n):
         if not 1 <= f_acc - qy[2] <= 31:
             continue
         got = conv(x, qx, w, qw, qy=qy, pad=k // 2, want_acc=False)
+        assert (got["info"]["lds_bytes"] > 65536) == (Cin == 256)
         y, zeros, sats = oracle.act(acc, f_acc, *qy, True, oracle.ROUND_AWAY, with_sat=True)
         assert np.array_equal(got["y"], y) and (got["zeros"], got["sats"]) == (zeros, sats)
 
